@@ -75,15 +75,26 @@ struct GeneralData {
     cd* w_coll = nullptr;    // collision layout: [l][p][i][k] = w_iklp           (nbp^4)
     cd* w_hf = nullptr;      // mean-field layout: [i][j][l][k] = w^-_ikjl        (nbp^4)
     cd* vt = nullptr;        // scratch: transposed right sandwich                (nbp^4)
-    cd* dmat = nullptr;      // scratch: D = T^dagger - R                         (nbp^4)
+    cd* dmat = nullptr;      // scratch: D = T^dagger - R + pair terms            (nbp^4)
     cd* hhf = nullptr;       // scratch: h^HF of the current stage [nbp][nbp]
     cd* gg = nullptr;        // scratch: G^> of the current stage [nbp][nbp]
     cd* ipart = nullptr;     // scratch: collision-integral partial sums [nbp^2][nipart]
     int nipart = 0;
-    // GW and the ladders: quasi-Hamiltonian and permuted G2 operand of a GEMM
-    cd* heps = nullptr;      // GW: [(p,q)][(j,l)] = h^eps_qjpl; ladders: h^pp, h^ph (nbp^4)
-    cd* bmat = nullptr;      // GW: [(i,k)][(p,q)] = G2_ipkq; ladders: see gen_bmat  (nbp^4)
-    cd* pimat = nullptr;     // Pi_ijkl at [i][j][k][l], then at [l][k][j][i]       (2 nbp^4)
+    // GW and the ladders (pair.hip): operands of the reduced pair products, in
+    // binary64 or (mixed) binary32, over the nb^2 pairs and zero beyond them
+    int* pt = nullptr;       // pair number -> p | q << 16, p < q
+    unsigned long long* pstat = nullptr;   // max |exchange-odd part| and max |G2| of the stage input
+    double* pdd = nullptr;   // GW: the polarization's real elements (ii,jj) [nb][nb]
+    int pld = 0, plds = 0, plda = 0;   // row lengths: nb^2, nb (nb+1)/2, nb (nb-1)/2 rounded up
+    void* px[2] = {};        // GW, TPH: G2 as a real pair map [pld][pld]
+    void* py[2] = {};        // GW, TPH: h^eps, h^ph as real pair maps [pld][pld]
+    void* pxo = nullptr;     // TPH: the exchange-odd part of G2 [pld][pld]
+    void* phs = nullptr;     // TPP: h^pp on exchange-even pairs [plds][plds], complex
+    void* pha = nullptr;     // TPP: h^pp on exchange-odd pairs [plda][plda]
+    void* pgs = nullptr;     // TPP: G2 between even pairs [plds][plds]
+    void* pga = nullptr;     // TPP: G2 between odd pairs [plda][plda]
+    void* pgso = nullptr;    // TPP: G2, even rows and odd columns [plds][plda]
+    void* pgao = nullptr;    // TPP: G2, odd rows and even columns [plda][plds]
     cd* w_gw = nullptr;      // GW layout: [p][q][s][r] = w_sqrp                   (nbp^4)
     cd* w_pp = nullptr;      // TPP layout: [k][l][p][q] = w_pqkl                  (nbp^4)
     cd* w_ph = nullptr;      // TPH layout: [j][k][p][q] = w_pjkq                  (nbp^4)
@@ -210,6 +221,11 @@ g1g2_status gen_observables(g1g2_ctx* c, const Regs& s, double t, g1g2_obs* o);
 g1g2_status gen_pad(g1g2_ctx* c, const cd* src_dev, cd* dst_dev, int rank);
 g1g2_status gen_unpad(g1g2_ctx* c, const cd* src_dev, cd* dst_dev, int rank);
 void gen_free(g1g2_ctx* c);
+// the polarization and ladder terms (pair.hip): buffers, one stage's terms added
+// into D, release
+g1g2_status pair_setup(g1g2_ctx* c, bool gw, bool pp, bool ph);
+g1g2_status pair_add(g1g2_ctx* c, const Regs& in, double ws);
+void pair_free(g1g2_ctx* c);
 
 // ---- jellium (jellium.hip)
 int jel_max_nb();

@@ -19,12 +19,8 @@
 // from the same row blocks.  gen_combine forms -i (D - D^dagger) with an
 // LDS-tiled pair transpose and applies the Runge-Kutta register update.
 //
-// GW (eq:g2-eq-gw-pi) adds Pi - [Pi_lkji]^*, Pi_ijkl = sum_pq h^eps_qjpl G2_ipkq
-// (eq:gwpi), evaluated as one (nbp^2)^3 complex GEMM
-//     Pi[(i,k)][(j,l)] = sum_(p,q) B[(i,k)][(p,q)] H[(p,q)][(j,l)],
-//     B[(i,k)][(p,q)] = G2_ipkq,   H[(p,q)][(j,l)] = h^eps_qjpl,
-// with h^eps (eq:gwhcorr) built per (p,q) block as H_pq = i [G<, M_pq],
-// M_pq[s][r] = w_sqrp (G^> = G^< - i 1 removes the G<...G< terms).
+// The polarization and the ladders of GW, the T matrices and DSL are added into
+// D before the combine (pair.hip).
 #include <algorithm>
 #include <cmath>
 #include <cstring>
@@ -32,52 +28,10 @@
 #include <vector>
 
 #include "ctx.h"
+#include "gen_common.h"
 #include "mfma.h"
 
 namespace {
-
-template <int NB>
-struct Shape {
-    static constexpr int NT = NB / 16;
-    static constexpr int TILES = NT * NT;
-    static constexpr int WAVES = (TILES % 4 == 0) ? 4 : ((TILES % 3 == 0) ? 3 : 1);
-    static constexpr int TPW = TILES / WAVES;
-    static constexpr int THREADS = 64 * WAVES;
-    static constexpr int LD = NB + 1;
-};
-
-template <typename T>
-__device__ __forceinline__ void ldc(const cd* p, T& r, T& i) {
-    cd v = *p;
-    r = (T)v.x;
-    i = (T)v.y;
-}
-template <typename T>
-__device__ __forceinline__ void ldc(const float2* p, T& r, T& i) {
-    float2 v = *p;
-    r = (T)v.x;
-    i = (T)v.y;
-}
-__device__ __forceinline__ void stc(cd* p, double r, double i) { *p = make_double2(r, i); }
-__device__ __forceinline__ void stc(float2* p, double r, double i) { *p = make_float2((float)r, (float)i); }
-
-// Work-groups are dispatched round-robin over the 8 XCDs (each with its own
-// L2).  Logical block b of a grid of g work-groups (g a multiple of 8) is
-// mapped so that each XCD owns a contiguous range of logical blocks, which
-// keeps neighbouring blocks (adjacent output lines) in one L2.
-__device__ __forceinline__ int xcd_block(int b, int g) { return (b & 7) * (g >> 3) + (b >> 3); }
-
-template <typename T, typename S, int NB>
-__device__ __forceinline__ void stage_block(const S* __restrict__ src, T* re, T* im) {
-    constexpr int LD = Shape<NB>::LD;
-    for (int idx = threadIdx.x; idx < NB * NB; idx += blockDim.x) {
-        int r = idx / NB, c = idx % NB;
-        T a, b;
-        ldc(src + idx, a, b);
-        re[r * LD + c] = a;
-        im[r * LD + c] = b;
-    }
-}
 
 // --------------------------------------------------------------------------- K1
 // h^HF_ij = h0_ij - i sum_kl w^-_ikjl G^<_lk (eq:h_HF) and G^> = G^< - i 1.
@@ -372,23 +326,10 @@ struct SmallOps {
     T h_re[STAGE ? NB * LD : 1], h_im[STAGE ? NB * LD : 1];
 };
 
-// Nb = 64 runs eight waves of two tiles instead of four waves of four.  In
-// gen_main (one work-group per compute unit) that is two waves per SIMD: 0.82
-// instead of 1.11 ms per launch in binary64; holding a wave's rows of G> in
-// registers as well gained nothing in binary64 and lost in binary32.  In
-// gen_heps (two work-groups per compute unit) it is 0.30 instead of 0.36 ms;
-// gen_hlad (one work-group per compute unit) takes the same shape.
-template <int NB>
-struct MainShape : Shape<NB> {
-    static constexpr int WAVES = NB == 64 ? 8 : Shape<NB>::WAVES;
-    static constexpr int TPW = Shape<NB>::TILES / WAVES;
-    static constexpr int THREADS = 64 * WAVES;
-};
-
-template <typename T, typename S, int NB>
+template <typename T, typename S, typename DS, int NB>
 __global__ __launch_bounds__(MainShape<NB>::THREADS) void gen_main_kernel(
     const cd* __restrict__ g2, const S* __restrict__ vt, const S* __restrict__ wcoll,
-    const cd* __restrict__ gg, const cd* __restrict__ hhf, S* __restrict__ dout,
+    const cd* __restrict__ gg, const cd* __restrict__ hhf, DS* __restrict__ dout,
     cd* __restrict__ ipart, double ws) {
     typedef MainShape<NB> SH;
     constexpr int LD = SH::LD;
@@ -624,15 +565,16 @@ __device__ __forceinline__ void g1_pair(const G1Args& g, int i, int j, int lane,
 }
 
 // --------------------------------------------------------------------------- K4
-// dG2 = -i (D - D^dagger) [+ -i (Pi - conj(Pi_lkji)) for GW], fused RK4 update;
+// dG2 = -i (D - D^dagger), fused RK4 update; for GW and DSL the polarization's
+// elements X_ijij = i (dd_ij + dd_ji), their own partners, enter here;
 // the G1 equation (K5) on the same launch, in work-groups of its own, so that
 // the latency of its partial-sum reads overlaps the G2 streaming.
-template <int MODE, typename S, bool GW>
+template <int MODE, typename S>
 __global__ __launch_bounds__(256) void gen_combine_kernel(const S* __restrict__ D, int n,
                                                          const cd* __restrict__ in,
                                                          const cd* __restrict__ y,
                                                          cd* __restrict__ acc, cd* __restrict__ out,
-                                                         const cd* __restrict__ pim, int nbp,
+                                                         const double* __restrict__ dd, int nbp,
                                                          double cb, double cc, G1Args g1, int ng1) {
     __shared__ double t1r[32][33], t1i[32][33], t2r[32][33], t2i[32][33];
     auto tri = [](int t, int& hi, int& lo) {   // t = hi (hi + 1) / 2 + lo, lo <= hi
@@ -673,11 +615,9 @@ __global__ __launch_bounds__(256) void gen_combine_kernel(const S* __restrict__ 
     __syncthreads();
     auto update = [&](int row, int col, double zr, double zi) {
         const size_t e = (size_t)row * n + col;
-        if (GW) {   // Pi_ijkl and the partner Pi_lkji, both stored at e (see gen_gemm)
-            cd p1 = pim[e];
-            cd p2 = pim[(size_t)n * n + e];
-            zr += p1.x - p2.x;
-            zi += p1.y + p2.y;
+        if (dd && row == col) {
+            const int i = row / nbp, j = row % nbp, nb = g1.nb;
+            if (i < nb && j < nb) zi += dd[i * nb + j] + dd[j * nb + i];
         }
         cd f = make_double2(zi, -zr);  // -i z
         cd yin = make_double2(0.0, 0.0);
@@ -689,319 +629,6 @@ __global__ __launch_bounds__(256) void gen_combine_kernel(const S* __restrict__ 
         update(by * 32 + r, bx * 32 + tx, t1r[r][tx] - t2r[tx][r], t1i[r][tx] + t2i[tx][r]);
         if (bx != by) update(bx * 32 + r, by * 32 + tx, t2r[r][tx] - t1r[tx][r], t2i[r][tx] + t1i[tx][r]);
     }
-}
-
-// --------------------------------------------------------------------------- GW kernels
-// H[(p,q)][(j,l)] = h^eps_qjpl = i (G< M_pq - M_pq G<)[j][l], M_pq[s][r] = w_sqrp.
-template <typename T, typename S, int NB>
-__global__ __launch_bounds__(MainShape<NB>::THREADS) void gen_heps_kernel(const S* __restrict__ wgw,
-                                                                     const cd* __restrict__ gl,
-                                                                     S* __restrict__ heps, double ws) {
-    typedef MainShape<NB> SH;
-    constexpr int LD = SH::LD;
-    __shared__ T m_re[NB * LD], m_im[NB * LD];
-    const int wave = threadIdx.x >> 6;
-    for (int blk = blockIdx.x; blk < NB * NB; blk += gridDim.x) {
-        stage_block<T, S, NB>(wgw + (size_t)blk * NB * NB, m_re, m_im);
-        __syncthreads();
-        for (int t = 0; t < SH::TPW; ++t) {
-            const int tile = wave * SH::TPW + t, ti = tile / SH::NT, tj = tile % SH::NT;
-            CAcc<T> acc;
-            acc.clear();
-            cgemm_tile<T, NB>(
-                acc, [&](int i, int k, T& r, T& m) { ldc(gl + i * NB + k, r, m); },
-                [&](int k, int j, T& r, T& m) {
-                    r = m_re[k * LD + j];
-                    m = m_im[k * LD + j];
-                },
-                ti * 16, tj * 16);
-            cgemm_tile<T, NB>(
-                acc,
-                [&](int i, int k, T& r, T& m) {
-                    r = -m_re[i * LD + k];
-                    m = -m_im[i * LD + k];
-                },
-                [&](int k, int j, T& r, T& m) { ldc(gl + k * NB + j, r, m); }, ti * 16, tj * 16);
-#pragma unroll
-            for (int r4 = 0; r4 < 4; ++r4) {
-                int row = ti * 16 + tile_row<T>(r4), col = tj * 16 + tile_col();
-                // i * acc
-                stc(heps + (size_t)blk * NB * NB + row * NB + col, -ws * (double)acc.im(r4),
-                    ws * (double)acc.re(r4));
-            }
-        }
-        __syncthreads();
-    }
-}
-
-// B[(i,k)][(p,q)] = G2_ipkq
-// Quasi-Hamiltonians of the two T-matrix ladders, one column-pair block of
-// the interaction at a time (G^> = G^< - i):
-//   KIND 0, eq:HTPPcorr:  h^pp_ijkl = -sum_pq (G>_ip G>_jq - G<_ip G<_jq) w_pqkl
-//                         = [-(G> M G>^T) + (G< M G<^T)]_ij,  M_pq = w_pqkl, block (k,l)
-//   KIND 1, eq:HTPHcorr:  h^ph_ijkl = -sum_pq (G>_ip G<_ql - G<_ip G>_ql) w_pjkq
-//                         = [-(G> M G<) + (G< M G>)]_il,      M_pq = w_pjkq, block (j,k)
-// wl holds the blocks M contiguously (w_pp / w_ph layouts).  The NB x NB
-// result (r, c) of block blk is stored at out[(r NB + c) NB^2 + blk], which is
-// h^pp as the pair matrix [(ij)][(kl)]; h^ph, the left GEMM operand of
-// Lambda^ph_ijkl = sum_pq h^ph_ipql G2_qjkp (eq:lambdaph), is stored with its
-// column pair swapped, [(il)][(kj)]: the product runs over K = (q, p), so that
-// its right operand G2_qjkp is contiguous along the inner index p.
-template <typename T, typename S, int NB, int KIND>
-__global__ __launch_bounds__(MainShape<NB>::THREADS) void gen_hlad_kernel(const S* __restrict__ wl,
-                                                                     const cd* __restrict__ gl,
-                                                                     const cd* __restrict__ gg,
-                                                                     S* __restrict__ out, double ws) {
-    typedef MainShape<NB> SH;
-    constexpr int LD = SH::LD;
-    __shared__ T m_re[NB * LD], m_im[NB * LD], q_re[NB * LD], q_im[NB * LD];
-    const int wave = threadIdx.x >> 6;
-    const int b0 = xcd_block(blockIdx.x, gridDim.x);
-    auto Ggt = [&](int i, int k, T& r, T& m) { ldc(gg + i * NB + k, r, m); };   // G>[i][k]
-    auto Glt = [&](int i, int k, T& r, T& m) { ldc(gl + i * NB + k, r, m); };   // G<[i][k]
-    auto Mop = [&](int k, int j, T& r, T& m) {
-        r = m_re[k * LD + j];
-        m = m_im[k * LD + j];
-    };
-    auto Qop = [&](int i, int k, T& r, T& m) {
-        r = q_re[i * LD + k];
-        m = q_im[i * LD + k];
-    };
-    for (int blk = b0; blk < NB * NB; blk += gridDim.x) {
-        stage_block<T, S, NB>(wl + (size_t)blk * NB * NB, m_re, m_im);
-        __syncthreads();
-        CAcc<T> acc[SH::TPW];
-#pragma unroll
-        for (int t = 0; t < SH::TPW; ++t) acc[t].clear();
-#pragma unroll
-        for (int half = 0; half < 2; ++half) {
-            // q = -G> M (half 0) or +G< M (half 1)
-#pragma unroll
-            for (int t = 0; t < SH::TPW; ++t) {
-                const int tile = wave * SH::TPW + t, ti = tile / SH::NT, tj = tile % SH::NT;
-                CAcc<T> p;
-                p.clear();
-                if (half == 0) cgemm_tile<T, NB>(p, Ggt, Mop, ti * 16, tj * 16);
-                else cgemm_tile<T, NB>(p, Glt, Mop, ti * 16, tj * 16);
-                const T sg = half == 0 ? (T)-1 : (T)1;
-#pragma unroll
-                for (int r4 = 0; r4 < 4; ++r4) {
-                    int row = ti * 16 + tile_row<T>(r4), col = tj * 16 + tile_col();
-                    q_re[row * LD + col] = sg * p.re(r4);
-                    q_im[row * LD + col] = sg * p.im(r4);
-                }
-            }
-            __syncthreads();
-            // acc += q R:  pp R = G>^T (half 0), G<^T (half 1);  ph R = G< (half 0), G> (half 1)
-#pragma unroll
-            for (int t = 0; t < SH::TPW; ++t) {
-                const int tile = wave * SH::TPW + t, ti = tile / SH::NT, tj = tile % SH::NT;
-                if (KIND == 0) {
-                    if (half == 0) cgemm_tile<T, NB>(acc[t], Qop, [&](int k, int j, T& r, T& m) { Ggt(j, k, r, m); }, ti * 16, tj * 16);
-                    else cgemm_tile<T, NB>(acc[t], Qop, [&](int k, int j, T& r, T& m) { Glt(j, k, r, m); }, ti * 16, tj * 16);
-                } else {
-                    if (half == 0) cgemm_tile<T, NB>(acc[t], Qop, Glt, ti * 16, tj * 16);
-                    else cgemm_tile<T, NB>(acc[t], Qop, Ggt, ti * 16, tj * 16);
-                }
-            }
-            __syncthreads();
-        }
-#pragma unroll
-        for (int t = 0; t < SH::TPW; ++t) {
-            const int tile = wave * SH::TPW + t, ti = tile / SH::NT, tj = tile % SH::NT;
-#pragma unroll
-            for (int r4 = 0; r4 < 4; ++r4) {
-                int row = ti * 16 + tile_row<T>(r4), col = tj * 16 + tile_col();
-                stc(out + (size_t)(row * NB + col) * NB * NB + (KIND == 1 ? (blk % NB) * NB + blk / NB : blk),
-                    ws * acc[t].re(r4), ws * acc[t].im(r4));
-            }
-        }
-    }
-}
-
-// Permuted copy of G2 as a GEMM operand (the left one of the GW product, the
-// right one of the ladder products):
-//   MODE 0 (GW):   b[(i,k)][(p,q)] = G2_ipkq
-//   MODE 1 (TPP):  b[(p,q)][(k,l)] = G2_pqkl
-//   MODE 2 (TPH):  b[(q,p)][(j,k)] = G2_qjkp   (the TPH product runs over K = (q, p))
-// The binary64 products read G2 in place, so these copies are made for the
-// binary32 operands only.
-template <typename S, int MODE>
-__global__ __launch_bounds__(256) void gen_bmat_kernel(const cd* __restrict__ g2, S* __restrict__ b,
-                                                      int nbp) {
-    const size_t n4 = (size_t)nbp * nbp * nbp * nbp;
-    for (size_t e = blockIdx.x * (size_t)blockDim.x + threadIdx.x; e < n4;
-         e += (size_t)gridDim.x * blockDim.x) {
-        size_t x3 = e % nbp, t = e / nbp;
-        size_t x2 = t % nbp;
-        t /= nbp;
-        size_t x1 = t % nbp, x0 = t / nbp;
-        size_t src;
-        if (MODE == 0) src = ((x0 * nbp + x2) * nbp + x1) * nbp + x3;        // (i,k,p,q) <- G2_ipkq
-        else if (MODE == 1) src = e;
-        else src = ((x0 * nbp + x2) * nbp + x3) * nbp + x1;                  // (q,p,j,k) <- G2_qjkp
-        cd v = g2[src];
-        stc(b + e, v.x, v.y);
-    }
-}
-
-// Pi[(i,k)][(j,l)] = sum_K B[(i,k)][K] H[K][(j,l)], stored as pim[i][j][k][l].
-// 64x64 output tile per work-group, four waves of 32x32, K staged in slices of 16.
-// With T = float the products are accumulated in binary32 over 64-deep chunks
-// and the chunk sums are added in binary64 (chunked compensated summation).
-// OUT selects the epilogue:
-//   0 (GW):  pim[i][j][k][l] = C[(i,k)][(j,l)], and the same value at
-//            pim[n^2 + ((l nbp + k) nbp + j) nbp + i]          (binary64 buffer)
-//   1 (TPP): D[(i,j)][(k,l)] += C[(i,j)][(k,l)]               (D in storage S)
-//   2 (TPH): D[(i,j)][(k,l)] += C[(i,l)][(j,k)]
-// AG2 reads the GW operand B[(i,k)][(p,q)] = G2_ipkq in place from the binary64
-// G2 instead of a permuted copy: within a K slice p = k0 / nbp is uniform and q
-// runs over 16 consecutive values, so the loads keep their 256-byte rows.
-// BG2T reads the TPH operand B[(q,p)][(j,k)] = G2_qjkp in place, at
-// q nbp^3 + (j nbp + k) nbp + p: a K slice is one q and 16 consecutive p, so a
-// column's 16 values are one 256-byte row; they are stored to LDS transposed.
-template <typename T, typename S, int OUT, bool AG2 = false, bool BG2T = false>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2)))
-void gen_gemm_kernel(const S* __restrict__ A, const S* __restrict__ B,
-                                                      void* __restrict__ dst, int n, int nbp) {
-    constexpr int KS = 16;                    // depth of one staged K slice
-    constexpr int PER = 64 * KS / 256;          // elements of A (and of B) per thread and slice
-    // three real products per complex multiply-add instead of four,
-    //   Re = Ar Br - Ai Bi,  Im = (Ar + Ai)(Br + Bi) - Ar Br - Ai Bi;
-    // the operand sums are formed from the values read for the first two
-    // products (one add per operand and MFMA step) rather than staged in LDS.
-    // The slices are kept as interleaved complex values, so an operand pair is
-    // one 16-byte (binary64) or 8-byte LDS access.  Measured per Nb = 64
-    // launch in binary64: split re/im arrays with staged sums (51 KB) 6.85 ms,
-    // without the sums (34 KB) 6.42 ms, interleaved (34 KB) 6.27 ms; a 32-deep
-    // slice or a second LDS buffer was slower
-    typedef typename std::conditional<sizeof(T) == 8, double2, float2>::type CT;
-    __shared__ CT a_c[64][KS + 1];
-    __shared__ CT b_c[KS][65];
-    const int bm = blockIdx.y * 64, bn = blockIdx.x * 64;
-    const int wave = threadIdx.x >> 6;
-    const int wm = (wave >> 1) * 32, wn = (wave & 1) * 32;
-    double accd[2][2][2][4];
-    typename MF<T>::acc p1[2][2], p2[2][2], p3[2][2];   // Ar Br, Ai Bi, (Ar + Ai)(Br + Bi)
-    for (int a = 0; a < 2; ++a)
-        for (int b = 0; b < 2; ++b) {
-            p1[a][b] = p2[a][b] = p3[a][b] = MF<T>::zero();
-            for (int r4 = 0; r4 < 4; ++r4) accd[a][b][0][r4] = accd[a][b][1][r4] = 0.0;
-        }
-    // the next K slice is loaded into registers while the current one runs
-    T pa_re[PER], pa_im[PER], pb_re[PER], pb_im[PER];
-    size_t arow[PER];   // AG2: the (i, k) part i nbp^3 + k nbp of each A row's G2 index
-#pragma unroll
-    for (int q = 0; q < PER; ++q) {
-        const int row = bm + (threadIdx.x + q * 256) / KS;
-        arow[q] = AG2 ? ((size_t)(row / nbp) * nbp * nbp + row % nbp) * nbp : (size_t)row * n;
-    }
-    auto fetch = [&](int k0) {
-        const size_t acol = AG2 ? (size_t)(k0 / nbp) * nbp * nbp + k0 % nbp : (size_t)k0;
-        const size_t bq = (size_t)(k0 / nbp) * nbp * nbp * nbp + k0 % nbp;   // BG2T
-#pragma unroll
-        for (int q = 0; q < PER; ++q) {
-            const int idx = threadIdx.x + q * 256;
-            ldc(A + arow[q] + acol + idx % KS, pa_re[q], pa_im[q]);
-            if (BG2T)
-                ldc(B + bq + (size_t)(bn + idx / KS) * nbp + idx % KS, pb_re[q], pb_im[q]);
-            else
-                ldc(B + (size_t)(k0 + idx / 64) * n + bn + idx % 64, pb_re[q], pb_im[q]);
-        }
-    };
-    fetch(0);
-    for (int k0 = 0; k0 < n; k0 += KS) {
-#pragma unroll
-        for (int q = 0; q < PER; ++q) {
-            const int idx = threadIdx.x + q * 256;
-            a_c[idx / KS][idx % KS] = CT{pa_re[q], pa_im[q]};
-            if (BG2T)
-                b_c[idx % KS][idx / KS] = CT{pb_re[q], pb_im[q]};
-            else
-                b_c[idx / 64][idx % 64] = CT{pb_re[q], pb_im[q]};
-        }
-        __syncthreads();
-        if (k0 + KS < n) fetch(k0 + KS);
-        // the wave issues its matrix-core work at raised priority, so that of the
-        // two work-groups on a compute unit the one past its barrier goes first
-        // (0.5% in binary64, 1% in binary32)
-        __builtin_amdgcn_s_setprio(1);
-        {
-            const int lane = threadIdx.x & 63, li = lane & 15, lk = lane >> 4;
-#pragma unroll
-            for (int k4 = 0; k4 < KS; k4 += 4) {
-                T ar[2], ai[2], as[2], br[2], bi[2], bs[2];
-#pragma unroll
-                for (int a = 0; a < 2; ++a) {
-                    const int i = wm + a * 16 + li;
-                    const CT v = a_c[i][k4 + lk];
-                    ar[a] = v.x;
-                    ai[a] = v.y;
-                    as[a] = ar[a] + ai[a];
-                }
-#pragma unroll
-                for (int b = 0; b < 2; ++b) {
-                    const int j = wn + b * 16 + li;
-                    const CT v = b_c[k4 + lk][j];
-                    br[b] = v.x;
-                    bi[b] = v.y;
-                    bs[b] = br[b] + bi[b];
-                }
-#pragma unroll
-                for (int a = 0; a < 2; ++a)
-#pragma unroll
-                    for (int b = 0; b < 2; ++b) {
-                        p1[a][b] = MF<T>::mac(ar[a], br[b], p1[a][b]);
-                        p2[a][b] = MF<T>::mac(ai[a], bi[b], p2[a][b]);
-                        p3[a][b] = MF<T>::mac(as[a], bs[b], p3[a][b]);
-                    }
-            }
-        }
-        __builtin_amdgcn_s_setprio(0);
-        __syncthreads();
-        if (sizeof(T) == 4 && ((k0 + KS) % 64 == 0 || k0 + KS >= n)) {
-            for (int a = 0; a < 2; ++a)
-                for (int b = 0; b < 2; ++b) {
-                    for (int r4 = 0; r4 < 4; ++r4) {
-                        const double d1 = p1[a][b][r4], d2 = p2[a][b][r4], d3 = p3[a][b][r4];
-                        accd[a][b][0][r4] += d1 - d2;
-                        accd[a][b][1][r4] += d3 - d1 - d2;
-                    }
-                    p1[a][b] = p2[a][b] = p3[a][b] = MF<T>::zero();
-                }
-        }
-    }
-    for (int a = 0; a < 2; ++a)
-        for (int b = 0; b < 2; ++b)
-#pragma unroll
-            for (int r4 = 0; r4 < 4; ++r4) {
-                const int row = bm + wm + a * 16 + tile_row<T>(r4);
-                const int col = bn + wn + b * 16 + tile_col();
-                const double vr = sizeof(T) == 4 ? accd[a][b][0][r4] : (double)(p1[a][b][r4] - p2[a][b][r4]);
-                const double vi = sizeof(T) == 4 ? accd[a][b][1][r4]
-                                                 : (double)(p3[a][b][r4] - p1[a][b][r4] - p2[a][b][r4]);
-                if (OUT == 0) {
-                    // Pi_ijkl at [i][j][k][l] and, for the partner term of the
-                    // combine, again at [l][k][j][i] of a second n x n array: the
-                    // scatter costs this matrix-core-bound kernel 0.06 ms and
-                    // spares the memory-bound combine a gather (0.47 -> 0.36 ms)
-                    const int i = row / nbp, k = row % nbp, j = col / nbp, l = col % nbp;
-                    ((cd*)dst)[(((size_t)i * nbp + j) * nbp + k) * nbp + l] = make_double2(vr, vi);
-                    ((cd*)dst)[(size_t)n * n + (((size_t)l * nbp + k) * nbp + j) * nbp + i] = make_double2(vr, vi);
-                } else {
-                    size_t e;
-                    if (OUT == 1) {
-                        e = (size_t)row * n + col;
-                    } else {
-                        const int i = row / nbp, l = row % nbp, j = col / nbp, k = col % nbp;
-                        e = (((size_t)i * nbp + j) * nbp + k) * nbp + l;
-                    }
-                    S* D = (S*)dst;
-                    T dr, di;
-                    ldc(D + e, dr, di);
-                    stc(D + e, (double)dr + vr, (double)di + vi);
-                }
-            }
 }
 
 // --------------------------------------------------------------------------- layout helpers
@@ -1108,7 +735,7 @@ int main_grid(int nbp) { return std::min(nbp * nbp, 512); }
 
 // ws: the switching factor phi(t) of the stage; every w-dependent output
 // (sandwich, h^HF, collision partials, quasi-Hamiltonians) is linear in w
-template <typename T, typename S, int NB>
+template <typename T, typename S, typename DS, int NB>
 g1g2_status run_blocks(g1g2_ctx* c, const Regs& in, double ws) {
     GeneralData& g = c->gen;
     const bool mixed = sizeof(T) == 4;
@@ -1122,70 +749,11 @@ g1g2_status run_blocks(g1g2_ctx* c, const Regs& in, double ws) {
                        c->stream, wrows, in.g1, (S*)g.vt, grid_vt, hf);
     HIP_OK(c, hipGetLastError());
     prof_mark(c, "gen_vt");
-    const int se = c->d.selfenergy;
-    const int n = NB * NB;
-    if (se == G1G2_GW || se == G1G2_DSL) {
-        const S* wgw = mixed ? (const S*)g.w_gw32 : (const S*)g.w_gw;
-        hipLaunchKernelGGL((gen_heps_kernel<T, S, NB>), dim3(grid_vt), dim3(MainShape<NB>::THREADS), 0,
-                           c->stream, wgw, in.g1, (S*)g.heps, ws);
-        HIP_OK(c, hipGetLastError());
-        prof_mark(c, "gen_heps");
-        if constexpr (std::is_same<S, cd>::value) {   // binary64: the G2 operand is read in place
-            hipLaunchKernelGGL((gen_gemm_kernel<T, S, 0, true>), dim3(n / 64, n / 64), dim3(256), 0, c->stream,
-                               (const S*)in.g2, (const S*)g.heps, (void*)g.pimat, n, NB);
-        } else {                                      // binary32: from a permuted binary32 copy
-            hipLaunchKernelGGL((gen_bmat_kernel<S, 0>), dim3(2048), dim3(256), 0, c->stream, in.g2,
-                               (S*)g.bmat, NB);
-            HIP_OK(c, hipGetLastError());
-            prof_mark(c, "gen_bmat");
-            hipLaunchKernelGGL((gen_gemm_kernel<T, S, 0>), dim3(n / 64, n / 64), dim3(256), 0, c->stream,
-                               (const S*)g.bmat, (const S*)g.heps, (void*)g.pimat, n, NB);
-        }
-        HIP_OK(c, hipGetLastError());
-        prof_mark(c, "gen_gemm");
-    }
-    hipLaunchKernelGGL((gen_main_kernel<T, S, NB>), dim3(g.nipart), dim3(MainShape<NB>::THREADS), 0,
-                       c->stream, in.g2, (const S*)g.vt, wcoll, g.gg, g.hhf, (S*)g.dmat, g.ipart, ws);
+    hipLaunchKernelGGL((gen_main_kernel<T, S, DS, NB>), dim3(g.nipart), dim3(MainShape<NB>::THREADS), 0,
+                       c->stream, in.g2, (const S*)g.vt, wcoll, g.gg, g.hhf, (DS*)g.dmat, g.ipart, ws);
     HIP_OK(c, hipGetLastError());
     prof_mark(c, "gen_main");
-    // T-matrix ladders: D += Lambda, so that the combine forms Lambda - Lambda^dagger,
-    // the partner [Lambda_klij]^* of eq:g2-eq-tpp-lambda / eq:g2-eq-tph-lambda
-    if (se == G1G2_TPP || se == G1G2_DSL) {
-        const S* wpp = mixed ? (const S*)g.w_pp32 : (const S*)g.w_pp;
-        hipLaunchKernelGGL((gen_hlad_kernel<T, S, NB, 0>), dim3(grid_vt), dim3(MainShape<NB>::THREADS), 0,
-                           c->stream, wpp, in.g1, g.gg, (S*)g.heps, ws);
-        // the TPP operand is G2 itself: binary64 reads it in place, binary32 from a copy
-        const S* g2op = (const S*)g.bmat;
-        if constexpr (std::is_same<S, cd>::value) g2op = (const S*)in.g2;
-        else hipLaunchKernelGGL((gen_bmat_kernel<S, 1>), dim3(2048), dim3(256), 0, c->stream, in.g2,
-                                (S*)g.bmat, NB);
-        HIP_OK(c, hipGetLastError());
-        prof_mark(c, "gen_hlad");
-        hipLaunchKernelGGL((gen_gemm_kernel<T, S, 1>), dim3(n / 64, n / 64), dim3(256), 0, c->stream,
-                           (const S*)g.heps, g2op, (void*)g.dmat, n, NB);
-        HIP_OK(c, hipGetLastError());
-        prof_mark(c, "gen_gemm");
-    }
-    if (se == G1G2_TPH || se == G1G2_DSL) {
-        const S* wph = mixed ? (const S*)g.w_ph32 : (const S*)g.w_ph;
-        hipLaunchKernelGGL((gen_hlad_kernel<T, S, NB, 1>), dim3(grid_vt), dim3(MainShape<NB>::THREADS), 0,
-                           c->stream, wph, in.g1, g.gg, (S*)g.heps, ws);
-        // the TPH operand G2_qjkp: binary64 reads it in place, binary32 from a copy
-        if constexpr (!std::is_same<S, cd>::value)
-            hipLaunchKernelGGL((gen_bmat_kernel<S, 2>), dim3(2048), dim3(256), 0, c->stream, in.g2,
-                               (S*)g.bmat, NB);
-        HIP_OK(c, hipGetLastError());
-        prof_mark(c, "gen_hlad");
-        if constexpr (std::is_same<S, cd>::value)
-            hipLaunchKernelGGL((gen_gemm_kernel<T, S, 2, false, true>), dim3(n / 64, n / 64), dim3(256), 0,
-                               c->stream, (const S*)g.heps, (const S*)in.g2, (void*)g.dmat, n, NB);
-        else
-            hipLaunchKernelGGL((gen_gemm_kernel<T, S, 2>), dim3(n / 64, n / 64), dim3(256), 0, c->stream,
-                               (const S*)g.heps, (const S*)g.bmat, (void*)g.dmat, n, NB);
-        HIP_OK(c, hipGetLastError());
-        prof_mark(c, "gen_gemm");
-    }
-    return G1G2_OK;
+    return c->d.selfenergy == G1G2_SOA ? G1G2_OK : pair_add(c, in, ws);
 }
 
 template <typename S, int MODE>
@@ -1197,24 +765,20 @@ g1g2_status run_combine(g1g2_ctx* c, const Regs& in, const Regs& y, const Regs& 
     const G1Args g1{g.ipart, g.nipart, g.hhf, in.g1, y.g1, acc.g1, out.g1,
                     g.icoll, g.nb, guard_of(c)};
     const int ng1 = (g.nbp * (g.nbp + 1) / 2 + 3) / 4;   // work-groups of the G1 pairs
-    if (c->d.selfenergy == G1G2_GW || c->d.selfenergy == G1G2_DSL)
-        hipLaunchKernelGGL((gen_combine_kernel<MODE, S, true>), dim3(ng1 + ntiles), dim3(256), 0, c->stream,
-                           (const S*)g.dmat, n, in.g2, y.g2, acc.g2, out.g2, g.pimat, g.nbp, cb, cc, g1, ng1);
-    else
-        hipLaunchKernelGGL((gen_combine_kernel<MODE, S, false>), dim3(ng1 + ntiles), dim3(256), 0, c->stream,
-                           (const S*)g.dmat, n, in.g2, y.g2, acc.g2, out.g2, g.pimat, g.nbp, cb, cc, g1, ng1);
+    hipLaunchKernelGGL((gen_combine_kernel<MODE, S>), dim3(ng1 + ntiles), dim3(256), 0, c->stream, (const S*)g.dmat,
+                       n, in.g2, y.g2, acc.g2, out.g2, g.pdd, g.nbp, cb, cc, g1, ng1);
     HIP_OK(c, hipGetLastError());
     prof_mark(c, "gen_combine");
     return G1G2_OK;
 }
 
-template <typename T, typename S>
+template <typename T, typename S, typename DS>
 g1g2_status dispatch_blocks(g1g2_ctx* c, const Regs& in, double ws) {
     switch (c->gen.nbp) {
-        case 16: return run_blocks<T, S, 16>(c, in, ws);
-        case 32: return run_blocks<T, S, 32>(c, in, ws);
-        case 48: return run_blocks<T, S, 48>(c, in, ws);
-        case 64: return run_blocks<T, S, 64>(c, in, ws);
+        case 16: return run_blocks<T, S, DS, 16>(c, in, ws);
+        case 32: return run_blocks<T, S, DS, 32>(c, in, ws);
+        case 48: return run_blocks<T, S, DS, 48>(c, in, ws);
+        case 64: return run_blocks<T, S, DS, 64>(c, in, ws);
         default: return set_error(c, G1G2_EUNSUPPORTED, "general basis supports nb <= 64");
     }
 }
@@ -1322,7 +886,6 @@ g1g2_status gen_setup(g1g2_ctx* c, const cd* h0, const cd* w) {
                     for (int p = 0; p < nb; ++p) wg[P4(p, q, s1, r)] = WX(s1, q, r, p);  // M_pq[s][r] = w_sqrp
         if ((s = upload(c, &g.w_gw, wg)) != G1G2_OK) return s;
         if (mixed && (s = upload(c, &g.w_gw32, to_f32(wg))) != G1G2_OK) return s;
-        HIP_OK(c, hipMalloc(&g.pimat, 2 * n4 * sizeof(cd)));
     }
     if (pp || ph) {
         std::vector<cd> wl(n4, cmk(0, 0));
@@ -1343,14 +906,11 @@ g1g2_status gen_setup(g1g2_ctx* c, const cd* h0, const cd* w) {
             if (mixed && (s = upload(c, &g.w_ph32, to_f32(wl))) != G1G2_OK) return s;
         }
     }
-    if (gw || pp || ph) {
-        const size_t es = mixed ? sizeof(float2) : sizeof(cd);
-        HIP_OK(c, hipMalloc(&g.heps, n4 * es));
-        HIP_OK(c, hipMalloc(&g.bmat, n4 * es));
-    }
+    if ((gw || pp || ph) && (s = pair_setup(c, gw, pp, ph)) != G1G2_OK) return s;
     const size_t es = mixed ? sizeof(float2) : sizeof(cd);
     HIP_OK(c, hipMalloc(&g.vt, n4 * es));
-    HIP_OK(c, hipMalloc(&g.dmat, n4 * es));
+    // D is binary32 in mixed second Born only: the terms of pair.hip are added in binary64
+    HIP_OK(c, hipMalloc(&g.dmat, n4 * (se == G1G2_SOA ? es : sizeof(cd))));
     HIP_OK(c, hipMalloc(&g.hhf, (size_t)nbp * nbp * sizeof(cd)));
     HIP_OK(c, hipMalloc(&g.gg, (size_t)nbp * nbp * sizeof(cd)));
     HIP_OK(c, hipMalloc(&g.icoll, (size_t)nbp * nbp * sizeof(cd)));
@@ -1364,10 +924,14 @@ g1g2_status gen_stage(g1g2_ctx* c, int mode, double t, const Regs& in, const Reg
     const double ws = c->switch_value(t);
     g1g2_status s;
     if (c->d.precision == G1G2_MIXED) {
-        if ((s = dispatch_blocks<float, float2>(c, in, ws)) != G1G2_OK) return s;
-        return dispatch_combine<float2>(c, mode, in, y, acc, out, cb, cc);
+        if (c->d.selfenergy == G1G2_SOA) {
+            if ((s = dispatch_blocks<float, float2, float2>(c, in, ws)) != G1G2_OK) return s;
+            return dispatch_combine<float2>(c, mode, in, y, acc, out, cb, cc);
+        }
+        if ((s = dispatch_blocks<float, float2, cd>(c, in, ws)) != G1G2_OK) return s;
+        return dispatch_combine<cd>(c, mode, in, y, acc, out, cb, cc);
     }
-    if ((s = dispatch_blocks<double, cd>(c, in, ws)) != G1G2_OK) return s;
+    if ((s = dispatch_blocks<double, cd, cd>(c, in, ws)) != G1G2_OK) return s;
     return dispatch_combine<cd>(c, mode, in, y, acc, out, cb, cc);
 }
 
@@ -1423,8 +987,9 @@ g1g2_status gen_unpad(g1g2_ctx* c, const cd* src, cd* dst, int rank) {
 
 void gen_free(g1g2_ctx* c) {
     GeneralData& g = c->gen;
+    pair_free(c);
     void* ptrs[] = {g.h0,    g.wm_rows,   g.w_coll, g.w_hf,  g.vt,     g.dmat,   g.hhf,
-                    g.gg,    g.ipart,     g.heps,   g.bmat,  g.pimat,  g.wm_rows32, g.w_coll32,
+                    g.gg,    g.ipart,     g.wm_rows32, g.w_coll32,
                     g.w_gw,  g.w_gw32,    g.icoll,  g.w_pp,  g.w_ph,   g.w_pp32, g.w_ph32};
     for (void* p : ptrs)
         if (p) (void)hipFree(p);

@@ -364,6 +364,36 @@ def test_general_rhs_parity(lib, nb, se, prec):
     p.close()
 
 
+@pytest.mark.parametrize("nb,exchange", [(2, True), (2, False), (3, True), (7, False), (8, True), (17, False),
+                                         (33, True), (45, False)])
+@pytest.mark.parametrize("se", ["gw", "tpp", "tph", "dsl_x"])
+@pytest.mark.parametrize("prec", ["fp64", "mixed"])
+def test_general_pair_products(lib, nb, exchange, se, prec):
+    """The reduced pair products at sizes around their tile edges (nb^2 pairs
+    against tiles of 64 and, at nb = 45 in binary64, 128; dG2 vanishes
+    identically at nb = 1), also for a G2 without the exchange symmetry, whose odd
+    part takes products of its own.  The bounds are those of the right-hand
+    side at the tile sizes above."""
+    from paper_2002_12717_amd import binding as B
+    say(f"[general pair products] nb={nb} se={se} prec={prec} exchange={exchange}")
+    r = rng(205, nb, len(se))
+    h, w, gl = gue(nb, r), factorized_w(nb, 6, r), random_gless(nb, r)
+    g2 = random_g2(nb, r, scale=0.05, exchange=exchange)
+    code, flags = _gen_se(se)
+    p = B.Propagator(B.GENERAL, code, nb, h, gl, w=w,
+                     precision=B.FP64 if prec == "fp64" else B.MIXED, flags=flags)
+    G1d, G2d = cuda(gl), cuda(g2)
+    dG1d, dG2d = torch.zeros_like(G1d), torch.zeros_like(G2d)
+    p.rhs(0.0, G1d, G2d, dG1d, dG2d)
+    p.close()
+    d1, d2 = OG.rhs(T(h), T(w), T(gl), T(g2), se)
+    e1 = rel(dG1d.cpu().numpy(), d1.numpy())
+    e2 = rel(dG2d.cpu().numpy(), d2.numpy())
+    say(f"   err G1 {e1:.2e}  err G2 {e2:.2e}")
+    tol = 1e-12 if prec == "fp64" else 2e-5
+    assert e1 < tol and e2 < tol
+
+
 def _compare_general_trajectory(system, se, chunks, chunk_steps, prec, tol, switch=None):
     from paper_2002_12717_amd import binding as B
     code, flags = _gen_se(se)
