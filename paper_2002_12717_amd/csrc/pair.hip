@@ -335,7 +335,9 @@ __device__ __forceinline__ void tile_order(int b, int nr, int nc, int& r, int& c
 // ODD is the product with the exchange-odd part of G2 (K_PH).
 template <typename T, int WT>
 struct PairLds {
-    static constexpr int TILE = 32 * WT, KS = 16, VN = 16 / sizeof(T), LDA = KS + VN, LDB = TILE + 16;
+    static constexpr int TILE = 32 * WT, KS = 16;
+    static constexpr int VN = WT == 1 ? 2 : 16 / sizeof(T);   // values per load
+    static constexpr int LDA = KS + VN, LDB = TILE + 16;
     static constexpr int STAGE = 2 * (TILE * LDA + KS * LDB);
     static constexpr int EPI = 4 * 16 * 17 * (int)(sizeof(double) / sizeof(T));
     static constexpr int SIZE = STAGE > EPI ? STAGE : EPI;
@@ -427,16 +429,18 @@ __device__ __forceinline__ void pair_tile(const T* __restrict__ X, const T* __re
     // the quads (A,B) and (B,A) put their shares into slots that no other quad
     // writes: the quad of the later row pair into the slots themselves, the other
     // one into their Hermitian partners, where -conj of the share belongs.
+    // The loads of a quad's four slots are issued together: one memory latency per
+    // 16x16 tile.
     double* const ep = (double*)lds + wave * 16 * 17;
     const size_t n1 = tab.nbp;
-    auto add = [&](int a1, int a2, int b1, int b2, double vr, double vi) {
-        const size_t s = KIND == K_GW ? ((a1 * n1 + b1) * n1 + a2) * n1 + b2
-                                      : ((a1 * n1 + b1) * n1 + b2) * n1 + a2;
-        cd d = D[s];
-        d.x += vr;
-        d.y += vi;
-        D[s] = d;
-    };
+    const int qr = 2 * (lane >> 3), qc = 2 * (lane & 7);
+    int prow[WT], pcol[WT];
+#pragma unroll
+    for (int a = 0; a < WT; ++a) {
+        const int r = bm + wm + a * 16 + qr, c = bn + wn + a * 16 + qc;
+        prow[a] = r < noff ? tab.pt[r >> 1] : 0;
+        pcol[a] = c < noff ? tab.pt[c >> 1] : 0;
+    }
 #pragma unroll
     for (int a = 0; a < WT; ++a)
 #pragma unroll
@@ -444,66 +448,81 @@ __device__ __forceinline__ void pair_tile(const T* __restrict__ X, const T* __re
 #pragma unroll
             for (int r4 = 0; r4 < 4; ++r4)
                 ep[tile_row<T>(r4) * 17 + tile_col()] = F32 ? accd[F32 ? a : 0][F32 ? b : 0][r4] : (double)acc[a][b][r4];
-            __syncthreads();
-            const int qr = 2 * (lane >> 3), qc = 2 * (lane & 7);
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");   // one wave's LDS accesses stay in order
+            __builtin_amdgcn_wave_barrier();
             const double r00 = ep[qr * 17 + qc], r01 = ep[qr * 17 + qc + 1];
             const double r10 = ep[(qr + 1) * 17 + qc], r11 = ep[(qr + 1) * 17 + qc + 1];
             const int row = bm + wm + a * 16 + qr, col = bn + wn + b * 16 + qc;
-            __syncthreads();
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            __builtin_amdgcn_wave_barrier();
             if (row >= n2 || col >= n2) continue;
+            size_t slot[4];
+            cd val[4];
+            bool use[4] = {false, false, false, false};
+            auto set = [&](int k, int a1, int a2, int b1, int b2, double vr, double vi) {
+                slot[k] = KIND == K_GW ? ((a1 * n1 + b1) * n1 + a2) * n1 + b2 : ((a1 * n1 + b1) * n1 + b2) * n1 + a2;
+                val[k] = cmk(vr, vi);
+                use[k] = true;
+            };
             // share c r of an element r: i r (even), r and -r for the two slots (odd)
             auto c1 = [&](double x, double y) { return ODD ? cmk(x, y) : cmk(-y, x); };
             auto c2 = [&](double x, double y) { return ODD ? cmk(-x, -y) : cmk(-y, x); };
             if (row < noff && col < noff) {
-                const int va = tab.pt[row >> 1], vb = tab.pt[col >> 1];
+                const int va = prow[a], vb = pcol[b];
                 const int a1 = va & 0xffff, a2 = va >> 16, b1 = vb & 0xffff, b2 = vb >> 16;
                 const double xr = 0.25 * (r00 - r11), xi = 0.25 * (r10 + r01);
                 const double yr = 0.25 * (r00 + r11), yi = 0.25 * (r10 - r01);
-                const cd s1 = c1(xr, xi), s2 = c2(xr, xi);
-                if (row > col) {
-                    add(a1, a2, b1, b2, s1.x, s1.y);
-                    add(b1, b2, a1, a2, s2.x, s2.y);
-                } else if (row < col) {
-                    add(b2, b1, a2, a1, -s1.x, s1.y);
-                    add(a2, a1, b2, b1, -s2.x, s2.y);
+                const cd s1 = c1(xr, xi), s2 = c2(xr, xi), t1 = c1(yr, yi), t2 = c2(yr, yi);
+                const bool lo = row < col;   // the Hermitian partners' slots
+                if (row != col) {
+                    set(0, lo ? b2 : a1, lo ? b1 : a2, lo ? a2 : b1, lo ? a1 : b2, lo ? -s1.x : s1.x, s1.y);
+                    set(1, lo ? a2 : b1, lo ? a1 : b2, lo ? b2 : a1, lo ? b1 : a2, lo ? -s2.x : s2.x, s2.y);
                 } else {
-                    add(a1, a2, a1, a2, s1.x + s2.x, s1.y + s2.y);
+                    set(0, a1, a2, a1, a2, s1.x + s2.x, s1.y + s2.y);
                 }
-                const cd t1 = c1(yr, yi), t2 = c2(yr, yi);
-                add(a1, a2, b2, b1, t1.x, t1.y);
-                add(b2, b1, a1, a2, t2.x, t2.y);
+                set(2, a1, a2, b2, b1, t1.x, t1.y);
+                set(3, b2, b1, a1, a2, t2.x, t2.y);
             } else if (row < noff) {          // B = (b,b)
-                const int va = tab.pt[row >> 1], a1 = va & 0xffff, a2 = va >> 16;
-                for (int y = 0; y < 2 && col + y < n2; ++y) {
+                const int va = prow[a], a1 = va & 0xffff, a2 = va >> 16;
+#pragma unroll
+                for (int y = 0; y < 2; ++y) {
                     const int bb = col + y - noff;
+                    if (bb >= tab.nb) continue;
                     const double xr = 0.5 * (y ? r01 : r00), xi = 0.5 * (y ? r11 : r10);
                     const cd s1 = c1(xr, xi), s2 = c2(xr, xi);
-                    add(bb, bb, a2, a1, -s1.x, s1.y);
-                    add(a2, a1, bb, bb, -s2.x, s2.y);
+                    set(2 * y, bb, bb, a2, a1, -s1.x, s1.y);
+                    set(2 * y + 1, a2, a1, bb, bb, -s2.x, s2.y);
                 }
             } else if (col < noff) {          // A = (a,a)
-                const int vb = tab.pt[col >> 1], b1 = vb & 0xffff, b2 = vb >> 16;
-                for (int y = 0; y < 2 && row + y < n2; ++y) {
+                const int vb = pcol[b], b1 = vb & 0xffff, b2 = vb >> 16;
+#pragma unroll
+                for (int y = 0; y < 2; ++y) {
                     const int aa = row + y - noff;
+                    if (aa >= tab.nb) continue;
                     const double xr = 0.5 * (y ? r10 : r00), xi = 0.5 * (y ? r11 : r01);
                     const cd s1 = c1(xr, xi), s2 = c2(xr, xi);
-                    add(aa, aa, b1, b2, s1.x, s1.y);
-                    add(b1, b2, aa, aa, s2.x, s2.y);
+                    set(2 * y, aa, aa, b1, b2, s1.x, s1.y);
+                    set(2 * y + 1, b1, b2, aa, aa, s2.x, s2.y);
                 }
             } else {
+#pragma unroll
                 for (int y = 0; y < 4; ++y) {
                     const int aa = row + (y >> 1) - noff, bb = col + (y & 1) - noff;
                     if (aa >= tab.nb || bb >= tab.nb) continue;
                     const double v = y == 0 ? r00 : y == 1 ? r01 : y == 2 ? r10 : r11;
-                    if (KIND == K_GW) {
-                        // slot [ab][ab] is its own partner: the combine adds both shares
-                        dd[aa * tab.nb + bb] = v;
-                    } else {
-                        const cd s1 = c1(v, 0.0);
-                        add(aa, aa, bb, bb, s1.x, s1.y);
-                    }
+                    // GW: slot [ab][ab] is its own partner, the combine adds both shares
+                    const cd s1 = c1(v, 0.0);
+                    if (KIND == K_GW) dd[aa * tab.nb + bb] = v;
+                    else set(y, aa, aa, bb, bb, s1.x, s1.y);
                 }
             }
+            cd d[4];
+#pragma unroll
+            for (int k = 0; k < 4; ++k)
+                if (use[k]) d[k] = D[slot[k]];
+#pragma unroll
+            for (int k = 0; k < 4; ++k)
+                if (use[k]) D[slot[k]] = cadd(d[k], val[k]);
         }
 }
 
@@ -515,7 +534,7 @@ __global__ __launch_bounds__(256, 2) void gen_pair_gemm_kernel(const T* __restri
                                                               double* __restrict__ dd, PairTab tab, int ntile) {
     __shared__ __attribute__((aligned(16))) T lds[PairLds<T, WT>::SIZE];
     if constexpr (!ODD) pair_tile<T, WT, KIND, false>(X, Y, D, dd, tab, ntile, lds);
-    if constexpr (KIND == K_PH && (ODD || WT == 2))
+    if constexpr (KIND == K_PH && (ODD || WT <= 2))
         if (has_odd(tab)) pair_tile<T, WT, KIND, true>(Xodd, Y, D, dd, tab, ntile, lds);
 }
 
@@ -532,31 +551,32 @@ __global__ __launch_bounds__(256, 2) void gen_pair_gemm_kernel(const T* __restri
 // sectors coincide, so each is a launch of its own.  Where G2 has an
 // exchange-odd part, the tile's product with it (whose columns lie in the other
 // sector) follows in the same work-group.
-template <typename T, bool ODD>
+template <typename T, int W, bool ODD>
 __device__ __forceinline__ void pp_tile(const typename V2<T>::type* __restrict__ A,
                                     const typename V2<T>::type* __restrict__ B, cd* __restrict__ D,
                                     const PairTab& tab, bool even, int nr, int lds, int lda,
-                                    typename V2<T>::type (*a_c)[65], typename V2<T>::type (*b_c)[65]) {
+                                    typename V2<T>::type (*a_c)[32 * W + 1],
+                                        typename V2<T>::type (*b_c)[32 * W + 1]) {
     typedef typename V2<T>::type CT;
-    constexpr int KS = 16, PER = 64 * KS / 256;
+    constexpr int TILE = 32 * W, KS = 16, PER = TILE * KS / 256;
     const int ns = tab.nt + tab.nb;
     const int ldr = even ? lds : lda;                  // rows and K of this sector
     const int kend = ((even ? ns : tab.nt) + KS - 1) / KS * KS;
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, li = lane & 15, lk = lane >> 4;
-    const int wm = (wave >> 1) * 32, wn = (wave & 1) * 32;
+    const int wm = (wave >> 1) * 16 * W, wn = (wave & 1) * 16 * W;
     int tr, tc;
-    tile_order(blockIdx.x, nr, lds / 64, tr, tc);
-    const int bm = tr * 64, bn = tc * 64;
+    tile_order(blockIdx.x, nr, lds / TILE, tr, tc);
+    const int bm = tr * TILE, bn = tc * TILE;
     const bool ceven = even != ODD;                // sector of the columns
     const int ldb = ceven ? lds : lda, ncol = ceven ? ns : tab.nt;
     if (bn >= ncol) return;
     constexpr bool F32 = sizeof(T) == 4;
-    double accd[2][2][2][4];   // binary32 only
-    typename MF<T>::acc p1[2][2], p2[2][2], p3[2][2];   // Ar Br, Ai Bi, (Ar + Ai)(Br + Bi)
+    double accd[W][W][2][4];   // binary32 only
+    typename MF<T>::acc p1[W][W], p2[W][W], p3[W][W];   // Ar Br, Ai Bi, (Ar + Ai)(Br + Bi)
 #pragma unroll
-    for (int a = 0; a < 2; ++a)
+    for (int a = 0; a < W; ++a)
 #pragma unroll
-        for (int b = 0; b < 2; ++b) {
+        for (int b = 0; b < W; ++b) {
             p1[a][b] = p2[a][b] = p3[a][b] = MF<T>::zero();
 #pragma unroll
             for (int r4 = 0; r4 < 4; ++r4) accd[a][b][0][r4] = accd[a][b][1][r4] = 0.0;
@@ -566,7 +586,7 @@ __device__ __forceinline__ void pp_tile(const typename V2<T>::type* __restrict__
     auto fetch = [&](int k0) {
 #pragma unroll
         for (int u = 0; u < PER; ++u) {
-            const int idx = threadIdx.x + u * 256, k = idx / 64, c = idx % 64;
+            const int idx = threadIdx.x + u * 256, k = idx / TILE, c = idx % TILE;
             pa[u] = *(const CV*)(A + (size_t)(k0 + k) * ldr + bm + c);
             pb[u] = *(const CV*)(B + (size_t)(k0 + k) * ldb + bn + c);
         }
@@ -576,8 +596,8 @@ __device__ __forceinline__ void pp_tile(const typename V2<T>::type* __restrict__
 #pragma unroll
         for (int u = 0; u < PER; ++u) {
             const int idx = threadIdx.x + u * 256;
-            *(CV*)&a_c[idx / 64][idx % 64] = pa[u];
-            *(CV*)&b_c[idx / 64][idx % 64] = pb[u];
+            *(CV*)&a_c[idx / TILE][idx % TILE] = pa[u];
+            *(CV*)&b_c[idx / TILE][idx % TILE] = pb[u];
         }
         __syncthreads();
         if (k0 + KS < kend) fetch(k0 + KS);
@@ -586,25 +606,25 @@ __device__ __forceinline__ void pp_tile(const typename V2<T>::type* __restrict__
         __builtin_amdgcn_s_setprio(1);
 #pragma unroll
         for (int k4 = 0; k4 < KS; k4 += 4) {
-            T ar[2], ai[2], as[2], br[2], bi[2], bs[2];
+            T ar[W], ai[W], as[W], br[W], bi[W], bs[W];
 #pragma unroll
-            for (int a = 0; a < 2; ++a) {
+            for (int a = 0; a < W; ++a) {
                 const CV v = *(const CV*)&a_c[k4 + lk][wm + a * 16 + li];
                 ar[a] = v.x;
                 ai[a] = v.y;
                 as[a] = ar[a] + ai[a];
             }
 #pragma unroll
-            for (int b = 0; b < 2; ++b) {
+            for (int b = 0; b < W; ++b) {
                 const CV v = *(const CV*)&b_c[k4 + lk][wn + b * 16 + li];
                 br[b] = v.x;
                 bi[b] = v.y;
                 bs[b] = br[b] + bi[b];
             }
 #pragma unroll
-            for (int a = 0; a < 2; ++a)
+            for (int a = 0; a < W; ++a)
 #pragma unroll
-                for (int b = 0; b < 2; ++b) {
+                for (int b = 0; b < W; ++b) {
                     p1[a][b] = MF<T>::mac(ar[a], br[b], p1[a][b]);
                     p2[a][b] = MF<T>::mac(ai[a], bi[b], p2[a][b]);
                     p3[a][b] = MF<T>::mac(as[a], bs[b], p3[a][b]);
@@ -614,9 +634,9 @@ __device__ __forceinline__ void pp_tile(const typename V2<T>::type* __restrict__
         __syncthreads();
         if (F32 && ((k0 + KS) % 64 == 0 || k0 + KS >= kend)) {
 #pragma unroll
-            for (int a = 0; a < 2; ++a)
+            for (int a = 0; a < W; ++a)
 #pragma unroll
-                for (int b = 0; b < 2; ++b) {
+                for (int b = 0; b < W; ++b) {
 #pragma unroll
                     for (int r4 = 0; r4 < 4; ++r4) {
                         const double d1 = p1[a][b][r4], d2 = p2[a][b][r4], d3 = p3[a][b][r4];
@@ -629,50 +649,74 @@ __device__ __forceinline__ void pp_tile(const typename V2<T>::type* __restrict__
     }
     const size_t n1 = tab.nbp;
     const double sr = even ? 1.0 : -1.0, sc = ceven ? 1.0 : -1.0;
+    int prow[W][4], pcol[W];   // pairs p | q << 16, -1 outside
+    auto pair_at = [&](int x, int nx) {
+        int p, q;
+        if (x >= nx) return -1;
+        pair_of(tab, x, p, q);
+        return p | q << 16;
+    };
 #pragma unroll
-    for (int a = 0; a < 2; ++a)
+    for (int a = 0; a < W; ++a) {
+        pcol[a] = pair_at(bn + wn + a * 16 + tile_col(), ncol);
 #pragma unroll
-        for (int b = 0; b < 2; ++b)
+        for (int r4 = 0; r4 < 4; ++r4) prow[a][r4] = pair_at(bm + wm + a * 16 + tile_row<T>(r4), even ? ns : tab.nt);
+    }
+    const double sg[4] = {1.0, sr, sc, sr * sc};
+#pragma unroll
+    for (int a = 0; a < W; ++a)
+#pragma unroll
+        for (int b = 0; b < W; ++b) {
+            // the exchange images of four elements, their loads issued together
+            cd d[4][4];
+            size_t x[4][4];
+            bool use[4][4];
+            const int k = pcol[b] & 0xffff, l = pcol[b] >> 16;
 #pragma unroll
             for (int r4 = 0; r4 < 4; ++r4) {
-                const int row = bm + wm + a * 16 + tile_row<T>(r4);
-                const int col = bn + wn + b * 16 + tile_col();
-                if (row >= (even ? ns : tab.nt) || col >= ncol) continue;
-                const double vr = F32 ? accd[a][b][0][r4] : (double)(p1[a][b][r4] - p2[a][b][r4]);
-                const double vi = F32 ? accd[a][b][1][r4]
-                                                 : (double)(p3[a][b][r4] - p1[a][b][r4] - p2[a][b][r4]);
-                int i, j, k, l;
-                pair_of(tab, row, i, j);
-                pair_of(tab, col, k, l);
-                auto add = [&](int i1, int i2, int i3, int i4, double s) {
-                    const size_t x = ((i1 * n1 + i2) * n1 + i3) * n1 + i4;
-                    cd d = D[x];
-                    d.x += s * vr;
-                    d.y += s * vi;
-                    D[x] = d;
-                };
-                add(i, j, k, l, 1.0);
-                if (i != j) add(j, i, k, l, sr);
-                if (k != l) add(i, j, l, k, sc);
-                if (i != j && k != l) add(j, i, l, k, sr * sc);
+                const int i = prow[a][r4] & 0xffff, j = prow[a][r4] >> 16;
+                const bool in = pcol[b] >= 0 && prow[a][r4] >= 0;
+                x[r4][0] = ((i * n1 + j) * n1 + k) * n1 + l;
+                x[r4][1] = ((j * n1 + i) * n1 + k) * n1 + l;
+                x[r4][2] = ((i * n1 + j) * n1 + l) * n1 + k;
+                x[r4][3] = ((j * n1 + i) * n1 + l) * n1 + k;
+                use[r4][0] = in;
+                use[r4][1] = in && i != j;
+                use[r4][2] = in && k != l;
+                use[r4][3] = in && i != j && k != l;
+#pragma unroll
+                for (int m = 0; m < 4; ++m)
+                    if (use[r4][m]) d[r4][m] = D[x[r4][m]];
             }
+#pragma unroll
+            for (int r4 = 0; r4 < 4; ++r4) {
+                const double vr = F32 ? accd[a][b][0][r4] : (double)(p1[a][b][r4] - p2[a][b][r4]);
+                const double vi = F32 ? accd[a][b][1][r4] : (double)(p3[a][b][r4] - p1[a][b][r4] - p2[a][b][r4]);
+#pragma unroll
+                for (int m = 0; m < 4; ++m)
+                    if (use[r4][m]) D[x[r4][m]] = cmk(d[r4][m].x + sg[m] * vr, d[r4][m].y + sg[m] * vi);
+            }
+        }
 }
 
-template <typename T>
+template <typename T, int W>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2)))
 void gen_gemm_kernel(const typename V2<T>::type* __restrict__ A, const typename V2<T>::type* __restrict__ B,
                      const typename V2<T>::type* __restrict__ Bodd, cd* __restrict__ D, PairTab tab, bool even,
                      int nr, int lds, int lda) {
-    __shared__ typename V2<T>::type a_c[16][65], b_c[16][65];
-    pp_tile<T, false>(A, B, D, tab, even, nr, lds, lda, a_c, b_c);
-    if (has_odd(tab)) pp_tile<T, true>(A, Bodd, D, tab, even, nr, lds, lda, a_c, b_c);
+    __shared__ typename V2<T>::type a_c[16][32 * W + 1], b_c[16][32 * W + 1];
+    pp_tile<T, W, false>(A, B, D, tab, even, nr, lds, lda, a_c, b_c);
+    if (has_odd(tab)) pp_tile<T, W, true>(A, Bodd, D, tab, even, nr, lds, lda, a_c, b_c);
 }
 
 // --------------------------------------------------------------------------- host side
 int round_up(int v, int m) { return (v + m - 1) / m * m; }
 
-// 128x128 tiles where they give every compute unit one
-bool big_tiles(int n2) { return (round_up(n2, 128) / 128) * (round_up(n2, 128) / 128) >= 256; }
+// Tile edges by size: the largest whose tiles give each of the 256 compute units
+// one.  With fewer tiles than that the product is bound by the K loop of a
+// work-group, which is proportional to the tile's area.
+int tiles(int n, int edge) { return round_up(n, edge) / edge; }
+bool fills(int n, int edge) { return tiles(n, edge) * tiles(n, edge) >= 256; }
 
 template <typename T, typename S, int NB>
 g1g2_status pair_run(g1g2_ctx* c, const Regs& in, double ws) {
@@ -730,43 +774,47 @@ g1g2_status pair_run(g1g2_ctx* c, const Regs& in, double ws) {
     auto product = [&](auto kind) -> g1g2_status {
         constexpr int KIND = decltype(kind)::value;
         const T *x = (const T*)g.px[KIND], *xo = (const T*)g.pxo, *y = (const T*)g.py[KIND];
+        auto launch = [&](auto wt, auto odd) -> g1g2_status {
+            constexpr int WT = decltype(wt)::value;
+            constexpr bool ODD = decltype(odd)::value;
+            const int n = tiles(n2, 32 * WT);
+            hipLaunchKernelGGL((gen_pair_gemm_kernel<T, WT, KIND, ODD>), dim3(n * n), dim3(256), 0, c->stream, x, xo, y,
+                               D, g.pdd, tab, n);
+            HIP_OK(c, hipGetLastError());
+            prof_mark(c, ODD ? "gen_pair_gemm_odd" : "gen_pair_gemm");
+            return G1G2_OK;
+        };
+        typedef std::integral_constant<bool, false> both;
         if constexpr (sizeof(T) == 8) {
-            if (big_tiles(n2)) {
-                const int nt128 = round_up(n2, 128) / 128;
-                hipLaunchKernelGGL((gen_pair_gemm_kernel<T, 4, KIND>), dim3(nt128 * nt128), dim3(256), 0, c->stream, x,
-                                   xo, y, D, g.pdd, tab, nt128);
-                HIP_OK(c, hipGetLastError());
-                prof_mark(c, "gen_pair_gemm");
-                if constexpr (KIND == K_PH) {
-                    hipLaunchKernelGGL((gen_pair_gemm_kernel<T, 4, KIND, true>), dim3(nt128 * nt128), dim3(256), 0,
-                                       c->stream, x, xo, y, D, g.pdd, tab, nt128);
-                    HIP_OK(c, hipGetLastError());
-                    prof_mark(c, "gen_pair_gemm_odd");
-                }
-                return G1G2_OK;
+            if (fills(n2, 128)) {
+                const g1g2_status s = launch(std::integral_constant<int, 4>(), both());
+                if constexpr (KIND == K_PH)
+                    return s != G1G2_OK ? s
+                                        : launch(std::integral_constant<int, 4>(), std::integral_constant<bool, true>());
+                return s;
             }
         }
-        const int nt64 = round_up(n2, 64) / 64;
-        hipLaunchKernelGGL((gen_pair_gemm_kernel<T, 2, KIND>), dim3(nt64 * nt64), dim3(256), 0, c->stream, x, xo, y, D,
-                           g.pdd, tab, nt64);
-        HIP_OK(c, hipGetLastError());
-        prof_mark(c, "gen_pair_gemm");
-        return G1G2_OK;
+        if (fills(n2, 64)) return launch(std::integral_constant<int, 2>(), both());
+        return launch(std::integral_constant<int, 1>(), both());
     };
     g1g2_status s;
     if (gw && (s = product(std::integral_constant<int, K_GW>())) != G1G2_OK) return s;
     if (ph && (s = product(std::integral_constant<int, K_PH>())) != G1G2_OK) return s;
     if (pp) {
-        const int rs = g.plds / 64, ra = g.plda / 64, cs = g.plds / 64;
-        hipLaunchKernelGGL((gen_gemm_kernel<T>), dim3(rs * cs), dim3(256), 0, c->stream, (const CT*)g.phs,
-                           (const CT*)g.pgs, (const CT*)g.pgso, D, tab, true, rs, g.plds, g.plda);
-        HIP_OK(c, hipGetLastError());
-        prof_mark(c, "gen_gemm");
-        if (nt > 0) {
-            hipLaunchKernelGGL((gen_gemm_kernel<T>), dim3(ra * cs), dim3(256), 0, c->stream, (const CT*)g.pha,
-                               (const CT*)g.pga, (const CT*)g.pgao, D, tab, false, ra, g.plds, g.plda);
+        auto sector = [&](auto w, bool even) -> g1g2_status {
+            constexpr int W = decltype(w)::value, E = 32 * W;
+            const int nr = tiles(even ? npair : nt, E), nc = g.plds / E;
+            hipLaunchKernelGGL((gen_gemm_kernel<T, W>), dim3(nr * nc), dim3(256), 0, c->stream,
+                               (const CT*)(even ? g.phs : g.pha), (const CT*)(even ? g.pgs : g.pga),
+                               (const CT*)(even ? g.pgso : g.pgao), D, tab, even, nr, g.plds, g.plda);
             HIP_OK(c, hipGetLastError());
             prof_mark(c, "gen_gemm");
+            return G1G2_OK;
+        };
+        for (int even = 1; even >= (nt > 0 ? 0 : 1); --even) {
+            s = fills(npair, 64) ? sector(std::integral_constant<int, 2>(), even != 0)
+                                 : sector(std::integral_constant<int, 1>(), even != 0);
+            if (s != G1G2_OK) return s;
         }
     }
     return G1G2_OK;
@@ -794,7 +842,7 @@ g1g2_status pair_setup(g1g2_ctx* c, bool gw, bool pp, bool ph) {
     HIP_OK(c, hipMalloc(&g.pstat, 2 * sizeof(unsigned long long)));
     HIP_OK(c, hipMalloc(&g.pdd, (size_t)nb * nb * sizeof(double)));
     HIP_OK(c, hipMemsetAsync(g.pdd, 0, (size_t)nb * nb * sizeof(double), c->stream));
-    g.pld = round_up(n2, es == sizeof(double) && big_tiles(n2) ? 128 : 64);
+    g.pld = round_up(n2, es == sizeof(double) && fills(n2, 128) ? 128 : 64);
     g.plds = round_up(nt + nb, 64);
     g.plda = std::max(64, round_up(nt, 64));
     // the paddings stay zero: K paddings enter the products
