@@ -117,6 +117,10 @@ g1g2_status stage(g1g2_ctx* c, int mode, double t, const Regs& in, const Regs& y
 
 // One classical RK4 step on the registers (y, acc, s0, s1).
 g1g2_status rk4_step(g1g2_ctx* c, double t, double dt) {
+    if (hub_tile_ok(c))   // mixed precision keeps the running sum, binary64 the third stage register
+        return c->d.precision == G1G2_MIXED
+                   ? hub_tile_step(c, t, dt, c->y, c->s0, c->s1, c->s0, c->acc, false, true)
+                   : hub_tile_step(c, t, dt, c->y, c->s0, c->s1, c->acc, c->acc, false, true);
     g1g2_status s;
     if ((s = stage(c, RK_FIRST, t, c->y, c->y, c->acc, c->s0, dt / 6.0, dt / 2.0)) != G1G2_OK) return s;
     if ((s = stage(c, RK_MID, t + 0.5 * dt, c->s0, c->y, c->acc, c->s1, dt / 3.0, dt / 2.0)) != G1G2_OK)
@@ -296,6 +300,7 @@ g1g2_status g1g2_init(g1g2_ctx** out, const g1g2_desc* d, const void* h0, const 
     if (G2_0) {
         if ((s = load_component(c, G2_0, dev, c->y.g2, 4)) != G1G2_OK) return fail(s);
     }
+    if (d->basis == G1G2_HUBBARD && (s = hub_check_state(c)) != G1G2_OK) return fail(s);
     if (hipStreamSynchronize(c->stream) != hipSuccess) return fail(G1G2_EDEVICE);
     *out = c;
     return G1G2_OK;
@@ -497,6 +502,11 @@ g1g2_status g1g2_set_state(g1g2_ctx* c, const void* G1, const void* G2, double t
     }
     if ((s = guard_clear(c)) != G1G2_OK) return s;
     if (c->d.basis == G1G2_JELLIUM && (s = jel_state_changed(c)) != G1G2_OK) return s;
+    if (c->d.basis == G1G2_HUBBARD) {
+        const bool before = hub_tile_ok(c);
+        if ((s = hub_check_state(c)) != G1G2_OK) return s;
+        if (hub_tile_ok(c) != before) drop_graph(c);   // captured steps take other kernels
+    }
     HIP_OK(c, hipStreamSynchronize(c->stream));
     c->t = t;
     return G1G2_OK;
@@ -629,6 +639,7 @@ g1g2_status g1g2_batch_init(g1g2_ctx** out, const g1g2_desc* d, int32_t n, const
                            hipMemcpyHostToDevice, c->stream) != hipSuccess)
             return fail(G1G2_EDEVICE);
     }
+    if ((s = hub_check_state(c)) != G1G2_OK) return fail(s);
     if (hipStreamSynchronize(c->stream) != hipSuccess) return fail(G1G2_EDEVICE);
     *out = c;
     return G1G2_OK;

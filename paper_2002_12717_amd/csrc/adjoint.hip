@@ -692,11 +692,17 @@ g1g2_status g1g2_adjoint(g1g2_ctx* c, const double* wa, const double* wb, double
             const int m = (int)(n - n0);
             if ((s = copy_reg(c, st->seg[m], c->y)) != G1G2_OK) return s;
             const double t = st->t0 + (double)n * dt;
-            if ((s = stage_fwd(c, RK_FIRST, t, c->y, c->y, c->acc, st->seg2[m], dt / 6.0, dt / 2.0)) != G1G2_OK) return s;
-            if ((s = stage_fwd(c, RK_MID, t + 0.5 * dt, st->seg2[m], c->y, c->acc, st->seg3[m], dt / 3.0, dt / 2.0)) != G1G2_OK) return s;
-            if ((s = stage_fwd(c, RK_MID, t + 0.5 * dt, st->seg3[m], c->y, c->acc, st->seg4[m], dt / 3.0, dt)) != G1G2_OK) return s;
-            if (n + 1 < n1)
-                if ((s = stage_fwd(c, RK_LAST, t + dt, st->seg4[m], c->y, c->acc, c->y, dt / 6.0, 0.0)) != G1G2_OK) return s;
+            const Regs &s2 = st->seg2[m], &s3 = st->seg3[m], &s4 = st->seg4[m];
+            const bool last = n + 1 < n1;
+            if (hub_tile_ok(c)) {   // the reverse sweep reads the stage states whole
+                if ((s = hub_tile_step(c, t, dt, c->y, s2, s3, s4, c->acc, true, last)) != G1G2_OK) return s;
+                continue;
+            }
+            if ((s = stage_fwd(c, RK_FIRST, t, c->y, c->y, c->acc, s2, dt / 6.0, dt / 2.0)) != G1G2_OK) return s;
+            if ((s = stage_fwd(c, RK_MID, t + 0.5 * dt, s2, c->y, c->acc, s3, dt / 3.0, dt / 2.0)) != G1G2_OK) return s;
+            if ((s = stage_fwd(c, RK_MID, t + 0.5 * dt, s3, c->y, c->acc, s4, dt / 3.0, dt)) != G1G2_OK) return s;
+            if (last)
+                if ((s = stage_fwd(c, RK_LAST, t + dt, s4, c->y, c->acc, c->y, dt / 6.0, 0.0)) != G1G2_OK) return s;
         }
         // reverse over the segment: Y2 = y + dt/2 k1, Y3 = y + dt/2 k2, Y4 = y + dt k3
         for (int64_t n = n1 - 1; n >= n0; --n) {

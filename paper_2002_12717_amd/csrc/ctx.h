@@ -55,6 +55,16 @@ struct HubbardData {
     cd* diag = nullptr;            // per cluster n_diag [ns]^3 gathered diagonal tensors
     long long diag_elems = 0;      // complex elements of diag (0: the closure gathers none)
     std::vector<int> chunk;        // elements of G2 per work-group, per cluster
+    // stages over one triangle of the pair matrix (hub_tile.hip); tiles null: not eligible
+    int* tiles = nullptr;          // tile words of all clusters
+    WorkItem* twork = nullptr;     // work list over them
+    int ntwork = 0;
+    bool tile_row = false;         // one tile per item, a wave per row
+    std::vector<std::pair<int, int>> tile_shapes;   // (tiles per item, ns) of the items
+    WorkItem* dtile = nullptr;     // work list of the diagonal tensors
+    int ndtile = 0;
+    cd* tdiag = nullptr;           // the diagonal tensors
+    unsigned long long* tsym = nullptr;   // result of the symmetry check
     int* nbr = nullptr;            // concatenated neighbour tables
     cd* hop = nullptr;
     double* d0 = nullptr;
@@ -136,6 +146,7 @@ struct g1g2_ctx {
     hipStream_t stream = nullptr;
     int device = 0;
     std::string err;
+    bool herm = false;         // Hubbard: the state passed hub_check_state
     double t = 0.0;
     int64_t step = 0;
     size_t n1 = 0, n2 = 0;     // internal element counts of G1 and G2
@@ -204,6 +215,21 @@ g1g2_status hub_stage(g1g2_ctx* c, int mode, double t, const Regs& in, const Reg
 g1g2_status hub_stage_diag(g1g2_ctx* c, int mode, double t, const Regs& in, const Regs& y,
                            const Regs& acc, const Regs& out, double cb, double cc, cd* diag);
 size_t hub_diag_bytes(const g1g2_ctx* c);
+// Stages over one triangle of the pair matrix (hub_tile.hip): set-up after the
+// neighbour tables, the symmetry check of the state y (synchronizes; call
+// whenever a state is set), whether steps take them now, one step, release.
+// hub_tile_step writes y4 by the third stage and, with last, the new state to y;
+// full: the stage registers are written whole, not only where stages read them.
+constexpr int TILE_ROW_MIN = 44;   // least ns of the wave-per-row form
+constexpr int TILE_VEC = 384;      // most tiles x ns of an item (its LDS vectors)
+g1g2_status hub_tile_setup(g1g2_ctx* c, const std::vector<int>& nbr, const std::vector<int>& per_item);
+g1g2_status hub_check_state(g1g2_ctx* c);
+bool hub_tile_ok(const g1g2_ctx* c);
+g1g2_status hub_tile_step(g1g2_ctx* c, double t, double dt, const Regs& y, const Regs& y2, const Regs& y3,
+                          const Regs& y4, const Regs& acc, bool full, bool last);
+void hub_tile_free(g1g2_ctx* c);
+std::vector<WorkItem> xcd_order(const std::vector<WorkItem>& g2, const std::vector<long long>& cost,
+                                const std::vector<WorkItem>& g1);
 // The static device scratch of g1g2_rhs_noalloc on the context's device:
 // looked up once per device at context set-up.
 g1g2_status hub_noalloc_setup(g1g2_ctx* c);

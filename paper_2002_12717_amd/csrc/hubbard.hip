@@ -28,22 +28,7 @@
 
 namespace {
 
-using hub::Cl;
-using hub::hf_diag;
-using hub::make_cl;
-
-// Selfenergies of the stage kernels.  DSL (Sec. VI) is GW on the three
-// channels with both ladders added on channel A.
-enum { SE_SOA = 0, SE_TPP = 1, SE_TPH = 2, SE_GW = 3, SE_DSL = 4 };
-
-__host__ __device__ constexpr bool has_pol(int se) { return se == SE_GW || se == SE_DSL; }
-__host__ __device__ constexpr bool has_pp(int se) { return se == SE_TPP || se == SE_DSL; }
-__host__ __device__ constexpr bool has_ph(int se) { return se == SE_TPH || se == SE_DSL; }
-
-// G2 channels stored per cluster and diagonal tensors gathered per stage
-// (GW's six layouts first, then the particle-hole ladder's two).
-__host__ __device__ constexpr int n_channels(int se) { return has_pol(se) ? 3 : 1; }
-__host__ __device__ constexpr int n_diag(int se) { return (has_pol(se) ? 6 : 0) + (has_ph(se) ? 2 : 0); }
+using namespace hub;
 
 // Right-hand side of one element e = ((i ns + j) ns + k) ns + l of the
 // cluster's block A = G2^{up down up down}:
@@ -175,37 +160,6 @@ __device__ __forceinline__ cd hub_g1_rhs(const Cl& a, const TA* __restrict__ A, 
     return cmul_mi(cadd(c, coll));
 }
 
-struct StageArgs {
-    const ClusterDesc* __restrict__ desc;
-    const WorkItem* __restrict__ work;
-    const int* __restrict__ nbr;
-    const cd* __restrict__ hop;
-    const double* __restrict__ d0;
-    const double* __restrict__ xdrv;
-    double s_drive;
-    double u_scale;   // switching factor phi(t) of the stage
-    const cd* in1;
-    const cd* in2;
-    const cd* y1;
-    const cd* y2;
-    cd* acc1;
-    cd* acc2;
-    cd* out1;
-    cd* out2;
-    double cb, cc;
-    DivGuard guard;
-    const cd* diag;   // per cluster: GW's six [ns]^3 layouts, then TPH's R and S (hub_diag_kernel)
-};
-
-// Storage of the G2 stage registers.  Mixed precision keeps the stage copies
-// (the inputs of stages 2-4 and the outputs of stages 1-3) in binary32; y and
-// acc, and every G1 register, stay binary64.
-template <int MODE, bool MIXED>
-struct StageTypes {
-    using In = typename std::conditional<MIXED && (MODE == RK_MID || MODE == RK_LAST), float2, cd>::type;
-    using Out = typename std::conditional<MIXED && (MODE == RK_FIRST || MODE == RK_MID), float2, cd>::type;
-};
-
 template <int MODE, int SE, bool MIXED>
 __global__ __launch_bounds__(256) void hub_stage_kernel(StageArgs s) {
     using TI = typename StageTypes<MODE, MIXED>::In;
@@ -301,27 +255,6 @@ __global__ __launch_bounds__(256) void hub_diag_kernel(const ClusterDesc* __rest
 // A work item is a range [start, end) of wave units u = slice * nkb + kb,
 // nkb = ceil(ns / rpw); wave w of the work-group takes units start + w,
 // start + w + 4, ...
-constexpr int NS_MAX_ROW = 64;
-constexpr int Z_MAX_ROW = 4;
-
-// A wave-uniform value moved to scalar registers.
-__device__ __forceinline__ double wave_uniform(double v) {
-    const long long b = __double_as_longlong(v);
-    const unsigned lo = (unsigned)__builtin_amdgcn_readfirstlane((int)(unsigned)(b & 0xffffffffLL));
-    const unsigned hi = (unsigned)__builtin_amdgcn_readfirstlane((int)(unsigned)(b >> 32));
-    return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
-}
-__device__ __forceinline__ cd wave_uniform(cd v) { return cmk(wave_uniform(v.x), wave_uniform(v.y)); }
-__device__ __forceinline__ int wave_uniform(int v) { return __builtin_amdgcn_readfirstlane(v); }
-
-// Element i of an array below 4 GiB, addressed as base + 32-bit byte offset:
-// with a wave-uniform base the load takes the scalar-base + vector-offset form
-// and needs no 64-bit address arithmetic per lane.
-template <typename T>
-__device__ __forceinline__ cd ldo(const T* __restrict__ p, unsigned i) {
-    return ld_c(reinterpret_cast<const T*>(reinterpret_cast<const char*>(p) + i * (unsigned)sizeof(T)), 0);
-}
-
 // REALH: every hopping of the launch is real (h_pq = h_qp), so each neighbour
 // term is a real-by-complex product.
 template <int MODE, int SE, bool MIXED, bool REALH>
@@ -588,7 +521,6 @@ constexpr int SLICE_THREADS_BIG = 1024;
 // 0.373 and mixed TPH 3% slower.
 __host__ __device__ constexpr int row64_waves(int se, bool) { return se == SE_TPH ? 8 : 6; }
 __host__ __device__ constexpr int row64_threads(int se, bool mixed) { return 128 * row64_waves(se, mixed); }
-constexpr int SLICE_ELEMS = 4096;
 // TPP: the diagonal entries A_ppij of the staged slices (p < ns), kept in LDS;
 // a TPP item holds at most SLICE_DIAG / ns slices
 constexpr int SLICE_DIAG = 128;
@@ -602,12 +534,6 @@ constexpr long long SLICE_MIN_ELEMS = 1LL << 20;
 // for the row kernel and 34k, 27k and 28k for the persistent work-group)
 constexpr long long SMALL_SLICE_MAX = 4096;
 constexpr int SLICE_SMALL = 256;
-
-// n / d for n < 2^16 and 1 <= d <= 4096, with mg = slice_magic(d)
-__host__ __device__ constexpr unsigned slice_magic(unsigned d) { return d == 1 ? 0u : 0xffffffffu / d + 1u; }
-__device__ __forceinline__ int slice_div(int n, unsigned mg) {
-    return mg == 0u ? n : (int)__umulhi((unsigned)n, mg);
-}
 
 template <int MODE, int SE, bool MIXED, bool REALH, bool ROW64>
 __global__ __launch_bounds__(SLICE_THREADS_BIG) __attribute__((amdgpu_waves_per_eu(ROW64 ? row64_waves(SE, MIXED) : 1))) void hub_slice_kernel(StageArgs s) {
@@ -1051,33 +977,6 @@ __global__ __launch_bounds__(PERSIST_THREADS) void hub_persistent_kernel(Persist
     if (tid == 0) p.guard.div[0] = step0 + (unsigned long long)p.nsteps;
 }
 
-StageArgs make_stage(g1g2_ctx* c, double t, const Regs& in, const Regs& y, const Regs& acc,
-                     const Regs& out, double cb, double cc) {
-    HubbardData& H = c->hub;
-    StageArgs s;
-    s.desc = H.desc;
-    s.work = H.work;
-    s.nbr = H.nbr;
-    s.hop = H.hop;
-    s.d0 = H.d0;
-    s.xdrv = H.xdrv;
-    s.s_drive = H.drive_value(t);
-    s.u_scale = c->switch_value(t);
-    s.in1 = in.g1;
-    s.in2 = in.g2;
-    s.y1 = y.g1;
-    s.y2 = y.g2;
-    s.acc1 = acc.g1;
-    s.acc2 = acc.g2;
-    s.out1 = out.g1;
-    s.out2 = out.g2;
-    s.cb = cb;
-    s.cc = cc;
-    s.guard = guard_of(c);
-    s.diag = H.diag;
-    return s;
-}
-
 template <int MODE, int SE, bool MIXED>
 void launch_stage_t(g1g2_ctx* c, const StageArgs& s) {
     if (n_diag(SE) > 0) {
@@ -1248,6 +1147,33 @@ g1g2_status upload(g1g2_ctx* c, V** dst, const std::vector<V>& h) {
 
 }  // namespace
 
+hub::StageArgs hub_make_stage(g1g2_ctx* c, double t, const Regs& in, const Regs& y, const Regs& acc,
+                     const Regs& out, double cb, double cc) {
+    HubbardData& H = c->hub;
+    StageArgs s;
+    s.desc = H.desc;
+    s.work = H.work;
+    s.nbr = H.nbr;
+    s.hop = H.hop;
+    s.d0 = H.d0;
+    s.xdrv = H.xdrv;
+    s.s_drive = H.drive_value(t);
+    s.u_scale = c->switch_value(t);
+    s.in1 = in.g1;
+    s.in2 = in.g2;
+    s.y1 = y.g1;
+    s.y2 = y.g2;
+    s.acc1 = acc.g1;
+    s.acc2 = acc.g2;
+    s.out1 = out.g1;
+    s.out2 = out.g2;
+    s.cb = cb;
+    s.cc = cc;
+    s.guard = guard_of(c);
+    s.diag = H.diag;
+    return s;
+}
+
 double HubbardData::drive_value(double t) const {
     double s = 0.0;
     for (size_t m = 0; m < drive_c.size(); ++m) {
@@ -1258,6 +1184,7 @@ double HubbardData::drive_value(double t) const {
 }
 
 void hub_free(g1g2_ctx* c) {
+    hub_tile_free(c);
     HubbardData& H = c->hub;
     void* ptrs[] = {H.desc, H.work, H.dwork, H.diag, H.nbr, H.hop, H.d0, H.xdrv};
     for (void* p : ptrs)
@@ -1493,6 +1420,15 @@ g1g2_status hub_setup(g1g2_ctx* c, int ncl, const int* nsv, const double* Uv, co
         HIP_OK(c, hipMemcpyAsync(H.xdrv, H.drive_x.data(), xoff * sizeof(double), hipMemcpyHostToDevice,
                                  c->stream));
     HIP_OK(c, hipStreamSynchronize(c->stream));
+    // steps over one triangle of the pair matrix, at the sizes that take whole slices
+    // by default
+    if (slicek && !small1 && realhop && !(fl & G1G2_HUB_SLICE_KERNEL)) {
+        std::vector<int> per(ncl, SLICE_ELEMS);
+        if (chunk_in)
+            for (int cl = 0; cl < ncl; ++cl)
+                if (chunk_in[cl] > 0) per[cl] = std::min(per[cl], chunk_in[cl]);
+        return hub_tile_setup(c, nbr_all, per);
+    }
     return G1G2_OK;
 }
 
@@ -1551,7 +1487,7 @@ g1g2_status hub_stage(g1g2_ctx* c, int mode, double t, const Regs& in, const Reg
 
 g1g2_status hub_stage_diag(g1g2_ctx* c, int mode, double t, const Regs& in, const Regs& y,
                            const Regs& acc, const Regs& out, double cb, double cc, cd* diag) {
-    StageArgs s = make_stage(c, t, in, y, acc, out, cb, cc);
+    StageArgs s = hub_make_stage(c, t, in, y, acc, out, cb, cc);
     s.diag = diag;
     switch (mode) {
         case RK_RHS: return launch_stage<RK_RHS>(c, s);

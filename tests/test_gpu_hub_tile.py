@@ -1,0 +1,139 @@
+"""Hubbard steps over one triangle of the pair matrix against the CPU oracle.
+
+The path serves Hermitian states of systems of at least 2^20 G2 elements with
+real hoppings.  Tolerances are those of the other step tests: 1e-10 relative in
+binary64, 1e-5 in mixed precision.
+"""
+import numpy as np
+import pytest
+import torch
+
+from oracle import hubbard as OH, integrate as OI
+from workloads import chain_hopping, random_g2, random_gless, rng, square_hopping
+
+pytestmark = pytest.mark.gpu
+
+
+def say(*a):
+    print(*a, flush=True)
+
+
+def T(x):
+    return torch.as_tensor(np.asarray(x), dtype=torch.complex128)
+
+
+def rel(a, b):
+    a, b = np.asarray(a), np.asarray(b)
+    return float(np.abs(a - b).max() / max(np.abs(b).max(), 1e-300))
+
+
+def _code(se):
+    from paper_2002_12717_amd import binding as B
+    return {"soa": B.SOA, "tpp": B.TPP, "tph": B.TPH, "gw": B.GW, "dsl": B.DSL}[se]
+
+
+def _system(lx, ly, periodic, r):
+    h = square_hopping(lx, ly, periodic=periodic) if ly > 1 else chain_hopping(lx)
+    ns = h.shape[0]
+    h0 = np.stack([h + np.diag(r.uniform(-0.5, 0.5, ns)), 0.8 * h + np.diag(r.uniform(-0.5, 0.5, ns))]).astype(complex)
+    return ns, h0, np.stack([random_gless(ns, r), random_gless(ns, r)])
+
+
+def _oracle(h0, U, se, g1, g2, dt, steps):
+    y = [T(g1[0]), T(g1[1])] + [T(a) for a in g2]
+
+    def f(t, y):
+        kw = dict(B=y[3], C=y[4]) if len(y) > 3 else {}
+        return OH.rhs(T(h0[0]), T(h0[1]), U, y[0], y[1], y[2], se, **kw)
+    for n in range(steps):
+        y = OI.rk4_step(f, n * dt, y, dt)
+    return np.stack([y[0].numpy(), y[1].numpy()]), np.stack([a.numpy() for a in y[2:]])
+
+
+@pytest.mark.parametrize("lx,ly,periodic,se", [(33, 1, False, "soa"), (8, 4, True, "tpp"), (11, 3, False, "tph"),
+                                               (5, 5, True, "gw"), (8, 4, False, "dsl"), (9, 5, True, "soa"),
+                                               (9, 5, False, "tpp"), (7, 7, True, "tph"), (9, 5, True, "gw"),
+                                               (9, 5, False, "dsl")])
+@pytest.mark.parametrize("prec", ["fp64", "mixed"])
+def test_tile_steps_match_oracle(lib, lx, ly, periodic, se, prec):
+    """Two steps of a random Hermitian state: the packed form (below 44 sites) and
+    the wave-per-row form, every closure, neighbours across the diagonal near (open
+    lattices) and far (periodic ones)."""
+    from paper_2002_12717_amd import binding as B
+    say(f"[tile steps] {lx}x{ly} periodic={periodic} {se} {prec}")
+    r = rng(511, lx, ly, len(se))
+    ns, h0, g1 = _system(lx, ly, periodic, r)
+    nch = 3 if se in ("gw", "dsl") else 1
+    g2 = np.stack([random_g2(ns, r, scale=0.05, exchange=False) for _ in range(nch)])
+    U, dt = 1.3, 0.02
+    p = B.Propagator(B.HUBBARD, _code(se), ns, h0, g1, U=U, precision=B.FP64 if prec == "fp64" else B.MIXED)
+    p.set_state(g1, g2 if nch == 3 else g2[0])
+    p.step(dt, 2)
+    G1, G2, _ = p.get_state()
+    herm = p.observables()["herm_resid"]
+    p.close()
+    r1, r2 = _oracle(h0, U, se, g1, g2, dt, 2)
+    e1, e2 = rel(G1, r1), rel(G2, r2 if nch == 3 else r2[0])
+    say(f"   err G1 {e1:.2e}  err G2 {e2:.2e}  hermiticity {herm:.1e}")
+    tol = 1e-10 if prec == "fp64" else 1e-5
+    assert e1 < tol and e2 < tol
+    assert herm < 1e-14
+
+
+@pytest.mark.parametrize("se", ["soa", "tpp", "tph", "gw", "dsl"])
+@pytest.mark.parametrize("prec", ["fp64", "mixed"])
+def test_tile_batch_of_mixed_sizes(lib, se, prec):
+    """One 33-site cluster with small ones, so that items pack from 3 tiles to all
+    of a cluster (a one-site cluster has no correlation to compare: G2 = 0 exactly)."""
+    from paper_2002_12717_amd import binding as B
+    say(f"[tile batch] {se} {prec}")
+    r = rng(512, len(se))
+    shapes = [(33, 1), (2, 1), (3, 3), (3, 1), (4, 4), (5, 1), (6, 6), (5, 3)]
+    cl = [_system(a, b, b > 2, r) for a, b in shapes]
+    U = [0.7 + 0.2 * q for q in range(len(cl))]
+    b = B.Batch(_code(se), [c[0] for c in cl], U, [c[1] for c in cl], [c[2] for c in cl],
+                precision=B.FP64 if prec == "fp64" else B.MIXED)
+    b.step(0.02, 2)
+    worst = 0.0
+    for q, (ns, h0, g1) in enumerate(cl):
+        nch = 3 if se in ("gw", "dsl") else 1
+        r1, r2 = _oracle(h0, U[q], se, g1, np.zeros((nch,) + (ns,) * 4, complex), 0.02, 2)
+        G1, G2 = b.get_cluster(q)
+        worst = max(worst, rel(G1, r1), rel(G2, r2 if nch == 3 else r2[0]))
+    b.close()
+    say(f"   worst rel err {worst:.2e}")
+    assert worst < (1e-10 if prec == "fp64" else 1e-5)
+
+
+def test_tile_path_needs_a_hermitian_state(lib):
+    """A state without the pair symmetry takes the slice kernel, bit for bit as when
+    that kernel is asked for, and a Hermitian one set afterwards the triangle again;
+    graph replays follow the change."""
+    from paper_2002_12717_amd import binding as B
+    r = rng(513)
+    ns, h0, g1 = _system(33, 1, False, r)
+    sym = random_g2(ns, r, scale=0.05, exchange=False)
+    bad = sym.copy()
+    bad[3, 4, 5, 6] += 1e-3
+    s = torch.cuda.Stream()
+    p = B.Propagator(B.HUBBARD, B.SOA, ns, h0, g1, U=1.1, stream=s.cuda_stream)
+    q = B.Propagator(B.HUBBARD, B.SOA, ns, h0, g1, U=1.1, flags=B.HUB_SLICE_KERNEL)
+    e = B.Propagator(B.HUBBARD, B.SOA, ns, h0, g1, U=1.1)
+    for rep in range(2):
+        p.set_state(g1, bad)
+        q.set_state(g1, bad)
+        p.step(0.01, 8)
+        q.step(0.01, 8)
+        a, b = p.get_state(), q.get_state()
+        assert np.array_equal(a[0], b[0]) and np.array_equal(a[1], b[1])
+        p.set_state(g1, sym)
+        q.set_state(g1, sym)
+        e.set_state(g1, sym)
+        p.step(0.01, 16)
+        q.step(0.01, 16)
+        e.step(0.01, 16)
+        a, b, c = p.get_state(), q.get_state(), e.get_state()
+        assert np.array_equal(a[0], c[0]) and np.array_equal(a[1], c[1])   # replayed and eager steps
+        assert rel(a[0], b[0]) < 1e-12 and rel(a[1], b[1]) < 1e-12
+    for x in (p, q, e):
+        x.close()
