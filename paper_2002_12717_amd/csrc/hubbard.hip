@@ -977,6 +977,183 @@ __global__ __launch_bounds__(PERSIST_THREADS) void hub_persistent_kernel(Persist
     if (tid == 0) p.guard.div[0] = step0 + (unsigned long long)p.nsteps;
 }
 
+// Whole Runge-Kutta steps of a cluster whose elements the threads of one
+// work-group own alone: PER G2 elements per thread and, in threads of their own,
+// one G1 element.  A stage is bound by its latency, so whatever does not change
+// over the steps is prepared in registers: the LDS index and the (real) hopping
+// of every neighbour, Z slots per index, and the indices into G1.  What is left
+// per stage are the loads of the state, two fused update lines and one barrier
+// (the diagonal of h^HF is formed from G1 by each thread, and G1 runs beside G2
+// instead of after it).  ns <= 5 takes PER = 1; ns = 6 takes PER = 2 for chains (Z = 2),
+// whose neighbours still fit the registers.  Buffers as in
+// hub_persistent_kernel: binary64 alternates between two, mixed precision keeps y
+// in the first and two binary32 stage copies in the second.
+// threads: ns^4 / PER + 2 ns^2 in whole waves, at most three waves per SIMD
+constexpr int small_threads(int per) { return per == 1 ? 704 : 768; }
+
+template <int SE, bool MIXED, int PER, int Z>
+__global__ __launch_bounds__(small_threads(PER)) void hub_small_kernel(PersistArgs p) {
+    constexpr int CAP = PER == 1 ? 640 : 1296;   // ns^4 <= 625 or 1,296
+    __shared__ cd sA[2][CAP];
+    __shared__ cd sG[2][PERSIST_G1];
+    float2* const sF = reinterpret_cast<float2*>(sA[1]);
+    const ClusterDesc d = p.desc[0];
+    const int ns = d.ns, ns2 = ns * ns, ns3 = ns2 * ns, n2 = ns2 * ns2, n1 = 2 * ns2, z = d.zmax;
+    const int tid = threadIdx.x, nown = blockDim.x - n1;   // G2 owners, then the G1 owners
+    const double U = d.U;
+    const int* nbr = p.nbr + d.nbroff;
+    const cd* hop = p.hop + d.nbroff;
+    const double* d0 = p.d0 + d.d0off;
+    const bool g1 = tid >= nown;
+    // neighbour slots of site x and spin sg: the LDS index shifted by stride, hopping 0 where there is none
+    auto slots = [&](int sg, int x, int at, int stride, int* off, double* h) {
+#pragma unroll
+        for (int q = 0; q < Z; ++q) {
+            const int u = q < z ? nbr[(sg * ns + x) * z + q] : -1;
+            off[q] = u >= 0 ? at + (u - x) * stride : at;
+            h[q] = u >= 0 ? hop[(sg * ns + x) * z + q].x : 0.0;
+        }
+    };
+    int oi[PER][Z], oj[PER][Z], ok[PER][Z], ol[PER][Z];
+    double hi[PER][Z], hj[PER][Z], hk[PER][Z], hl[PER][Z], dd0[PER];
+    unsigned pk[PER];
+    cd y2[PER], acc2[PER];
+#pragma unroll
+    for (int q = 0; q < PER; ++q) {
+        const int e = g1 ? n2 : tid + q * nown, x = min(e, n2 - 1);
+        const int l = x % ns, k = (x / ns) % ns, j = (x / ns2) % ns, i = x / ns3;
+        pk[q] = (unsigned)i | ((unsigned)j << 8) | ((unsigned)k << 16) | ((unsigned)l << 24);
+        slots(0, i, x, ns3, oi[q], hi[q]);
+        slots(1, j, x, ns2, oj[q], hj[q]);
+        slots(0, k, x, ns, ok[q], hk[q]);
+        slots(1, l, x, 1, ol[q], hl[q]);
+        dd0[q] = d0[i] + d0[ns + j] - d0[k] - d0[ns + l];
+        y2[q] = acc2[q] = cmk(0.0, 0.0);
+        if (e < n2) {
+            y2[q] = p.y2[e];
+            sA[0][e] = y2[q];
+        }
+    }
+    // the G1 element: its neighbours along both indices and the collision integral's elements
+    const int ge = g1 ? tid - nown : 0, sig = ge / ns2, gr = ge - sig * ns2, gi = gr / ns, gj = gr - gi * ns;
+    int o1[Z], o2[Z];
+    double h1[Z], h2[Z];
+    slots(sig, gi, ge, ns, o1, h1);
+    slots(sig, gj, ge, 1, o2, h2);
+    const int ci = sig ? ((gi * ns + gi) * ns + gi) * ns + gj : ((gi * ns + gi) * ns + gj) * ns + gi;
+    const int cj = sig ? ((gj * ns + gj) * ns + gj) * ns + gi : ((gj * ns + gj) * ns + gi) * ns + gj;
+    const int oth = sig ? 0 : ns2;   // the other spin's block
+    const double gd0 = d0[sig * ns + gi] - d0[sig * ns + gj];
+    cd y1 = cmk(0.0, 0.0), acc1 = cmk(0.0, 0.0);
+    if (g1) {
+        y1 = p.y1[ge];
+        sG[0][ge] = y1;
+    }
+    __syncthreads();
+    const double h = p.dt;
+    const unsigned long long step0 = p.guard.div[0];
+
+    auto stage = [&](auto stc, const auto* A, auto* out, const cd* X, cd* outG, int step) {
+        constexpr int st = decltype(stc)::value;
+        const double cb = (st == 0 || st == 3) ? h / 6.0 : h / 3.0, cc = st < 2 ? 0.5 * h : h;
+        const cd* Y = X + ns2;
+        auto advance = [&](cd f, cd& y, cd& acc) {   // the update of rk_update
+            if (st == 0) acc = cmk(fma(cb, f.x, y.x), fma(cb, f.y, y.y));
+            else if (st < 3) acc = cmk(fma(cb, f.x, acc.x), fma(cb, f.y, acc.y));
+            else y = cmk(fma(cb, f.x, acc.x), fma(cb, f.y, acc.y));
+            return st == 3 ? y : cmk(fma(cc, f.x, y.x), fma(cc, f.y, y.y));
+        };
+        if (!g1) {
+#pragma unroll
+            for (int q = 0; q < PER; ++q) {
+                const int e = tid + q * nown;
+                if (e < n2) {
+                    unsigned u = pk[q];
+                    if (PER > 1) asm volatile("" : "+v"(u));   // keep derived offsets out of the step loop
+                    const int i = u & 255, j = (u >> 8) & 255, k = (u >> 16) & 255, l = u >> 24;
+                    const cd av = ld_c(A, e);
+                    const cd gs = csub(cadd(Y[i * ns + i], X[j * ns + j]), cadd(Y[k * ns + k], X[l * ns + l]));
+                    cd c = cmul(cmk(fma(U, gs.y, dd0[q]), -U * gs.x), av);
+#pragma unroll
+                    for (int v = 0; v < Z; ++v) {
+                        const cd a = ld_c(A, oi[q][v]), b = ld_c(A, oj[q][v]);
+                        c = cmk(fma(hi[q][v], a.x, fma(hj[q][v], b.x, c.x)), fma(hi[q][v], a.y, fma(hj[q][v], b.y, c.y)));
+                    }
+#pragma unroll
+                    for (int v = 0; v < Z; ++v) {
+                        const cd a = ld_c(A, ok[q][v]), b = ld_c(A, ol[q][v]);
+                        c = cmk(fma(-hk[q][v], a.x, fma(-hl[q][v], b.x, c.x)),
+                                fma(-hk[q][v], a.y, fma(-hl[q][v], b.y, c.y)));
+                    }
+                    // source (eq:soa-cubic-scheme)
+                    const cd xik = X[i * ns + k], xij = X[i * ns + j], xjk = X[j * ns + k], xlk = X[l * ns + k],
+                             xil = X[i * ns + l];
+                    const cd yjl = Y[j * ns + l], yji = Y[j * ns + i], yil = Y[i * ns + l], ykl = Y[k * ns + l],
+                             yjk = Y[j * ns + k];
+                    const double dd = (double)(i == j) - (double)(k == l);
+                    const cd t1 = cmul(csub(cmul(xij, xjk), cmul(xlk, xil)), yjl);
+                    const cd t2 = cmul(csub(cmul(yji, yil), cmul(ykl, yjk)), xik);
+                    c = cadd(c, cadd(cscale(cmul(xik, yjl), U * dd), cscale(cmul_i(cadd(t1, t2)), U)));
+                    if (SE == SE_TPH) {   // L_ijkl = i U (Y_il A_ijki - X_il A_ljkl), partner L_klij
+                        const cd a1 = ld_c(A, e - l + i), a2 = ld_c(A, ((l * ns + j) * ns + k) * ns + l);
+                        const cd b1 = ld_c(A, ((k * ns + l) * ns + i) * ns + k), b2 = ld_c(A, ((j * ns + l) * ns + i) * ns + j);
+                        const cd l1 = cmul_i(csub(cmul(yil, a1), cmul(xil, a2)));
+                        const cd l2 = cmul_i(csub(cmul(Y[k * ns + j], b1), cmul(X[k * ns + j], b2)));
+                        c = cadd(c, cscale(csub(l1, cconj(l2)), U));
+                    }
+                    if (SE == SE_TPP) {   // L_ijkl = delta_ij U A_iikl + i U (Y_ji A_iikl + X_ij A_jjkl), partner L_klij
+                        const int kl = k * ns + l, ij = i * ns + j;
+                        const cd dii = ld_c(A, (i * ns + i) * ns2 + kl), djj = ld_c(A, (j * ns + j) * ns2 + kl);
+                        const cd dkk = ld_c(A, (k * ns + k) * ns2 + ij), dll = ld_c(A, (l * ns + l) * ns2 + ij);
+                        cd l1 = cmul_i(cadd(cmul(yji, dii), cmul(xij, djj)));
+                        if (i == j) l1 = cadd(l1, dii);
+                        cd l2 = cmul_i(cadd(cmul(Y[l * ns + k], dkk), cmul(X[k * ns + l], dll)));
+                        if (k == l) l2 = cadd(l2, dkk);
+                        c = cadd(c, cscale(csub(l1, cconj(l2)), U));
+                    }
+                    st_c(out, e, advance(cmul_mi(c), y2[q], acc2[q]));
+                }
+            }
+        } else {
+            const cd g = X[ge], a = X[oth + gi * ns + gi], b = X[oth + gj * ns + gj];
+            cd c = cmul(cmk(fma(U, a.y - b.y, gd0), -U * (a.x - b.x)), g);
+#pragma unroll
+            for (int v = 0; v < Z; ++v) {
+                const cd u = X[o1[v]], w = X[o2[v]];
+                c = cmk(fma(h1[v], u.x, fma(-h2[v], w.x, c.x)), fma(h1[v], u.y, fma(-h2[v], w.y, c.y)));
+            }
+            c = cadd(c, cscale(cadd(cmul_mi(ld_c(A, ci)), cconj(cmul_mi(ld_c(A, cj)))), U));
+            const cd o = advance(cmul_mi(c), y1, acc1);
+            outG[ge] = o;
+            if (st == 3 && guard_bad(o, gi == gj)) guard_fire(p.guard, 0, step0 + step + 1);
+        }
+        __syncthreads();
+    };
+    for (int step = 0; step < p.nsteps; ++step) {
+        if constexpr (MIXED) {
+            float2* const f0 = sF;
+            float2* const f1 = sF + CAP;
+            stage(std::integral_constant<int, 0>(), sA[0], f0, sG[0], sG[1], step);
+            stage(std::integral_constant<int, 1>(), f0, f1, sG[1], sG[0], step);
+            stage(std::integral_constant<int, 2>(), f1, f0, sG[0], sG[1], step);
+            stage(std::integral_constant<int, 3>(), f0, sA[0], sG[1], sG[0], step);
+        } else {
+            stage(std::integral_constant<int, 0>(), sA[0], sA[1], sG[0], sG[1], step);
+            stage(std::integral_constant<int, 1>(), sA[1], sA[0], sG[1], sG[0], step);
+            stage(std::integral_constant<int, 2>(), sA[0], sA[1], sG[0], sG[1], step);
+            stage(std::integral_constant<int, 3>(), sA[1], sA[0], sG[1], sG[0], step);
+        }
+    }
+#pragma unroll
+    for (int q = 0; q < PER; ++q) {
+        const int e = g1 ? n2 : tid + q * nown;
+        if (e < n2) p.y2[e] = y2[q];
+    }
+    if (g1) p.y1[ge] = y1;
+    __syncthreads();   // every thread has read guard.div[0]
+    if (tid == 0) p.guard.div[0] = step0 + (unsigned long long)p.nsteps;
+}
+
 template <int MODE, int SE, bool MIXED>
 void launch_stage_t(g1g2_ctx* c, const StageArgs& s) {
     if (n_diag(SE) > 0) {
@@ -1442,21 +1619,34 @@ bool hub_persistent_ok(const g1g2_ctx* c) {
     return ns * ns * ns * ns <= PERSIST_MAX_G2 && 2 * ns * ns <= PERSIST_G1 && 2 * ns * z <= PERSIST_NBR;
 }
 
-template <bool MIXED, bool RH>
+template <int SE, bool MIXED>
+void launch_persistent_t(g1g2_ctx* c, const PersistArgs& p) {
+    const HubbardData& H = c->hub;
+    const int ns = H.hdesc[0].ns, z = H.hdesc[0].zmax, n2 = ns * ns * ns * ns, n1 = 2 * ns * ns;
+    const auto threads = [&](int per) { return ((n2 + per - 1) / per + n1 + 63) / 64 * 64; };
+    auto small = [&](auto per, auto zz) {
+        constexpr int PER = decltype(per)::value, Z = decltype(zz)::value;
+        hipLaunchKernelGGL((hub_small_kernel<SE, MIXED, PER, Z>), dim3(1), dim3(threads(PER)), 0, c->stream, p);
+    };
+    typedef std::integral_constant<int, 1> one;
+    typedef std::integral_constant<int, 2> two;
+    typedef std::integral_constant<int, 4> four;
+    if (H.realhop && ns <= 5 && z <= 2) small(one(), two());
+    else if (H.realhop && ns <= 5 && z <= 4) small(one(), four());
+    else if (H.realhop && ns <= 6 && z <= 2) small(two(), two());
+    else if (H.realhop && ns <= 6 && z <= 4) small(two(), four());
+    else if (H.realhop)
+        hipLaunchKernelGGL((hub_persistent_kernel<SE, MIXED, true>), dim3(1), dim3(PERSIST_THREADS), 0, c->stream, p);
+    else
+        hipLaunchKernelGGL((hub_persistent_kernel<SE, MIXED, false>), dim3(1), dim3(PERSIST_THREADS), 0, c->stream, p);
+}
+
+template <bool MIXED>
 void launch_persistent(g1g2_ctx* c, const PersistArgs& p) {
     switch (c->d.selfenergy) {
-        case G1G2_TPP:
-            hipLaunchKernelGGL((hub_persistent_kernel<SE_TPP, MIXED, RH>), dim3(1), dim3(PERSIST_THREADS), 0,
-                               c->stream, p);
-            break;
-        case G1G2_TPH:
-            hipLaunchKernelGGL((hub_persistent_kernel<SE_TPH, MIXED, RH>), dim3(1), dim3(PERSIST_THREADS), 0,
-                               c->stream, p);
-            break;
-        default:
-            hipLaunchKernelGGL((hub_persistent_kernel<SE_SOA, MIXED, RH>), dim3(1), dim3(PERSIST_THREADS), 0,
-                               c->stream, p);
-            break;
+        case G1G2_TPP: launch_persistent_t<SE_TPP, MIXED>(c, p); break;
+        case G1G2_TPH: launch_persistent_t<SE_TPH, MIXED>(c, p); break;
+        default: launch_persistent_t<SE_SOA, MIXED>(c, p); break;
     }
 }
 
@@ -1466,14 +1656,8 @@ g1g2_status hub_step_persistent(g1g2_ctx* c, double dt, int64_t nsteps) {
     for (int64_t n = 0; n < nsteps;) {
         const int chunk = (int)std::min<int64_t>(nsteps - n, 1024);
         PersistArgs p{H.desc, H.nbr, H.hop, H.d0, H.xdrv, c->y.g1, c->y.g2, dt, chunk, guard_of(c)};
-        const bool mixed = c->d.precision == G1G2_MIXED;
-        if (H.realhop) {
-            if (mixed) launch_persistent<true, true>(c, p);
-            else launch_persistent<false, true>(c, p);
-        } else {
-            if (mixed) launch_persistent<true, false>(c, p);
-            else launch_persistent<false, false>(c, p);
-        }
+        if (c->d.precision == G1G2_MIXED) launch_persistent<true>(c, p);
+        else launch_persistent<false>(c, p);
         HIP_OK(c, hipGetLastError());
         n += chunk;
     }

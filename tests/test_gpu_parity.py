@@ -180,6 +180,37 @@ def test_hubbard_persistent_small_cluster(lib, ns, se):
     pr.close()
 
 
+@pytest.mark.parametrize("lx,ly,periodic", [(1, 1, False), (4, 1, False), (5, 1, True), (6, 1, False), (2, 2, False),
+                                            (3, 2, False)])
+@pytest.mark.parametrize("se", ["soa", "tpp", "tph"])
+@pytest.mark.parametrize("prec", ["fp64", "mixed"])
+def test_hubbard_owned_element_steps(lib, lx, ly, periodic, se, prec):
+    """Clusters of up to six sites, whose G2 and G1 elements have a thread each (one
+    or two G2 elements, two or four neighbour slots): 300 steps in one call against
+    the row kernel's launched stages, to the bound of the persistent kernel's test."""
+    from paper_2002_12717_amd import binding as B
+    say(f"[owned elements] {lx}x{ly} {se} {prec}")
+    r = rng(117, lx, ly, len(se))
+    h = square_hopping(lx, ly, periodic=False) if ly > 1 else chain_hopping(lx, periodic=periodic)
+    ns = lx * ly
+    h0 = np.stack([h + np.diag(r.uniform(-0.5, 0.5, ns)), 0.7 * h]).astype(complex)
+    g1 = np.stack([random_gless(ns, r), random_gless(ns, r)])
+    out = []
+    for flags in (0, B.HUB_ROW_KERNEL):
+        p = B.Propagator(B.HUBBARD, _se(se), ns, h0, g1, U=0.9, flags=flags,
+                         precision=B.FP64 if prec == "fp64" else B.MIXED)
+        assert p.step_path() == ("hub_row" if flags else "hub_persistent")
+        p.step(0.01, 300)
+        out.append(p.get_state()[:2])
+        p.close()
+    e1 = float(np.abs(out[0][0] - out[1][0]).max())
+    e2 = float(np.abs(out[0][1] - out[1][1]).max())
+    say(f"   max diff G1 {e1:.2e}  G2 {e2:.2e}")
+    # binary32 stage copies round differently where the sums differ in the last bit
+    tol = 1e-12 if prec == "fp64" else 1e-6
+    assert e1 < tol and e2 < tol
+
+
 def test_hubbard_persistent_long_call_and_one_cluster_batch(lib):
     """A call of 2,500 steps (three launches of the persistent work-group, the
     last one partial) against 25 calls of 100 steps of the launched stages;
