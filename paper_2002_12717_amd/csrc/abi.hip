@@ -111,7 +111,7 @@ g1g2_status store_component(g1g2_ctx* c, const cd* src, void* dst, bool device, 
 g1g2_status stage(g1g2_ctx* c, int mode, double t, const Regs& in, const Regs& y, const Regs& acc,
                   const Regs& out, double cb, double cc) {
     if (c->d.basis == G1G2_HUBBARD) return hub_stage(c, mode, t, in, y, acc, out, cb, cc);
-    if (c->d.basis == G1G2_JELLIUM) return jel_stage(c, mode, in, y, acc, out, cb, cc);
+    if (c->d.basis == G1G2_JELLIUM) return jel_stage(c, mode, in, y, y, y, acc, out, cb, cc);   // RK_RHS
     return gen_stage(c, mode, t, in, y, acc, out, cb, cc);
 }
 
@@ -122,6 +122,14 @@ g1g2_status rk4_step(g1g2_ctx* c, double t, double dt) {
                    ? hub_tile_step(c, t, dt, c->y, c->s0, c->s1, c->s0, c->acc, false, true)
                    : hub_tile_step(c, t, dt, c->y, c->s0, c->s1, c->acc, c->acc, false, true);
     g1g2_status s;
+    if (c->d.basis == G1G2_JELLIUM) {   // binary64: the third stage register is Y4 (acc is free)
+        const Regs &y = c->y, &y2 = c->s0, &y3 = c->s1, &acc = c->acc;
+        const Regs& y4 = c->d.precision == G1G2_MIXED ? c->s0 : c->acc;
+        if ((s = jel_stage(c, RK_FIRST, y, y, y2, y3, acc, y2, dt / 6.0, dt / 2.0)) != G1G2_OK) return s;
+        if ((s = jel_stage(c, RK_MID, y2, y, y2, y3, acc, y3, dt / 3.0, dt / 2.0)) != G1G2_OK) return s;
+        if ((s = jel_stage(c, RK_MID, y3, y, y2, y3, acc, y4, dt / 3.0, dt)) != G1G2_OK) return s;
+        return jel_stage(c, RK_LAST, y4, y, y2, y3, acc, y, dt / 6.0, 0.0);
+    }
     if ((s = stage(c, RK_FIRST, t, c->y, c->y, c->acc, c->s0, dt / 6.0, dt / 2.0)) != G1G2_OK) return s;
     if ((s = stage(c, RK_MID, t + 0.5 * dt, c->s0, c->y, c->acc, c->s1, dt / 3.0, dt / 2.0)) != G1G2_OK)
         return s;
@@ -367,7 +375,7 @@ g1g2_status g1g2_rhs(g1g2_ctx* c, double t, const void* G1, const void* G2, void
         Regs in{(cd*)G1, (cd*)G2};
         Regs out{(cd*)dG1, (cd*)dG2};
         s = c->d.basis == G1G2_HUBBARD ? hub_stage(c, RK_RHS, t, in, in, in, out, 0.0, 0.0)
-                                       : jel_stage(c, RK_RHS, in, in, in, out, 0.0, 0.0);
+                                       : jel_stage(c, RK_RHS, in, in, in, in, in, out, 0.0, 0.0);
         if (s != G1G2_OK) return s;
         HIP_OK(c, hipStreamSynchronize(c->stream));
         return G1G2_OK;

@@ -259,8 +259,10 @@ g1g2_status jel_setup(g1g2_ctx* c, const int* dims, const double* eps, const dou
 void jel_free(g1g2_ctx* c);
 // the state register y changed (init, set_state): recompute the sums of its G2
 g1g2_status jel_state_changed(g1g2_ctx* c);
-g1g2_status jel_stage(g1g2_ctx* c, int mode, const Regs& in, const Regs& y, const Regs& acc, const Regs& out,
-                      double cb, double cc);
+// y2, y3: in binary64, which keeps no running sum, the outputs of the first two
+// stages (read by the last one); acc: the running sum of mixed precision
+g1g2_status jel_stage(g1g2_ctx* c, int mode, const Regs& in, const Regs& y, const Regs& y2, const Regs& y3,
+                      const Regs& acc, const Regs& out, double cb, double cc);
 g1g2_status jel_observables(g1g2_ctx* c, const Regs& s, g1g2_obs* o);
 
 // ---- adjoint (adjoint.hip)

@@ -19,13 +19,8 @@
 // caller (full) reads it.  The tile is read back, transposed through LDS and
 // written in whole rows.
 //
-// In binary64 the Runge-Kutta step keeps no running sum: the stage inputs
-// Y2 = y + dt/2 k1, Y3 = y + dt/2 k2, Y4 = y + dt k3 hold the slopes, and
-//     y' = y + [(Y2 - y) + 2 (Y3 - y) + (Y4 - y)] / 3 + dt/6 k4,
-// whose differences are exact up to one rounding of the stage inputs.  A stage
-// then moves one state less; the rounding error does not grow (three roundings
-// of weight 1/3, 2/3, 1/3 against one for each of the three running sums).
-// Mixed precision stores the stage inputs in binary32 and keeps the sum.
+// In binary64 the Runge-Kutta step keeps no running sum (rk_close); mixed
+// precision stores the stage inputs in binary32 and keeps it.
 //
 // Condition: hermitian state (checked when a state is set, hub_check_state), real
 // hoppings, ns <= 64, at most Z_MAX_ROW neighbours per site.
@@ -98,11 +93,7 @@ __device__ __forceinline__ cd tile_update(unsigned e, cd f, cd av, const cd* __r
         const cd a = ld_nt(acc + e);
         return cmk(fma(cb, f.x, a.x), fma(cb, f.y, a.y));
     }
-    const cd yv = ld_nt(y + e), a = ld_nt(r2 + e), b = ld_nt(r3 + e);
-    constexpr double third = 1.0 / 3.0;
-    const double sx = (a.x - yv.x) + 2.0 * (b.x - yv.x) + (av.x - yv.x);
-    const double sy = (a.y - yv.y) + 2.0 * (b.y - yv.y) + (av.y - yv.y);
-    return cmk(yv.x + fma(cb, f.x, sx * third), yv.y + fma(cb, f.y, sy * third));
+    return rk_close(ld_nt(y + e), ld_nt(r2 + e), ld_nt(r3 + e), av, f, cb);
 }
 
 // G1 of one cluster (eq:eom_g1_hubbard); the collision integral's elements of A

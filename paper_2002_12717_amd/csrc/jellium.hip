@@ -95,6 +95,7 @@ struct PrepArgs {
     const cd* y1;
     cd* acc1;
     cd* out1;
+    const cd *r21, *r31;      // binary64: Y2 and Y3 (last stage); null in mixed precision, which keeps acc
     double cb, cc;
     const cd* sc;             // [3][nb][nb] middle sums of the stage input
     const cd* sb;             // [nb][nb] down-spin sums from the up-down block
@@ -148,7 +149,13 @@ __global__ __launch_bounds__(JEL_THREADS) void jel_prep_kernel(PrepArgs s) {
     const cd I = cmul_mi(cmk(red[0][0], red[1][0]));
     const cd f = cmk(0.0, -2.0 * I.x);
     if (MODE == RK_FIRST && e == 0) guard_begin_step(s.guard);
-    rk_update<MODE>(e, f, s.in1[e], s.y1, s.acc1, s.out1, s.cb, s.cc);
+    if (MODE == RK_RHS || !s.r21) {
+        rk_update<MODE>(e, f, s.in1[e], s.y1, s.acc1, s.out1, s.cb, s.cc);
+    } else {
+        const cd y = s.y1[e];
+        s.out1[e] = MODE == RK_LAST ? rk_close(y, s.r21[e], s.r31[e], s.in1[e], f, s.cb)
+                                    : cmk(fma(s.cc, f.x, y.x), fma(s.cc, f.y, y.y));
+    }
     if (MODE == RK_LAST && guard_bad(s.out1[e], true)) guard_fire(s.guard, 0, s.guard.div[0]);
 }
 
@@ -161,7 +168,8 @@ struct StageArgsJ {
     const cd* skew;           // [2][nb][nb] S^a_{Pb+Q,Q} at [a][Pb][Q] (GW)
     const void* in2;          // stage input G2 [3][nb]^3 (binary64 or binary32 storage)
     const cd* y2;
-    cd* acc2;
+    cd* acc2;                 // running sum (mixed precision)
+    const cd *r22, *r32;      // binary64, last stage: Y2 and Y3
     void* out2;
     double cb, cc;
     int exch;                 // source with the exchange term (Psi^-)
@@ -248,6 +256,11 @@ __global__ __launch_bounds__(64 * JEL_WAVES) void jel_stage_kernel(StageArgsJ s)
     const TI* in = static_cast<const TI*>(s.in2) + c * n3;
     const cd* y = s.y2 + c * n3;
     cd* acc = s.acc2 + c * n3;
+    // binary64 keeps no running sum (rk_close); the stage copies of mixed precision
+    // are binary32 and it does.  6x6x6 GW, binary64, mean stage: 470 us with the sum
+    constexpr bool SUM = std::is_same<TI, float2>::value || std::is_same<TO, float2>::value;
+    const cd* r2 = s.r22 + c * n3;
+    const cd* r3 = s.r32 + c * n3;
     TO* out = static_cast<TO*>(s.out2) + c * n3;
     for (int Pb = wave; Pb < nb; Pb += JEL_WAVES) {
         const JMom mPb = jdec(g, __builtin_amdgcn_readfirstlane(Pb));
@@ -311,17 +324,24 @@ __global__ __launch_bounds__(64 * JEL_WAVES) void jel_stage_kernel(StageArgsJ s)
                     o = f;
                     st_c(out, (long long)e, f);
                 } else if (MODE == RK_FIRST) {
-                    acc[e] = cmk(fma(s.cb, f.x, av.x), fma(s.cb, f.y, av.y));
+                    if (SUM) acc[e] = cmk(fma(s.cb, f.x, av.x), fma(s.cb, f.y, av.y));
                     o = cmk(fma(s.cc, f.x, av.x), fma(s.cc, f.y, av.y));
                     st_c(out, (long long)e, o);
                 } else if (MODE == RK_MID) {
-                    const cd ac = acc[e], yv = y[e];
-                    acc[e] = cmk(fma(s.cb, f.x, ac.x), fma(s.cb, f.y, ac.y));
+                    const cd yv = y[e];
+                    if (SUM) {
+                        const cd ac = acc[e];
+                        acc[e] = cmk(fma(s.cb, f.x, ac.x), fma(s.cb, f.y, ac.y));
+                    }
                     o = cmk(fma(s.cc, f.x, yv.x), fma(s.cc, f.y, yv.y));
                     st_c(out, (long long)e, o);
                 } else {
-                    const cd ac = acc[e];
-                    o = cmk(fma(s.cb, f.x, ac.x), fma(s.cb, f.y, ac.y));
+                    if (SUM) {
+                        const cd ac = acc[e];
+                        o = cmk(fma(s.cb, f.x, ac.x), fma(s.cb, f.y, ac.y));
+                    } else {
+                        o = rk_close(y[e], r2[e], r3[e], av, f, s.cb);
+                    }
                     st_c(out, (long long)e, o);
                 }
                 o = stored_value<TO>(o);                    // as stored (rounded when binary32)
@@ -585,8 +605,8 @@ void launch_stage(g1g2_ctx* c, const StageArgsJ& s) {
 }
 
 template <int MODE>
-g1g2_status jel_stage_t(g1g2_ctx* c, const Regs& in, const Regs& y, const Regs& acc, const Regs& out, double cb,
-                        double cc, int rbuf, int wbuf) {
+g1g2_status jel_stage_t(g1g2_ctx* c, const Regs& in, const Regs& y, const Regs& y2, const Regs& y3, const Regs& acc,
+                        const Regs& out, double cb, double cc, int rbuf, int wbuf) {
     JelliumData& J = c->jel;
     PrepArgs p{};
     p.g = grid_of(c);
@@ -596,6 +616,9 @@ g1g2_status jel_stage_t(g1g2_ctx* c, const Regs& in, const Regs& y, const Regs& 
     p.y1 = y.g1;
     p.acc1 = acc.g1;
     p.out1 = out.g1;
+    const bool sum = c->d.precision == G1G2_MIXED;
+    p.r21 = sum ? nullptr : y2.g1;
+    p.r31 = sum ? nullptr : y3.g1;
     p.cb = cb;
     p.cc = cc;
     p.sc = J.sc[rbuf];
@@ -618,6 +641,8 @@ g1g2_status jel_stage_t(g1g2_ctx* c, const Regs& in, const Regs& y, const Regs& 
     s.in2 = in.g2;
     s.y2 = y.g2;
     s.acc2 = acc.g2;
+    s.r22 = y2.g2;
+    s.r32 = y3.g2;
     s.out2 = out.g2;
     s.cb = cb;
     s.cc = cc;
@@ -728,13 +753,13 @@ g1g2_status jel_state_changed(g1g2_ctx* c) {
     return jel_reduce(c, c->y.g2, 0);
 }
 
-g1g2_status jel_stage(g1g2_ctx* c, int mode, const Regs& in, const Regs& y, const Regs& acc, const Regs& out,
-                      double cb, double cc) {
+g1g2_status jel_stage(g1g2_ctx* c, int mode, const Regs& in, const Regs& y, const Regs& y2, const Regs& y3,
+                      const Regs& acc, const Regs& out, double cb, double cc) {
     JelliumData& J = c->jel;
     if (mode == RK_RHS) {   // a plain right-hand side of a caller state: its sums in buffer set 2
         g1g2_status s = jel_reduce(c, in.g2, 2);
         if (s != G1G2_OK) return s;
-        return jel_stage_t<RK_RHS>(c, in, y, acc, out, cb, cc, 2, 2);
+        return jel_stage_t<RK_RHS>(c, in, y, y, y, acc, out, cb, cc, 2, 2);
     }
     // the propagated registers alternate between buffer sets 0 and 1: a step
     // starts with the sums of y in set 0 and its last stage leaves those of the
@@ -742,9 +767,9 @@ g1g2_status jel_stage(g1g2_ctx* c, int mode, const Regs& in, const Regs& y, cons
     const int rbuf = J.parity, wbuf = J.parity ^ 1;
     J.parity ^= 1;
     switch (mode) {
-        case RK_FIRST: return jel_stage_t<RK_FIRST>(c, in, y, acc, out, cb, cc, rbuf, wbuf);
-        case RK_MID: return jel_stage_t<RK_MID>(c, in, y, acc, out, cb, cc, rbuf, wbuf);
-        default: return jel_stage_t<RK_LAST>(c, in, y, acc, out, cb, cc, rbuf, wbuf);
+        case RK_FIRST: return jel_stage_t<RK_FIRST>(c, in, y, y2, y3, acc, out, cb, cc, rbuf, wbuf);
+        case RK_MID: return jel_stage_t<RK_MID>(c, in, y, y2, y3, acc, out, cb, cc, rbuf, wbuf);
+        default: return jel_stage_t<RK_LAST>(c, in, y, y2, y3, acc, out, cb, cc, rbuf, wbuf);
     }
 }
 
