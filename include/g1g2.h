@@ -17,6 +17,10 @@
  *   general basis (nb spin orbitals):  h0, G1: [nb][nb];  w, G2: [nb]^4
  *   Hubbard basis (nb sites):          h0, G1: [2][nb][nb] (spin up, spin down);
  *                                      G2 = G2^{up down up down}: [nb]^4
+ * States obey eq:Gsymm_b, G2_ijkl = conj(G2_klij), and G^< is anti-Hermitian; the
+ * general basis relies on it.  Large Hubbard clusters evaluate one triangle of a
+ * state that has the symmetry (to 2^-44, checked when it is set) and every
+ * element of one that has not.
  *
  * Pointers are host memory unless G1G2_PTR_DEVICE is set in desc.flags (then
  * they are device pointers on the current HIP device, e.g. torch data_ptr()).
@@ -309,7 +313,10 @@ g1g2_status g1g2_batch_get_state(g1g2_ctx* ctx, int32_t cluster, void* G1, void*
  * ceil(sqrt(nsteps / 4))); g1g2_adjoint recomputes one segment at a time and
  * keeps its states and Runge-Kutta stage states, so device memory grows by
  * about (nsteps/interval + 4 interval + 8) states (a state of ns = 64 is
- * 268 MB: 4000 steps hold about 70 GB).
+ * 268 MB: 4000 steps hold about 70 GB).  With interval <= 0 a short run (at most
+ * 128 stage states, and an eighth of the device's memory) keeps the states of all
+ * its steps instead and recomputes nothing.  The buffers stay with the context
+ * and serve the next gradient of the same shape.
  * g1g2_adjoint then returns the loss
  *   L = sum_i a[i] d_i(T) + sum_i b[i] (n^up_ii(T) + n^dn_ii(T)),
  *   n_ii = Im G^<_ii,  d_i = n^up_ii n^dn_ii - Re G2_iiii,

@@ -119,8 +119,8 @@ g1g2_status stage(g1g2_ctx* c, int mode, double t, const Regs& in, const Regs& y
 g1g2_status rk4_step(g1g2_ctx* c, double t, double dt) {
     if (hub_tile_ok(c))   // mixed precision keeps the running sum, binary64 the third stage register
         return c->d.precision == G1G2_MIXED
-                   ? hub_tile_step(c, t, dt, c->y, c->s0, c->s1, c->s0, c->acc, false, true)
-                   : hub_tile_step(c, t, dt, c->y, c->s0, c->s1, c->acc, c->acc, false, true);
+                   ? hub_tile_step(c, t, dt, c->y, c->y, c->s0, c->s1, c->s0, c->acc, false, true)
+                   : hub_tile_step(c, t, dt, c->y, c->y, c->s0, c->s1, c->acc, c->acc, false, true);
     g1g2_status s;
     if (c->d.basis == G1G2_JELLIUM) {   // binary64: the third stage register is Y4 (acc is free)
         const Regs &y = c->y, &y2 = c->s0, &y3 = c->s1, &acc = c->acc;
@@ -204,6 +204,41 @@ g1g2_status capture(g1g2_ctx* c, double dt, int gsteps) {
 }
 
 }  // namespace
+
+g1g2_status step_begin(g1g2_ctx* c) {   // the steps of this call are numbered from the completed ones
+    hipLaunchKernelGGL(guard_count_kernel, dim3(1), dim3(1), 0, c->stream, c->ddiv, (unsigned long long)c->step);
+    HIP_OK(c, hipGetLastError());
+    prof_mark(c, "guard_count");
+    return G1G2_OK;
+}
+
+g1g2_status step_end(g1g2_ctx* c, double t, int64_t nsteps) {
+    c->t = t;
+    c->step += nsteps;
+    int flag = 0;
+    HIP_OK(c, hipMemcpyAsync(&flag, c->dflag, sizeof(int), hipMemcpyDeviceToHost, c->stream));
+    HIP_OK(c, hipStreamSynchronize(c->stream));
+    if (flag) {
+        std::vector<long long> first;
+        g1g2_status s = guard_read(c, first);
+        if (s != G1G2_OK) return s;
+        int q0 = -1, nbad = 0;
+        for (int q = 0; q < c->nguard; ++q)
+            if (first[q] >= 0) {
+                ++nbad;
+                if (q0 < 0 || first[q] < first[q0]) q0 = q;
+            }
+        std::string msg = "non-finite state or occupation outside [-0.5, 1.5]";
+        if (q0 >= 0) {
+            msg += " after step " + std::to_string(first[q0]);
+            if (c->nguard > 1)
+                msg += " in cluster " + std::to_string(q0) + " (" + std::to_string(nbad) + " of " +
+                       std::to_string(c->nguard) + " clusters flagged; see g1g2_batch_observables)";
+        }
+        return set_error(c, G1G2_EDIVERGED, msg);
+    }
+    return G1G2_OK;
+}
 
 extern "C" {
 
@@ -393,15 +428,9 @@ g1g2_status g1g2_rhs(g1g2_ctx* c, double t, const void* G1, const void* G2, void
 g1g2_status g1g2_step_rk4(g1g2_ctx* c, double dt, int64_t nsteps) {
     if (!c || nsteps < 0 || !(dt > 0.0) || !std::isfinite(dt)) return G1G2_EINVAL;
     const double t0 = c->t;
-    const int64_t step0 = c->step;
     g1g2_status s;
     int64_t n = 0;
-    if (nsteps > 0) {   // the steps of this call are numbered from the completed ones
-        hipLaunchKernelGGL(guard_count_kernel, dim3(1), dim3(1), 0, c->stream, c->ddiv,
-                           (unsigned long long)step0);
-        HIP_OK(c, hipGetLastError());
-        prof_mark(c, "guard_count");
-    }
+    if (nsteps > 0 && (s = step_begin(c)) != G1G2_OK) return s;
     if (c->d.basis == G1G2_HUBBARD && hub_persistent_ok(c)) {
         if ((s = hub_step_persistent(c, dt, nsteps)) != G1G2_OK) return s;
         n = nsteps;
@@ -414,30 +443,7 @@ g1g2_status g1g2_step_rk4(g1g2_ctx* c, double dt, int64_t nsteps) {
     }
     for (; n < nsteps; ++n)
         if ((s = rk4_step(c, t0 + (double)n * dt, dt)) != G1G2_OK) return s;
-    c->t = t0 + (double)nsteps * dt;
-    c->step = step0 + nsteps;
-    int flag = 0;
-    HIP_OK(c, hipMemcpyAsync(&flag, c->dflag, sizeof(int), hipMemcpyDeviceToHost, c->stream));
-    HIP_OK(c, hipStreamSynchronize(c->stream));
-    if (flag) {
-        std::vector<long long> first;
-        if ((s = guard_read(c, first)) != G1G2_OK) return s;
-        int q0 = -1, nbad = 0;
-        for (int q = 0; q < c->nguard; ++q)
-            if (first[q] >= 0) {
-                ++nbad;
-                if (q0 < 0 || first[q] < first[q0]) q0 = q;
-            }
-        std::string msg = "non-finite state or occupation outside [-0.5, 1.5]";
-        if (q0 >= 0) {
-            msg += " after step " + std::to_string(first[q0]);
-            if (c->nguard > 1)
-                msg += " in cluster " + std::to_string(q0) + " (" + std::to_string(nbad) + " of " +
-                       std::to_string(c->nguard) + " clusters flagged; see g1g2_batch_observables)";
-        }
-        return set_error(c, G1G2_EDIVERGED, msg);
-    }
-    return G1G2_OK;
+    return step_end(c, t0 + (double)nsteps * dt, nsteps);
 }
 
 g1g2_status g1g2_step_path(const g1g2_ctx* c, int32_t* path) {

@@ -28,6 +28,7 @@
 #include <algorithm>
 #include <cmath>
 #include <cstring>
+#include <new>
 #include <vector>
 
 #include "ctx.h"
@@ -474,8 +475,20 @@ __global__ void adj_terminal_kernel(Cl a, const cd* __restrict__ A, const double
 // ---------------------------------------------------------------------------- host
 namespace {
 
+// Stage states that the forward pass may keep when the library chooses the
+// interval: with four states per step the reverse sweep recomputes nothing.  Up to
+// this many (and an eighth of the device's memory) they cost no more than the
+// checkpoints and segments of a longer run would.
+constexpr int64_t ADJ_KEEP_STATES = 128;
+
 struct AdjState {
     int64_t nsteps = 0;
+    int64_t have_steps = 0;    // steps, interval and storage the buffers below were made for
+    int have_interval = 0;
+    size_t have_n1 = 0, have_n2 = 0;
+    bool have_mixed = false, have_keep = false;
+    bool ready = false;        // its buffers are complete (a forward pass has begun)
+    bool keep = false;         // one segment, whose states the forward pass kept
     bool mixed = false;        // binary32 G2 stage copies (Y2, Y3, Y4), as the mixed forward stages
     int interval = 0;
     double dt = 0.0, t0 = 0.0;
@@ -618,39 +631,85 @@ g1g2_status g1g2_forward_checkpointed(g1g2_ctx* c, double dt, int64_t nsteps, in
     if (c->hub.hdesc[0].ns > 64) return set_error(c, G1G2_EUNSUPPORTED, "adjoint supports ns <= 64");
     if (c->has_switch())
         return set_error(c, G1G2_EUNSUPPORTED, "the adjoint takes a constant U (switching is set)");
-    adj_free(c);
-    AdjState* st = new AdjState();
-    c->adj = st;
-    st->nsteps = nsteps;
-    st->mixed = c->d.precision == G1G2_MIXED;
+    const bool mixed = c->d.precision == G1G2_MIXED;
     // default: the interval that minimizes checkpoints + four states per segment step
-    st->interval = interval > 0 ? interval
-                                : std::max<int>(1, (int)std::ceil(std::sqrt((double)nsteps / 4.0)));
+    const int def = std::max<int>(1, (int)std::ceil(std::sqrt((double)nsteps / 4.0)));
+    const int group = interval > 0 ? interval : def;   // steps between divergence checks
+    size_t mtotal = 0;
+    HIP_OK(c, hipDeviceTotalMem(&mtotal, c->device));
+    const bool keep = interval <= 0 && hub_tile_ok(c) && 4 * nsteps <= ADJ_KEEP_STATES &&
+                      4 * (size_t)nsteps * c->n2 * sizeof(cd) <= mtotal / 8;
+    const int seglen = keep ? (int)nsteps : group;
+    AdjState* st = adj_of(c);
+    // the buffers of the last gradient serve again while its shape stays (allocating
+    // and releasing the 8x8 cluster's 56 states took 9 ms of a 77 ms gradient)
+    const bool reuse = st && st->have_steps == nsteps && st->have_interval == seglen && st->have_n1 == c->n1 &&
+                       st->have_n2 == c->n2 && st->have_mixed == mixed && st->have_keep == keep;
+    g1g2_status s;
+    if (!reuse) {
+        adj_free(c);
+        st = new (std::nothrow) AdjState();
+        if (!st) return set_error(c, G1G2_ENOMEM, "adjoint state");
+        c->adj = st;
+    }
+    st->ready = false;
+    st->nsteps = nsteps;
+    st->mixed = mixed;
+    st->keep = keep;
+    st->interval = seglen;
     st->dt = dt;
     st->t0 = c->t;
     st->nck = (int)((nsteps + st->interval - 1) / st->interval);
-    g1g2_status s;
-    st->ckpt.resize(st->nck + 1);       // last slot keeps the final state
-    for (auto& r : st->ckpt)
-        if ((s = alloc_reg(c, r)) != G1G2_OK) return s;
-    for (auto* v : {&st->seg, &st->seg2, &st->seg3, &st->seg4}) {
-        v->resize(st->interval);
-        for (auto& r : *v)
-            if ((s = alloc_reg(c, r, st->mixed && v != &st->seg)) != G1G2_OK) return s;
+    if (!reuse) {
+        st->ckpt.resize(st->nck + 1);       // last slot keeps the final state
+        for (auto& r : st->ckpt)
+            if ((s = alloc_reg(c, r)) != G1G2_OK) return s;
+        for (auto* v : {&st->seg, &st->seg2, &st->seg3, &st->seg4}) {
+            v->resize(st->interval);
+            for (auto& r : *v)
+                if ((s = alloc_reg(c, r, st->mixed && v != &st->seg)) != G1G2_OK) return s;
+        }
+        for (Regs* r : {&st->LAM, &st->LACC, &st->CA, &st->CB})
+            if ((s = alloc_reg(c, *r)) != G1G2_OK) return s;
+        const int ns = c->hub.hdesc[0].ns;
+        HIP_OK(c, hipMalloc(&st->red, (size_t)R_N * ns * ns * sizeof(cd)));
+        st->pairs_per_part = ADJ_PAIRS_PER_PART;
+        st->nparts = (ns * ns + ADJ_PAIRS_PER_PART - 1) / ADJ_PAIRS_PER_PART;
+        HIP_OK(c, hipMalloc(&st->part, (size_t)st->nparts * ns * ns * 2 * sizeof(cd)));
+        HIP_OK(c, hipMalloc(&st->spart, (size_t)8 * ns * ns * ns * sizeof(cd)));
+        HIP_OK(c, hipMalloc(&st->ebar, (size_t)2 * ns * sizeof(cd)));
+        HIP_OK(c, hipMalloc(&st->gpart, (size_t)(2 + (2 * ns * ns + 255) / 256) * sizeof(double)));
+        HIP_OK(c, hipMalloc(&st->grads, (size_t)4 * nsteps * 2 * sizeof(double)));
+        HIP_OK(c, hipMalloc(&st->dev_ab, (size_t)(2 * ns + 8) * sizeof(double)));
+        st->have_steps = nsteps;
+        st->have_interval = seglen;
+        st->have_n1 = c->n1;
+        st->have_n2 = c->n2;
+        st->have_mixed = mixed;
+        st->have_keep = keep;
     }
-    for (Regs* r : {&st->LAM, &st->LACC, &st->CA, &st->CB})
-        if ((s = alloc_reg(c, *r)) != G1G2_OK) return s;
     const int ns = c->hub.hdesc[0].ns;
-    HIP_OK(c, hipMalloc(&st->red, (size_t)R_N * ns * ns * sizeof(cd)));
     HIP_OK(c, hipMemsetAsync(st->red, 0, (size_t)R_N * ns * ns * sizeof(cd), c->stream));
-    st->pairs_per_part = ADJ_PAIRS_PER_PART;
-    st->nparts = (ns * ns + ADJ_PAIRS_PER_PART - 1) / ADJ_PAIRS_PER_PART;
-    HIP_OK(c, hipMalloc(&st->part, (size_t)st->nparts * ns * ns * 2 * sizeof(cd)));
-    HIP_OK(c, hipMalloc(&st->spart, (size_t)8 * ns * ns * ns * sizeof(cd)));
-    HIP_OK(c, hipMalloc(&st->ebar, (size_t)2 * ns * sizeof(cd)));
-    HIP_OK(c, hipMalloc(&st->gpart, (size_t)(2 + (2 * ns * ns + 255) / 256) * sizeof(double)));
-    HIP_OK(c, hipMalloc(&st->grads, (size_t)4 * nsteps * 2 * sizeof(double)));
-    HIP_OK(c, hipMalloc(&st->dev_ab, (size_t)(2 * ns + 8) * sizeof(double)));
+    st->ready = true;
+    if (keep) {
+        // the steps themselves fill the segment: y_n, Y2, Y3, Y4 of step n, each step
+        // writing the next y_n; checked for divergence as g1g2_step_rk4 does
+        if ((s = copy_reg(c, st->seg[0], c->y)) != G1G2_OK) return s;
+        for (int64_t n = 0; n < nsteps; n += group) {
+            const int64_t m1 = std::min<int64_t>(nsteps, n + group);
+            if ((s = step_begin(c)) != G1G2_OK) return s;
+            for (int64_t m = n; m < m1; ++m) {
+                const Regs& next = m + 1 < nsteps ? st->seg[m + 1] : st->ckpt[st->nck];
+                if ((s = hub_tile_step(c, st->t0 + (double)m * dt, dt, st->seg[m], next, st->seg2[m], st->seg3[m],
+                                       st->seg4[m], c->acc, true, true)) != G1G2_OK)
+                    return s;
+            }
+            const Regs& done = m1 < nsteps ? st->seg[m1] : st->ckpt[st->nck];
+            if ((s = copy_reg(c, c->y, done)) != G1G2_OK) return s;
+            if ((s = step_end(c, c->t + (double)(m1 - n) * dt, m1 - n)) != G1G2_OK) return s;
+        }
+        return G1G2_OK;
+    }
     for (int q = 0; q < st->nck; ++q) {
         if ((s = copy_reg(c, st->ckpt[q], c->y)) != G1G2_OK) return s;
         const int64_t n = std::min<int64_t>(st->interval, nsteps - (int64_t)q * st->interval);
@@ -663,7 +722,7 @@ g1g2_status g1g2_adjoint(g1g2_ctx* c, const double* wa, const double* wb, double
                          double* grad_U, double* loss) {
     if (!c || !wa || !wb) return G1G2_EINVAL;
     AdjState* st = adj_of(c);
-    if (!st) return set_error(c, G1G2_ESTATE, "call g1g2_forward_checkpointed first");
+    if (!st || !st->ready) return set_error(c, G1G2_ESTATE, "call g1g2_forward_checkpointed first");
     HubbardData& H = c->hub;
     const int ns = H.hdesc[0].ns;
     const double dt = st->dt;
@@ -687,15 +746,15 @@ g1g2_status g1g2_adjoint(g1g2_ctx* c, const double* wa, const double* wb, double
         const int64_t n0 = (int64_t)q * st->interval;
         const int64_t n1 = std::min<int64_t>(n0 + st->interval, st->nsteps);
         // recompute the segment forward, keeping y_n and the stage states of every step
-        if ((s = copy_reg(c, c->y, st->ckpt[q])) != G1G2_OK) return s;
-        for (int64_t n = n0; n < n1; ++n) {
+        if (!st->keep && (s = copy_reg(c, c->y, st->ckpt[q])) != G1G2_OK) return s;
+        for (int64_t n = n0; n < n1 && !st->keep; ++n) {
             const int m = (int)(n - n0);
             if ((s = copy_reg(c, st->seg[m], c->y)) != G1G2_OK) return s;
             const double t = st->t0 + (double)n * dt;
             const Regs &s2 = st->seg2[m], &s3 = st->seg3[m], &s4 = st->seg4[m];
             const bool last = n + 1 < n1;
             if (hub_tile_ok(c)) {   // the reverse sweep reads the stage states whole
-                if ((s = hub_tile_step(c, t, dt, c->y, s2, s3, s4, c->acc, true, last)) != G1G2_OK) return s;
+                if ((s = hub_tile_step(c, t, dt, c->y, c->y, s2, s3, s4, c->acc, true, last)) != G1G2_OK) return s;
                 continue;
             }
             if ((s = stage_fwd(c, RK_FIRST, t, c->y, c->y, c->acc, s2, dt / 6.0, dt / 2.0)) != G1G2_OK) return s;

@@ -186,6 +186,12 @@ void prof_mark(g1g2_ctx* c, const char* name);
 
 g1g2_status set_error(g1g2_ctx* c, g1g2_status s, const std::string& msg);
 
+// The frame of a call that advances the state (abi.hip): step_begin numbers the
+// steps to come for the divergence guard; step_end books nsteps completed ones at
+// time t, synchronizes and returns EDIVERGED if the guard has fired.
+g1g2_status step_begin(g1g2_ctx* c);
+g1g2_status step_end(g1g2_ctx* c, double t, int64_t nsteps);
+
 #define HIP_OK(ctx, expr)                                                                  \
     do {                                                                                   \
         hipError_t _e = (expr);                                                            \
@@ -218,15 +224,15 @@ size_t hub_diag_bytes(const g1g2_ctx* c);
 // Stages over one triangle of the pair matrix (hub_tile.hip): set-up after the
 // neighbour tables, the symmetry check of the state y (synchronizes; call
 // whenever a state is set), whether steps take them now, one step, release.
-// hub_tile_step writes y4 by the third stage and, with last, the new state to y;
+// hub_tile_step writes y4 by the third stage and, with last, the new state to out;
 // full: the stage registers are written whole, not only where stages read them.
 constexpr int TILE_ROW_MIN = 44;   // least ns of the wave-per-row form
 constexpr int TILE_VEC = 384;      // most tiles x ns of an item (its LDS vectors)
 g1g2_status hub_tile_setup(g1g2_ctx* c, const std::vector<int>& nbr, const std::vector<int>& per_item);
 g1g2_status hub_check_state(g1g2_ctx* c);
 bool hub_tile_ok(const g1g2_ctx* c);
-g1g2_status hub_tile_step(g1g2_ctx* c, double t, double dt, const Regs& y, const Regs& y2, const Regs& y3,
-                          const Regs& y4, const Regs& acc, bool full, bool last);
+g1g2_status hub_tile_step(g1g2_ctx* c, double t, double dt, const Regs& y, const Regs& out, const Regs& y2,
+                          const Regs& y3, const Regs& y4, const Regs& acc, bool full, bool last);
 void hub_tile_free(g1g2_ctx* c);
 std::vector<WorkItem> xcd_order(const std::vector<WorkItem>& g2, const std::vector<long long>& cost,
                                 const std::vector<WorkItem>& g1);

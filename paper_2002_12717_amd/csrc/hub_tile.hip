@@ -619,10 +619,10 @@ g1g2_status hub_tile_stage(g1g2_ctx* c, int mode, double t, const Regs& in, cons
     return G1G2_OK;
 }
 
-// One step from y, with stage registers Y2, Y3 and a third one: Y4 (binary64) or
+// One step from y to out (which may be y), with stage registers Y2, Y3 and a third one: Y4 (binary64) or
 // the running sum (mixed, where y4 may alias y2).
-g1g2_status hub_tile_step(g1g2_ctx* c, double t, double dt, const Regs& y, const Regs& y2, const Regs& y3,
-                          const Regs& y4, const Regs& acc, bool full, bool last) {
+g1g2_status hub_tile_step(g1g2_ctx* c, double t, double dt, const Regs& y, const Regs& out, const Regs& y2,
+                          const Regs& y3, const Regs& y4, const Regs& acc, bool full, bool last) {
     const bool mixed = c->d.precision == G1G2_MIXED;
     g1g2_status s;
     if ((s = hub_tile_stage(c, RK_FIRST, t, y, y, y, y, acc, y2, dt / 6.0, dt / 2.0, full)) != G1G2_OK) return s;
@@ -630,7 +630,7 @@ g1g2_status hub_tile_step(g1g2_ctx* c, double t, double dt, const Regs& y, const
         return s;
     if ((s = hub_tile_stage(c, RK_MID, t + 0.5 * dt, y3, y, y, y, acc, y4, dt / 3.0, dt, full)) != G1G2_OK) return s;
     if (!last) return G1G2_OK;
-    return hub_tile_stage(c, RK_LAST, t + dt, y4, y, mixed ? y : y2, mixed ? y : y3, acc, y, dt / 6.0, 0.0, full);
+    return hub_tile_stage(c, RK_LAST, t + dt, y4, y, mixed ? y : y2, mixed ? y : y3, acc, out, dt / 6.0, 0.0, full);
 }
 
 void hub_tile_free(g1g2_ctx* c) {

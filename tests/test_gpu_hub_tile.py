@@ -137,3 +137,32 @@ def test_tile_path_needs_a_hermitian_state(lib):
         assert rel(a[0], b[0]) < 1e-12 and rel(a[1], b[1]) < 1e-12
     for x in (p, q, e):
         x.close()
+
+
+@pytest.mark.parametrize("prec", ["fp64", "mixed"])
+def test_gradient_with_kept_states(lib, prec):
+    """A short run keeps the stage states of its forward pass; the gradient equals, bit
+    for bit, the one whose segments are recomputed, also when the buffers serve a
+    second gradient and when the number of steps changes."""
+    from paper_2002_12717_amd import binding as B
+    r = rng(514)
+    ns, h0, g1 = _system(33, 1, False, r)
+    g2 = random_g2(ns, r, scale=0.02, exchange=False)
+    a, b = r.uniform(-1, 1, ns), r.uniform(-1, 1, ns)
+    x = np.arange(ns) - 16.0
+    c, tc = 0.1 * r.standard_normal(5), 0.02 * np.arange(5)
+    out = {}
+    for interval in (0, 2):
+        p = B.Propagator(B.HUBBARD, B.SOA, ns, h0, g1, U=1.1, precision=B.FP64 if prec == "fp64" else B.MIXED)
+        p.set_drive(x, c, tc, 0.02)
+        res = []
+        for steps in (5, 5, 3):
+            p.set_state(g1, g2)
+            p.forward_checkpointed(0.01, steps, interval)
+            res.append(p.adjoint(a, b, 5) + tuple(p.get_state()[:2]))
+        p.close()
+        out[interval] = res
+    for u, v in zip(out[0], out[2]):
+        assert u[0] == v[0] and u[2] == v[2] and np.array_equal(u[1], v[1])
+        assert np.array_equal(u[3], v[3]) and np.array_equal(u[4], v[4])
+    assert out[0][0][0] == out[0][1][0] and np.array_equal(out[0][0][1], out[0][1][1])
