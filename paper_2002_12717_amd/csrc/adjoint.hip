@@ -89,10 +89,19 @@ __device__ __forceinline__ cd wsum(cd v) { return cmk(wsum(v.x), wsum(v.y)); }
 //   kind 2 free (j,k), kind 3 free (k,l), kind 4 free (i,l): X and Y cotangents
 //   kind 5 free (j,l): Y cotangent and M13 = sum conj(A) B
 // Kinds 0, 1, 2, 4 and 5 come from one pass over the cotangent: one work-group
-// per (i, j) slice, wave w over the rows k = w, w + 4, ... with lane = l.  Kind
-// 1 is summed over the slice; kinds 0 and 2 over l within a row, leaving
-// partials per (i, j, k) that adj_slice_fin_kernel sums over j or i; kinds 4
-// and 5 over k, leaving partials per (i, j, l).  Kind 3 is adj_lane_red_kernel.
+// per (i, j) slice, wave w over the rows k = w, w + ADJ_WAVES, ... with lane = l.
+// At fixed (i, j) their weights are products of a factor in k and one in l, so
+// the pass forms only the sums over l of a row,
+//   s1 = sum conj(Y_jl) B, s2 = sum conj(Y_kl) B, s3 = sum conj(Y_il) B, s4 = sum conj(A) B,
+// and the sums over k of a lane,
+//   q1 = sum conj(X_lk) B, q2 = sum conj(X_ik) B, q3 = sum conj(X_jk) B, q4 = sum conj(A) B,
+// eight complex multiply-adds per element instead of 25, and every kind follows
+// from them once per row or lane.  The eight real row sums are reduced together,
+// halving the number of values a lane holds in the first three exchanges: 10
+// exchanges instead of 48, whose LDS permutes bound the pass.  Kind 1 is summed
+// over the slice; kinds 0 and 2 leave partials per (i, j, k) that
+// adj_slice_fin_kernel sums over j or i; kinds 4 and 5 partials per (i, j, l).
+// Kind 3 is adj_lane_red_kernel.
 //
 // The same pass computes the G2 cotangent mu = i gs [conj(E) g + hop stencil
 // applied to g] + collision entries (the commutator stencil is its own
@@ -101,10 +110,32 @@ __device__ __forceinline__ cd wsum(cd v) { return cmk(wsum(v.x), wsum(v.y)); }
 // (cross-lane permute), the other neighbours whole rows; neighbour tables are
 // staged in LDS padded to four entries (a missing neighbour is the site itself
 // with hopping 0).
-__global__ __launch_bounds__(256) void adj_slice_red_kernel(AdjArgs s) {
+// Four waves: 8x8 sites 473 us per pass, eight 493, and 635 before the sums were
+// factored and the loads gathered ahead of the stores (the factored sums alone,
+// loads between stores, 750: more waves in flight without more loads only widened
+// what the L2 has to hold).
+constexpr int ADJ_WAVES = 4;
+
+// Sum of each of eight values over the 64 lanes; lane returns the sum of value
+// lane / 8.
+__device__ __forceinline__ double wsum8(const double (&v)[8], int lane) {
+    double a[4], b[2];
+    const bool h5 = lane & 32, h4 = lane & 16, h3 = lane & 8;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) a[q] = (h5 ? v[q + 4] : v[q]) + __shfl_xor(h5 ? v[q] : v[q + 4], 32, 64);
+#pragma unroll
+    for (int q = 0; q < 2; ++q) b[q] = (h4 ? a[q + 2] : a[q]) + __shfl_xor(h4 ? a[q] : a[q + 2], 16, 64);
+    double c = (h3 ? b[1] : b[0]) + __shfl_xor(h3 ? b[0] : b[1], 8, 64);
+#pragma unroll
+    for (int o = 4; o > 0; o >>= 1) c += __shfl_xor(c, o, 64);
+    return c;
+}
+
+__global__ __launch_bounds__(64 * ADJ_WAVES) void adj_slice_red_kernel(AdjArgs s) {
     constexpr int ZR = 4;
-    __shared__ cd sh4[4][4][64];   // per wave and lane: kinds 4 (X, Y) and 5 (Y, M13)
-    __shared__ double sh1[4][5];   // per wave: kind 1 (X re, im, Y re, im, U)
+    __shared__ cd sh4[ADJ_WAVES][5][64];   // per wave and lane: q1 .. q4 and the k = l term of q2
+    __shared__ double srow[64][8];         // per row k: s1 .. s4
+    __shared__ cd sdia[64];                // per row k: B at l = k
     __shared__ cd eu[64], ed[64];
     __shared__ int snb[2 * 64 * ZR];
     __shared__ cd shp[2 * 64 * ZR];
@@ -138,13 +169,11 @@ __global__ __launch_bounds__(256) void adj_slice_red_kernel(AdjArgs s) {
     for (int q = 0; q < ZR; ++q) src[q] = lane_ok ? nbd[l * ZR + q] : lane;
     const cd ei = eu[i], ej = ed[j], el = ed[l];
     const cd xij = X[i * ns + j], yji = Y[j * ns + i];
-    const cd xil = X[i * ns + l], yjl = Y[j * ns + l], yil = Y[i * ns + l];
-    cd x1 = cmk(0, 0), y1 = cmk(0, 0);
-    double up = 0.0;
-    cd a4x = cmk(0, 0), a4y = cmk(0, 0), a5y = cmk(0, 0), a5m = cmk(0, 0);
+    const cd yjl = Y[j * ns + l], yil = Y[i * ns + l];
+    cd q1 = cmk(0, 0), q2 = cmk(0, 0), q3 = cmk(0, 0), q4 = cmk(0, 0), qd = cmk(0, 0);
     cd* P = s.spart;
-    for (int k = wave; k < ns; k += 4) {
-        cd r0x = cmk(0, 0), r0m = cmk(0, 0), r2x = cmk(0, 0), r2y = cmk(0, 0);
+    for (int k = wave; k < ns; k += ADJ_WAVES) {
+        double sv[8] = {0, 0, 0, 0, 0, 0, 0, 0};
         const int e = ((i * ns + j) * ns + k) * ns + l;
         const cd g = lane_ok ? G[e] : cmk(0.0, 0.0);
         cd vl[ZR];
@@ -158,11 +187,23 @@ __global__ __launch_bounds__(256) void adj_slice_red_kernel(AdjArgs s) {
             const cd ek = eu[k];
             const cd E = cmk(ei.x + ej.x - ek.x - el.x, ei.y + ej.y - ek.y - el.y);
             cd hsum = cmul(cconj(E), g);
+            // every load of the row before its stores
+            cd vi[ZR], vj[ZR], vk[ZR];
 #pragma unroll
             for (int q = 0; q < ZR; ++q) {
-                hsum = cfma(hsum, hu[i * ZR + q], G[e + (nbu[i * ZR + q] - i) * ns3]);
-                hsum = cfma(hsum, hd[j * ZR + q], G[e + (nbd[j * ZR + q] - j) * ns2]);
-                hsum = csub(hsum, cmul(G[e + (nbu[k * ZR + q] - k) * ns], cconj(hu[k * ZR + q])));
+                vi[q] = G[e + (nbu[i * ZR + q] - i) * ns3];
+                vj[q] = G[e + (nbd[j * ZR + q] - j) * ns2];
+                vk[q] = G[e + (nbu[k * ZR + q] - k) * ns];
+            }
+            const cd av = ld_a(s, e);
+            const cd base = ld_nt(s.init ? s.lam2 + e : s.lacc2 + e);
+            const cd lv = s.has_next ? ld_nt(s.lam2 + e) : cmk(0.0, 0.0);
+            const cd xkl = X[k * ns + l], ykl = Y[k * ns + l];
+#pragma unroll
+            for (int q = 0; q < ZR; ++q) {
+                hsum = cfma(hsum, hu[i * ZR + q], vi[q]);
+                hsum = cfma(hsum, hd[j * ZR + q], vj[q]);
+                hsum = csub(hsum, cmul(vk[q], cconj(hu[k * ZR + q])));
                 hsum = csub(hsum, cmul(vl[q], cconj(hd[l * ZR + q])));
             }
             cd mu = cscale(cmul_i(hsum), gs);
@@ -175,90 +216,98 @@ __global__ __launch_bounds__(256) void adj_slice_red_kernel(AdjArgs s) {
                 cd bya = cscale(cmul_i(gy[i * ns + l]), gs), byb = cscale(cmul_i(gy[l * ns + i]), gs);
                 mu = cadd(mu, cscale(cmul_i(cadd(bya, cconj(byb))), a.U));
             }
-            const cd base = s.init ? s.lam2[e] : s.lacc2[e];
-            s.lacc2[e] = cadd(base, mu);
-            if (s.has_next) {
-                const cd lv = s.lam2[e];
-                s.gnext2[e] = cmk(s.alpha * lv.x + s.beta * mu.x, s.alpha * lv.y + s.beta * mu.y);
-            }
-            // source-term reductions
+            st_nt(s.lacc2 + e, cadd(base, mu));
+            if (s.has_next)
+                st_nt(s.gnext2 + e, cmk(s.alpha * lv.x + s.beta * mu.x, s.alpha * lv.y + s.beta * mu.y));
+            // sums of the source-term reductions; X_lk = -conj(X_kl) (G^< is anti-Hermitian, as
+            // the forward stage reads it), so conj(X_lk) = -X_kl
             const cd B = cscale(cmul_i(g), gs);
-            const cd cav = cconj(ld_a(s, e));
-            const cd xik = X[i * ns + k], xjk = X[j * ns + k], yjk = Y[j * ns + k];
-            // X_lk = -conj(X_kl) (G^< is anti-Hermitian, as the forward stage reads it): a row
-            // read instead of a column gather
-            const cd xkl = X[k * ns + l], ykl = Y[k * ns + l];
-            const cd xlk = cmk(-xkl.x, xkl.y);
-            const double dd = (double)(i == j) - (double)(k == l);
-            // kind 0
-            cd w0 = cscale(cconj(yjl), U * dd);
-            w0 = cadd(w0, cscale(cmul_i(cconj(cmul(yji, yil))), -U));
-            w0 = cadd(w0, cscale(cmul_i(cconj(cmul(ykl, yjk))), U));
-            r0x = cmul(w0, B);
-            r0m = cmul(cav, B);
-            // kind 1
-            x1 = cfma(x1, cscale(cmul_i(cconj(cmul(xjk, yjl))), -U), B);
-            y1 = cfma(y1, cscale(cmul_i(cconj(cmul(yil, xik))), -U), B);
-            const cd t1 = cmul(csub(cmul(xij, xjk), cmul(xlk, xil)), yjl);
-            const cd t2 = cmul(csub(cmul(yji, yil), cmul(ykl, yjk)), xik);
-            const cd psi1 = cadd(cscale(cmul(xik, yjl), dd), cmul_i(cadd(t1, t2)));   // Psi / U
-            up += psi1.x * B.x + psi1.y * B.y;
-            // kind 2
-            r2x = cmul(cscale(cmul_i(cconj(cmul(xij, yjl))), -U), B);
-            r2y = cmul(cscale(cmul_i(cconj(cmul(ykl, xik))), U), B);
-            // kind 4
-            a4x = cfma(a4x, cscale(cmul_i(cconj(cmul(xlk, yjl))), U), B);
-            a4y = cfma(a4y, cscale(cmul_i(cconj(cmul(yji, xik))), -U), B);
-            // kind 5
-            cd w5 = cscale(cconj(xik), U * dd);
-            w5 = cadd(w5, cscale(cmul_i(cconj(cmul(xij, xjk))), -U));
-            w5 = cadd(w5, cscale(cmul_i(cconj(cmul(xlk, xil))), U));
-            a5y = cfma(a5y, w5, B);
-            a5m = cfma(a5m, cav, B);
+            const cd cav = cconj(av);
+            const cd xik = X[i * ns + k], xjk = X[j * ns + k];
+            const cd m4 = cmul(cav, B), m2 = cmul(cconj(xik), B);
+            const cd m1 = cmul(cconj(yjl), B), n2 = cmul(cconj(ykl), B), n3 = cmul(cconj(yil), B);
+            q1 = csub(q1, cmul(xkl, B));
+            q2 = cadd(q2, m2);
+            q3 = cfma(q3, cconj(xjk), B);
+            q4 = cadd(q4, m4);
+            if (k == l) {
+                qd = m2;
+                sdia[k] = B;
+            }
+            sv[0] = m1.x;
+            sv[1] = m1.y;
+            sv[2] = n2.x;
+            sv[3] = n2.y;
+            sv[4] = n3.x;
+            sv[5] = n3.y;
+            sv[6] = m4.x;
+            sv[7] = m4.y;
         }
-        r0x = wsum(r0x);
-        r0m = wsum(r0m);
-        r2x = wsum(r2x);
-        r2y = wsum(r2y);
-        if (lane == 0) {
-            const size_t o = ((size_t)i * ns + j) * ns + k;
-            P[0 * (size_t)ns3 + o] = r0x;
-            P[1 * (size_t)ns3 + o] = r0m;
-            P[2 * (size_t)ns3 + o] = r2x;
-            P[3 * (size_t)ns3 + o] = r2y;
-        }
+        const double t = wsum8(sv, lane);
+        if ((lane & 7) == 0) srow[k][lane >> 3] = t;
     }
-    sh4[wave][0][lane] = a4x;
-    sh4[wave][1][lane] = a4y;
-    sh4[wave][2][lane] = a5y;
-    sh4[wave][3][lane] = a5m;
+    sh4[wave][0][lane] = q1;
+    sh4[wave][1][lane] = q2;
+    sh4[wave][2][lane] = q3;
+    sh4[wave][3][lane] = q4;
+    sh4[wave][4][lane] = qd;
+    __syncthreads();
+    if (wave != 0) return;
+    // lane = k: the rows' partials of kinds 0 and 2, the terms of kind 1 and of dL/dU
+    const double dij = i == j ? 1.0 : 0.0;
+    auto iU = [&](cd v) { return cscale(cmul_i(v), U); };   // i U v
+    cd x1 = cmk(0, 0), y1 = cmk(0, 0);
+    double up = 0.0;
+    if (lane_ok) {
+        const int k = lane;
+        const cd s1 = cmk(srow[k][0], srow[k][1]), s2 = cmk(srow[k][2], srow[k][3]);
+        const cd s3 = cmk(srow[k][4], srow[k][5]), s4 = cmk(srow[k][6], srow[k][7]), Bkk = sdia[k];
+        const cd xik = X[i * ns + k], xjk = X[j * ns + k], yjk = Y[j * ns + k];
+        cd r0 = csub(cscale(s1, U * dij), cscale(cmul(cconj(yjk), Bkk), U));
+        r0 = cadd(r0, iU(csub(cmul(cconj(yjk), s2), cmul(cconj(yji), s3))));
+        const size_t o = ((size_t)i * ns + j) * ns + k;
+        P[0 * (size_t)ns3 + o] = r0;
+        P[1 * (size_t)ns3 + o] = s4;
+        const cd c2 = iU(cmul(cconj(xij), s1));
+        P[2 * (size_t)ns3 + o] = cmk(-c2.x, -c2.y);
+        P[3 * (size_t)ns3 + o] = iU(cmul(cconj(xik), s2));
+        const cd u1 = cmul(cconj(xjk), s1), u3 = cmul(cconj(xik), s3);
+        x1 = iU(cmk(-u1.x, -u1.y));
+        y1 = iU(cmk(-u3.x, -u3.y));
+        // conj(Psi) B / U of the row, without its X_lk term
+        cd t = csub(cscale(cmul(cconj(xik), s1), dij), cmul(cconj(cmul(xik, yjk)), Bkk));
+        t = cadd(t, cmul_i(csub(cmul(cconj(cmul(yjk, xik)), s2),
+                                cadd(cmul(cconj(xij), u1), cmul(cconj(yji), u3)))));
+        up = t.x;
+    }
+    if (lane_ok) {   // lane = l: kinds 4 and 5
+        cd v[5];
+#pragma unroll
+        for (int q = 0; q < 5; ++q) {
+            v[q] = sh4[0][q][lane];
+#pragma unroll
+            for (int w = 1; w < ADJ_WAVES; ++w) v[q] = cadd(v[q], sh4[w][q][lane]);
+        }
+        const cd xil = X[i * ns + l];
+        const size_t o = ((size_t)i * ns + j) * ns + l;
+        P[4 * (size_t)ns3 + o] = iU(cmul(cconj(yjl), v[0]));
+        const cd c4 = iU(cmul(cconj(yji), v[1]));
+        P[5 * (size_t)ns3 + o] = cmk(-c4.x, -c4.y);
+        cd a5 = cscale(csub(cscale(v[1], dij), v[4]), U);
+        a5 = cadd(a5, iU(csub(cmul(cconj(xil), v[0]), cmul(cconj(xij), v[2]))));
+        P[6 * (size_t)ns3 + o] = a5;
+        P[7 * (size_t)ns3 + o] = v[3];
+        const cd t = cmul_i(cmul(cconj(cmul(xil, yjl)), v[0]));
+        up += t.x;
+    }
     x1 = wsum(x1);
     y1 = wsum(y1);
     up = wsum(up);
     if (lane == 0) {
-        sh1[wave][0] = x1.x;
-        sh1[wave][1] = x1.y;
-        sh1[wave][2] = y1.x;
-        sh1[wave][3] = y1.y;
-        sh1[wave][4] = up;
-    }
-    __syncthreads();
-    if (wave != 0) return;
-    if (lane_ok) {
-        const size_t o = ((size_t)i * ns + j) * ns + l;
-#pragma unroll
-        for (int q = 0; q < 4; ++q)
-            P[(4 + q) * (size_t)ns3 + o] = cadd(cadd(sh4[0][q][lane], sh4[1][q][lane]),
-                                                cadd(sh4[2][q][lane], sh4[3][q][lane]));
-    }
-    if (lane == 0) {
-        double v[5];
-#pragma unroll
-        for (int q = 0; q < 5; ++q) v[q] = (sh1[0][q] + sh1[1][q]) + (sh1[2][q] + sh1[3][q]);
         cd* R = s.red;
-        R[(R_X + 1) * ns2 + i * ns + j] = cmk(v[0], v[1]);
-        R[(R_Y + 1) * ns2 + j * ns + i] = cmk(v[2], v[3]);
-        R[R_UP * ns2 + i * ns + j] = cmk(v[4], 0.0);
+        R[(R_X + 1) * ns2 + i * ns + j] = x1;
+        R[(R_Y + 1) * ns2 + j * ns + i] = y1;
+        R[R_UP * ns2 + i * ns + j] = cmk(up, 0.0);
     }
 }
 
@@ -580,7 +629,7 @@ AdjArgs make_adj(g1g2_ctx* c, double t, const Regs& S, bool S32, const Regs& gin
 
 g1g2_status vjp(g1g2_ctx* c, const AdjArgs& s) {
     const int ns = s.a.ns, ns2 = ns * ns;
-    hipLaunchKernelGGL(adj_slice_red_kernel, dim3(ns2), dim3(256), 0, c->stream, s);
+    hipLaunchKernelGGL(adj_slice_red_kernel, dim3(ns2), dim3(64 * ADJ_WAVES), 0, c->stream, s);
     prof_mark(c, "adj_slice_red");
     hipLaunchKernelGGL(adj_lane_red_kernel, dim3(ns * s.nparts), dim3(256), 0, c->stream, s);
     prof_mark(c, "adj_lane_red");
