@@ -43,7 +43,7 @@ struct HubbardData {
     int ncl = 0;
     std::vector<ClusterDesc> hdesc;
     ClusterDesc* desc = nullptr;   // device copy
-    WorkItem* work = nullptr;      // device work list
+    WorkItem* work = nullptr;      // device work list; the allocation also holds tiles, twork, tsym and diag
     int nwork = 0;
     bool rows = false;             // row stage kernel (every ns <= 64, <= 4 neighbours)
     bool realhop = false;          // every hopping (off-diagonal h0) is real
@@ -61,9 +61,6 @@ struct HubbardData {
     int ntwork = 0;
     bool tile_row = false;         // one tile per item, a wave per row
     std::vector<std::pair<int, int>> tile_shapes;   // (tiles per item, ns) of the items
-    WorkItem* dtile = nullptr;     // work list of the diagonal tensors
-    int ndtile = 0;
-    cd* tdiag = nullptr;           // the diagonal tensors
     unsigned long long* tsym = nullptr;   // result of the symmetry check
     int* nbr = nullptr;            // concatenated neighbour tables
     cd* hop = nullptr;
@@ -221,19 +218,20 @@ g1g2_status hub_stage(g1g2_ctx* c, int mode, double t, const Regs& in, const Reg
 g1g2_status hub_stage_diag(g1g2_ctx* c, int mode, double t, const Regs& in, const Regs& y,
                            const Regs& acc, const Regs& out, double cb, double cc, cd* diag);
 size_t hub_diag_bytes(const g1g2_ctx* c);
-// Stages over one triangle of the pair matrix (hub_tile.hip): set-up after the
-// neighbour tables, the symmetry check of the state y (synchronizes; call
-// whenever a state is set), whether steps take them now, one step, release.
+// Stages over one triangle of the pair matrix (hub_tile.hip): the lists of its
+// set-up (kept with the work list, hub_setup), the symmetry check of the state y (synchronizes; call
+// whenever a state is set), whether steps take them now, one step.
 // hub_tile_step writes y4 by the third stage and, with last, the new state to out;
 // full: the stage registers are written whole, not only where stages read them.
 constexpr int TILE_ROW_MIN = 44;   // least ns of the wave-per-row form
 constexpr int TILE_VEC = 384;      // most tiles x ns of an item (its LDS vectors)
-g1g2_status hub_tile_setup(g1g2_ctx* c, const std::vector<int>& nbr, const std::vector<int>& per_item);
+void hub_tile_lists(g1g2_ctx* c, const std::vector<ClusterDesc>& desc, const std::vector<int>& nbr,
+                    const std::vector<int>& per_item, std::vector<int>& tiles, std::vector<WorkItem>& work);
+int hub_tile_diags(const g1g2_ctx* c);   // its diagonal tensors per cluster, in units of ns^3
 g1g2_status hub_check_state(g1g2_ctx* c);
 bool hub_tile_ok(const g1g2_ctx* c);
 g1g2_status hub_tile_step(g1g2_ctx* c, double t, double dt, const Regs& y, const Regs& out, const Regs& y2,
                           const Regs& y3, const Regs& y4, const Regs& acc, bool full, bool last);
-void hub_tile_free(g1g2_ctx* c);
 std::vector<WorkItem> xcd_order(const std::vector<WorkItem>& g2, const std::vector<long long>& cost,
                                 const std::vector<WorkItem>& g1);
 // The static device scratch of g1g2_rhs_noalloc on the context's device:

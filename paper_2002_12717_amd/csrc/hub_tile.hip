@@ -25,7 +25,6 @@
 // Condition: hermitian state (checked when a state is set, hub_check_state), real
 // hoppings, ns <= 64, at most Z_MAX_ROW neighbours per site.
 #include <algorithm>
-#include <cstring>
 #include <type_traits>
 #include <vector>
 
@@ -480,7 +479,7 @@ void launch_tile(g1g2_ctx* c, const StageArgs& s, const TileArgs& t) {
     const HubbardData& H = c->hub;
     if (n_tdiag(SE) > 0) {
         using TI = typename StageTypes<MODE, MIXED>::In;
-        hipLaunchKernelGGL((hub_tdiag_kernel<TI, SE>), dim3(H.ndtile), dim3(256), 0, c->stream, H.desc, H.dtile, s.in2,
+        hipLaunchKernelGGL((hub_tdiag_kernel<TI, SE>), dim3(H.ndwork), dim3(256), 0, c->stream, H.desc, H.dwork, s.in2,
                            const_cast<cd*>(t.diag));
     }
     size_t lds = 0;
@@ -512,24 +511,22 @@ void launch_tile_se(g1g2_ctx* c, const StageArgs& s, const TileArgs& t) {
 
 }  // namespace
 
-// Tiles and work items of every cluster (H.hdesc set).  nbr: the host neighbour
-// tables; per_item: the most G2 elements of an item per cluster.
-g1g2_status hub_tile_setup(g1g2_ctx* c, const std::vector<int>& nbr, const std::vector<int>& per_item) {
+// Tiles and work items of every cluster.  nbr: the host neighbour tables;
+// per_item: the most G2 elements of an item per cluster.
+void hub_tile_lists(g1g2_ctx* c, const std::vector<ClusterDesc>& desc, const std::vector<int>& nbr,
+                    const std::vector<int>& per_item, std::vector<int>& tiles, std::vector<WorkItem>& work) {
     HubbardData& H = c->hub;
     const int sel = c->d.selfenergy;
-    const int se = sel == G1G2_GW ? SE_GW : sel == G1G2_DSL ? SE_DSL : sel == G1G2_TPH ? SE_TPH
-                 : sel == G1G2_TPP ? SE_TPP : SE_SOA;
-    std::vector<int> tiles;
-    std::vector<WorkItem> work, g1, dwork;
+    const int nch = sel == G1G2_GW || sel == G1G2_DSL ? 3 : 1;
+    std::vector<WorkItem> g1;
     std::vector<long long> cost;
     H.tile_shapes.clear();
     H.tile_row = true;
-    long long doff = 0;
-    for (int cl = 0; cl < H.ncl; ++cl) {
-        const ClusterDesc& d = H.hdesc[cl];
+    for (int cl = 0; cl < (int)desc.size(); ++cl) {
+        const ClusterDesc& d = desc[cl];
         const int ns = d.ns, z = d.zmax;
         H.tile_row = H.tile_row && ns >= TILE_ROW_MIN;
-        for (int ch = 0; ch < n_channels(se); ++ch) {
+        for (int ch = 0; ch < nch; ++ch) {
             // block (b,a) of the upper triangle, b < a, is read by a stage when it neighbours
             // an evaluated block: some neighbour of b is >= a, or one of a is <= b
             const int* nb = nbr.data() + d.nbroff + (ch == 2 ? ns * z : 0);
@@ -557,31 +554,21 @@ g1g2_status hub_tile_setup(g1g2_ctx* c, const std::vector<int>& nbr, const std::
                 H.tile_shapes.push_back(shape);
         }
         g1.push_back({cl, -1, -1});
-        for (int t0 = 0; t0 < ns * ns * ns; t0 += 1024) dwork.push_back({cl, t0, std::min(ns * ns * ns, t0 + 1024)});
-        doff += (long long)ns * ns * ns;
     }
     // contiguous ranges per XCD: a block's i- and k-neighbours lie mostly in its range
     // (8x8 SOA 207 us; round-robin 222, ranges of 8x8 patches of blocks 214)
     work = xcd_order(work, cost, g1);
     H.ntwork = (int)work.size();
-    H.ndtile = (int)dwork.size();
-    // one allocation and one copy: tile words, work lists, check result, diagonal tensors
-    const auto pad = [](size_t b) { return (b + 255) / 256 * 256; };
-    const size_t o1 = pad(tiles.size() * sizeof(int)), o2 = o1 + pad(work.size() * sizeof(WorkItem)),
-                 o3 = o2 + pad(dwork.size() * sizeof(WorkItem)), o4 = o3 + 256;
-    std::vector<char> h(o3);
-    std::memcpy(h.data(), tiles.data(), tiles.size() * sizeof(int));
-    std::memcpy(h.data() + o1, work.data(), work.size() * sizeof(WorkItem));
-    std::memcpy(h.data() + o2, dwork.data(), dwork.size() * sizeof(WorkItem));
-    char* buf = nullptr;
-    HIP_OK(c, hipMalloc(&buf, o4 + (size_t)n_tdiag(se) * doff * sizeof(cd)));
-    H.tiles = (int*)buf;
-    H.twork = (WorkItem*)(buf + o1);
-    H.dtile = (WorkItem*)(buf + o2);
-    H.tsym = (unsigned long long*)(buf + o3);
-    H.tdiag = (cd*)(buf + o4);
-    HIP_OK(c, hipMemcpy(buf, h.data(), o3, hipMemcpyHostToDevice));
-    return G1G2_OK;
+}
+
+int hub_tile_diags(const g1g2_ctx* c) {
+    switch (c->d.selfenergy) {
+        case G1G2_TPP: return n_tdiag(SE_TPP);
+        case G1G2_TPH: return n_tdiag(SE_TPH);
+        case G1G2_GW: return n_tdiag(SE_GW);
+        case G1G2_DSL: return n_tdiag(SE_DSL);
+        default: return n_tdiag(SE_SOA);
+    }
 }
 
 // 2^-44: states that the library propagated, and inputs symmetric to rounding, pass
@@ -608,7 +595,7 @@ g1g2_status hub_tile_stage(g1g2_ctx* c, int mode, double t, const Regs& in, cons
     HubbardData& H = c->hub;
     StageArgs s = hub_make_stage(c, t, in, y, acc, out, cb, cc);
     s.work = H.twork;
-    const TileArgs ta{H.tiles, H.tdiag, y2.g1, y3.g1, y2.g2, y3.g2, full ? 1 : 0};
+    const TileArgs ta{H.tiles, H.diag, y2.g1, y3.g1, y2.g2, y3.g2, full ? 1 : 0};
     switch (mode) {
         case RK_FIRST: launch_tile_se<RK_FIRST>(c, s, ta); break;
         case RK_MID: launch_tile_se<RK_MID>(c, s, ta); break;
@@ -631,8 +618,4 @@ g1g2_status hub_tile_step(g1g2_ctx* c, double t, double dt, const Regs& y, const
     if ((s = hub_tile_stage(c, RK_MID, t + 0.5 * dt, y3, y, y, y, acc, y4, dt / 3.0, dt, full)) != G1G2_OK) return s;
     if (!last) return G1G2_OK;
     return hub_tile_stage(c, RK_LAST, t + dt, y4, y, mixed ? y : y2, mixed ? y : y3, acc, out, dt / 6.0, 0.0, full);
-}
-
-void hub_tile_free(g1g2_ctx* c) {
-    if (c->hub.tiles) (void)hipFree(c->hub.tiles);   // the one allocation of hub_tile_setup
 }

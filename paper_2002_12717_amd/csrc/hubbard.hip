@@ -1361,9 +1361,8 @@ double HubbardData::drive_value(double t) const {
 }
 
 void hub_free(g1g2_ctx* c) {
-    hub_tile_free(c);
     HubbardData& H = c->hub;
-    void* ptrs[] = {H.desc, H.work, H.dwork, H.diag, H.nbr, H.hop, H.d0, H.xdrv};
+    void* ptrs[] = {H.desc, H.work, H.dwork, H.nbr, H.hop, H.d0, H.xdrv};   // H.diag lies in H.work's allocation
     for (void* p : ptrs)
         if (p) (void)hipFree(p);
     std::vector<double> dc = H.drive_c, dtc = H.drive_tc, dx = H.drive_x;
@@ -1583,10 +1582,39 @@ g1g2_status hub_setup(g1g2_ctx* c, int ncl, const int* nsv, const double* Uv, co
     H.h_d0 = d0_all;
     g1g2_status s;
     if ((s = upload(c, &H.desc, desc)) != G1G2_OK) return s;
-    if ((s = upload(c, &H.work, work)) != G1G2_OK) return s;
-    if (n_diag(se) > 0) {
+    // steps over one triangle of the pair matrix, at the sizes that take whole slices
+    // by default
+    std::vector<int> tiles;
+    std::vector<WorkItem> twork;
+    const bool tile = slicek && !small1 && realhop && !(fl & G1G2_HUB_SLICE_KERNEL);
+    if (tile) {
+        std::vector<int> per(ncl, SLICE_ELEMS);
+        if (chunk_in)
+            for (int cl = 0; cl < ncl; ++cl)
+                if (chunk_in[cl] > 0) per[cl] = std::min(per[cl], chunk_in[cl]);
+        hub_tile_lists(c, desc, nbr_all, per, tiles, twork);
+    }
+    // one allocation: the work lists, the tiles, the symmetry check's result, the diagonal tensors
+    const auto pad = [](size_t b) { return (b + 255) / 256 * 256; };
+    const size_t ndiag = std::max(n_diag(se), tile ? hub_tile_diags(c) : 0);
+    const size_t o1 = pad(work.size() * sizeof(WorkItem)), o2 = o1 + pad(twork.size() * sizeof(WorkItem)),
+                 o3 = o2 + pad(tiles.size() * sizeof(int)), o4 = o3 + 256;
+    std::vector<char> lists(o3);
+    std::memcpy(lists.data(), work.data(), work.size() * sizeof(WorkItem));
+    std::memcpy(lists.data() + o1, twork.data(), twork.size() * sizeof(WorkItem));
+    std::memcpy(lists.data() + o2, tiles.data(), tiles.size() * sizeof(int));
+    char* buf = nullptr;
+    HIP_OK(c, hipMalloc(&buf, o4 + ndiag * (size_t)doff * sizeof(cd)));
+    H.work = (WorkItem*)buf;
+    HIP_OK(c, hipMemcpyAsync(buf, lists.data(), o3, hipMemcpyHostToDevice, c->stream));
+    if (tile) {
+        H.twork = (WorkItem*)(buf + o1);
+        H.tiles = (int*)(buf + o2);
+        H.tsym = (unsigned long long*)(buf + o3);
+    }
+    if (ndiag > 0) {
         if ((s = upload(c, &H.dwork, dwork)) != G1G2_OK) return s;
-        HIP_OK(c, hipMalloc(&H.diag, std::max<long long>(n_diag(se) * doff, 1) * sizeof(cd)));
+        H.diag = (cd*)(buf + o4);
     }
     if ((s = upload(c, &H.nbr, nbr_all)) != G1G2_OK) return s;
     if ((s = upload(c, &H.hop, hop_all)) != G1G2_OK) return s;
@@ -1597,15 +1625,6 @@ g1g2_status hub_setup(g1g2_ctx* c, int ncl, const int* nsv, const double* Uv, co
         HIP_OK(c, hipMemcpyAsync(H.xdrv, H.drive_x.data(), xoff * sizeof(double), hipMemcpyHostToDevice,
                                  c->stream));
     HIP_OK(c, hipStreamSynchronize(c->stream));
-    // steps over one triangle of the pair matrix, at the sizes that take whole slices
-    // by default
-    if (slicek && !small1 && realhop && !(fl & G1G2_HUB_SLICE_KERNEL)) {
-        std::vector<int> per(ncl, SLICE_ELEMS);
-        if (chunk_in)
-            for (int cl = 0; cl < ncl; ++cl)
-                if (chunk_in[cl] > 0) per[cl] = std::min(per[cl], chunk_in[cl]);
-        return hub_tile_setup(c, nbr_all, per);
-    }
     return G1G2_OK;
 }
 

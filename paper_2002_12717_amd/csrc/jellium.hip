@@ -281,7 +281,7 @@ __global__ __launch_bounds__(64 * JEL_WAVES) void jel_stage_kernel(StageArgsJ s)
         for (int j = 0; j < JEL_PB; ++j) {
             const size_t e = ((size_t)(Pv[j] < 0 ? 0 : Pv[j]) * nb + Pb) * nb + Qc;
             avs[j] = ld_c(in, (long long)e);
-            if (!REDUCE && (MODE == RK_MID || (MODE == RK_LAST && !SUM))) yvs[j] = ld_nt(y + e);
+            if (!REDUCE && (MODE == RK_MID || (MODE == RK_LAST && !SUM))) yvs[j] = y[e];
         }
 #pragma unroll
         for (int j = 0; j < JEL_PB; ++j) {
