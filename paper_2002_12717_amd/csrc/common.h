@@ -73,11 +73,16 @@ enum { RK_RHS = 0, RK_FIRST = 1, RK_MID = 2, RK_LAST = 3 };
 // The differences are exact (or rounded to the size of the step); the stage
 // inputs' own roundings enter with weights 1/3, 2/3, 1/3, less than the three
 // roundings of a running sum, and the first three stages move one state less.
-__device__ __forceinline__ cd rk_close(cd y, cd y2, cd y3, cd y4, cd f, double cb) {
+__device__ __forceinline__ double rk_diffs(double y, double y2, double y3, double y4) {
+    return (y2 - y) + 2.0 * (y3 - y) + (y4 - y);
+}
+__device__ __forceinline__ double rk_close(double y, double diffs, double f, double cb) {
     constexpr double third = 1.0 / 3.0;
-    const double sx = (y2.x - y.x) + 2.0 * (y3.x - y.x) + (y4.x - y.x);
-    const double sy = (y2.y - y.y) + 2.0 * (y3.y - y.y) + (y4.y - y.y);
-    return cmk(y.x + fma(cb, f.x, sx * third), y.y + fma(cb, f.y, sy * third));
+    return y + fma(cb, f, diffs * third);
+}
+__device__ __forceinline__ cd rk_close(cd y, cd y2, cd y3, cd y4, cd f, double cb) {
+    return cmk(rk_close(y.x, rk_diffs(y.x, y2.x, y3.x, y4.x), f.x, cb),
+               rk_close(y.y, rk_diffs(y.y, y2.y, y3.y, y4.y), f.y, cb));
 }
 
 // Streaming (non-temporal) loads and stores: data touched once per kernel,

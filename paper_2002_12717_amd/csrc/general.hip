@@ -501,8 +501,7 @@ struct G1Args {
     int nparts;
     const cd* hhf;
     const cd* gl;      // G^< of the stage
-    const cd* y;
-    cd* acc;
+    const cd *y, *y2, *y3;
     cd* out;
     cd* icoll;         // I, written by right-hand-side evaluations
     int nb;
@@ -514,10 +513,16 @@ __device__ __forceinline__ void g1_update(const G1Args& g, int e, cd comm, cd Ii
                                           double cb, double cc) {
     const cd f = cmul_mi(cadd(comm, cadd(Iij, cconj(Iji))));
     if (MODE == RK_RHS) g.icoll[e] = Iij;
-    rk_update<MODE>(e, f, g.gl[e], g.y, g.acc, g.out, cb, cc);
+    cd o = f;
+    if (MODE != RK_RHS) {
+        const cd y = g.y[e];
+        o = MODE == RK_LAST ? rk_close(y, g.y2[e], g.y3[e], g.gl[e], f, cb)
+                            : cmk(fma(cc, f.x, y.x), fma(cc, f.y, y.y));
+    }
+    g.out[e] = o;
     const int i = e / nbp, j = e % nbp;
     if (MODE == RK_FIRST && e == 0) guard_begin_step(g.guard);   // one thread per launch
-    if (MODE == RK_LAST && i < g.nb && guard_bad(g.out[e], i == j)) guard_fire(g.guard, 0, g.guard.div[0]);
+    if (MODE == RK_LAST && i < g.nb && guard_bad(o, i == j)) guard_fire(g.guard, 0, g.guard.div[0]);
 }
 
 // The elements (i,j) and (j,i), i <= j: both need I_ij and I_ji, so each
@@ -565,15 +570,20 @@ __device__ __forceinline__ void g1_pair(const G1Args& g, int i, int j, int lane,
 }
 
 // --------------------------------------------------------------------------- K4
-// dG2 = -i (D - D^dagger), fused RK4 update; for GW and DSL the polarization's
+// dG2 = -i (D - D^dagger), fused RK4 update; for GW and DSL (DD) the polarization's
 // elements X_ijij = i (dd_ij + dd_ji), their own partners, enter here;
 // the G1 equation (K5) on the same launch, in work-groups of its own, so that
 // the latency of its partial-sum reads overlaps the G2 streaming.
-template <int MODE, typename S>
-__global__ __launch_bounds__(256) void gen_combine_kernel(const S* __restrict__ D, int n,
-                                                         const cd* __restrict__ in,
-                                                         const cd* __restrict__ y,
-                                                         cd* __restrict__ acc, cd* __restrict__ out,
+// HBM bound: D, y and the next stage's input once per element, and no running
+// sum (the last stage reads the stage inputs instead, rk_close): 48 B per
+// element in binary64 stages 1 to 3 and 96 B in the last, against 64, 80, 80
+// and 64 B with one.  The state is read ahead of the transpose, its latency
+// beside that of D.  Stages 1 to 4, with the sum -> without: nb = 64 GW 210, 276,
+// 276, 167 -> 157, 157, 157, 349 us; nb = 32 second Born, binary32 D, 11.9, 13.6,
+// 13.6, 10.1 -> 9.3, 9.5, 9.5, 16.3 us.
+template <int MODE, typename S, bool DD>
+__global__ __launch_bounds__(256) void gen_combine_kernel(const S* __restrict__ D, int n, const cd* in,
+                                                         const cd* y, const cd* y2, const cd* y3, cd* out,
                                                          const double* __restrict__ dd, int nbp,
                                                          double cb, double cc, G1Args g1, int ng1) {
     __shared__ double t1r[32][33], t1i[32][33], t2r[32][33], t2i[32][33];
@@ -597,13 +607,15 @@ __global__ __launch_bounds__(256) void gen_combine_kernel(const S* __restrict__ 
     }
     // work-group -> tile pair (by, bx), bx <= by, in triangular order; both
     // tiles of the pair are updated from one read of D_(by,bx) and D_(bx,by)
-    const int tb = blockIdx.x - ng1;
-    int by = (int)((sqrtf(8.0f * (float)tb + 1.0f) - 1.0f) * 0.5f);
-    while ((by + 1) * (by + 2) / 2 <= tb) ++by;
-    while (by * (by + 1) / 2 > tb) --by;
-    const int bx = tb - by * (by + 1) / 2;
+    int by, bx;
+    tri(blockIdx.x - ng1, by, bx);
     const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
-    for (int r = ty; r < 32; r += 8) {
+    // element q of a thread: row r = ty + 8 (q / 2) of tile (by, bx) and, odd q, of (bx, by)
+    auto row = [&](int q) { return (q & 1 ? bx : by) * 32 + ty + 8 * (q >> 1); };
+    auto col = [&](int q) { return (q & 1 ? by : bx) * 32 + tx; };
+    double yr[8], yi[8], sr[8], si[8];
+#pragma unroll
+    for (int r = ty, q = 0; q < 4; r += 8, ++q) {
         double a, b;
         ldc(D + (size_t)(by * 32 + r) * n + bx * 32 + tx, a, b);
         t1r[r][tx] = a;
@@ -612,22 +624,38 @@ __global__ __launch_bounds__(256) void gen_combine_kernel(const S* __restrict__ 
         t2r[r][tx] = a;
         t2i[r][tx] = b;
     }
+    if (MODE != RK_RHS) {
+#pragma unroll
+        for (int q = 0; q < 8; ++q) {
+            const size_t e = (size_t)row(q) * n + col(q);
+            const cd v = y[e];
+            yr[q] = v.x;
+            yi[q] = v.y;
+            if (MODE == RK_LAST) {
+                const cd a = y2[e], b = y3[e], c = in[e];
+                sr[q] = rk_diffs(v.x, a.x, b.x, c.x);
+                si[q] = rk_diffs(v.y, a.y, b.y, c.y);
+            }
+        }
+    }
     __syncthreads();
-    auto update = [&](int row, int col, double zr, double zi) {
-        const size_t e = (size_t)row * n + col;
-        if (dd && row == col) {
-            const int i = row / nbp, j = row % nbp, nb = g1.nb;
+#pragma unroll
+    for (int q = 0; q < 8; ++q) {
+        if ((q & 1) && bx == by) continue;
+        // D_rc - conj(D_cr) on tile (by, bx) and, off the diagonal, on (bx, by)
+        const int r = ty + 8 * (q >> 1);
+        const double zr = q & 1 ? t2r[r][tx] - t1r[tx][r] : t1r[r][tx] - t2r[tx][r];
+        double zi = q & 1 ? t2i[r][tx] + t1i[tx][r] : t1i[r][tx] + t2i[tx][r];
+        if (DD && row(q) == col(q)) {
+            const int i = row(q) / nbp, j = row(q) % nbp, nb = g1.nb;
             if (i < nb && j < nb) zi += dd[i * nb + j] + dd[j * nb + i];
         }
-        cd f = make_double2(zi, -zr);  // -i z
-        cd yin = make_double2(0.0, 0.0);
-        if (MODE == RK_FIRST) yin = in[e];
-        rk_update<MODE>((int)e, f, yin, y, acc, out, cb, cc);
-    };
-    for (int r = ty; r < 32; r += 8) {
-        // D_rc - conj(D_cr) on tile (by, bx) and, off the diagonal, on (bx, by)
-        update(by * 32 + r, bx * 32 + tx, t1r[r][tx] - t2r[tx][r], t1i[r][tx] + t2i[tx][r]);
-        if (bx != by) update(bx * 32 + r, by * 32 + tx, t2r[r][tx] - t1r[tx][r], t2i[r][tx] + t1i[tx][r]);
+        const cd f = make_double2(zi, -zr);  // -i z
+        cd o;
+        if (MODE == RK_RHS) o = f;
+        else if (MODE == RK_LAST) o = cmk(rk_close(yr[q], sr[q], f.x, cb), rk_close(yi[q], si[q], f.y, cb));
+        else o = cmk(fma(cc, f.x, yr[q]), fma(cc, f.y, yi[q]));
+        out[(size_t)row(q) * n + col(q)] = o;
     }
 }
 
@@ -757,16 +785,21 @@ g1g2_status run_blocks(g1g2_ctx* c, const Regs& in, double ws) {
 }
 
 template <typename S, int MODE>
-g1g2_status run_combine(g1g2_ctx* c, const Regs& in, const Regs& y, const Regs& acc,
+g1g2_status run_combine(g1g2_ctx* c, const Regs& in, const Regs& y, const Regs& y2, const Regs& y3,
                         const Regs& out, double cb, double cc) {
     GeneralData& g = c->gen;
     const int n = g.nbp * g.nbp;
     const int nt = n / 32, ntiles = nt * (nt + 1) / 2;
-    const G1Args g1{g.ipart, g.nipart, g.hhf, in.g1, y.g1, acc.g1, out.g1,
+    const G1Args g1{g.ipart, g.nipart, g.hhf, in.g1, y.g1, y2.g1, y3.g1, out.g1,
                     g.icoll, g.nb, guard_of(c)};
     const int ng1 = (g.nbp * (g.nbp + 1) / 2 + 3) / 4;   // work-groups of the G1 pairs
-    hipLaunchKernelGGL((gen_combine_kernel<MODE, S>), dim3(ng1 + ntiles), dim3(256), 0, c->stream, (const S*)g.dmat,
-                       n, in.g2, y.g2, acc.g2, out.g2, g.pdd, g.nbp, cb, cc, g1, ng1);
+    const auto launch = [&](auto dd) {
+        hipLaunchKernelGGL((gen_combine_kernel<MODE, S, decltype(dd)::value>), dim3(ng1 + ntiles), dim3(256), 0,
+                           c->stream, (const S*)g.dmat, n, in.g2, y.g2, y2.g2, y3.g2, out.g2, g.pdd, g.nbp, cb, cc,
+                           g1, ng1);
+    };
+    if (g.pdd) launch(std::is_same<S, cd>());   // D is binary32 without a polarization only
+    else launch(std::false_type());
     HIP_OK(c, hipGetLastError());
     prof_mark(c, "gen_combine");
     return G1G2_OK;
@@ -784,13 +817,13 @@ g1g2_status dispatch_blocks(g1g2_ctx* c, const Regs& in, double ws) {
 }
 
 template <typename S>
-g1g2_status dispatch_combine(g1g2_ctx* c, int mode, const Regs& in, const Regs& y, const Regs& acc,
-                             const Regs& out, double cb, double cc) {
+g1g2_status dispatch_combine(g1g2_ctx* c, int mode, const Regs& in, const Regs& y, const Regs& y2,
+                             const Regs& y3, const Regs& out, double cb, double cc) {
     switch (mode) {
-        case RK_RHS: return run_combine<S, RK_RHS>(c, in, y, acc, out, cb, cc);
-        case RK_FIRST: return run_combine<S, RK_FIRST>(c, in, y, acc, out, cb, cc);
-        case RK_MID: return run_combine<S, RK_MID>(c, in, y, acc, out, cb, cc);
-        default: return run_combine<S, RK_LAST>(c, in, y, acc, out, cb, cc);
+        case RK_RHS: return run_combine<S, RK_RHS>(c, in, y, y2, y3, out, cb, cc);
+        case RK_FIRST: return run_combine<S, RK_FIRST>(c, in, y, y2, y3, out, cb, cc);
+        case RK_MID: return run_combine<S, RK_MID>(c, in, y, y2, y3, out, cb, cc);
+        default: return run_combine<S, RK_LAST>(c, in, y, y2, y3, out, cb, cc);
     }
 }
 
@@ -920,26 +953,26 @@ g1g2_status gen_setup(g1g2_ctx* c, const cd* h0, const cd* w) {
 }
 
 g1g2_status gen_stage(g1g2_ctx* c, int mode, double t, const Regs& in, const Regs& y,
-                      const Regs& acc, const Regs& out, double cb, double cc) {
+                      const Regs& y2, const Regs& y3, const Regs& out, double cb, double cc) {
     const double ws = c->switch_value(t);
     g1g2_status s;
     if (c->d.precision == G1G2_MIXED) {
         if (c->d.selfenergy == G1G2_SOA) {
             if ((s = dispatch_blocks<float, float2, float2>(c, in, ws)) != G1G2_OK) return s;
-            return dispatch_combine<float2>(c, mode, in, y, acc, out, cb, cc);
+            return dispatch_combine<float2>(c, mode, in, y, y2, y3, out, cb, cc);
         }
         if ((s = dispatch_blocks<float, float2, cd>(c, in, ws)) != G1G2_OK) return s;
-        return dispatch_combine<cd>(c, mode, in, y, acc, out, cb, cc);
+        return dispatch_combine<cd>(c, mode, in, y, y2, y3, out, cb, cc);
     }
     if ((s = dispatch_blocks<double, cd, cd>(c, in, ws)) != G1G2_OK) return s;
-    return dispatch_combine<cd>(c, mode, in, y, acc, out, cb, cc);
+    return dispatch_combine<cd>(c, mode, in, y, y2, y3, out, cb, cc);
 }
 
 g1g2_status gen_observables(g1g2_ctx* c, const Regs& s, double t, g1g2_obs* o) {
     (void)t;
     GeneralData& g = c->gen;
     // one right-hand-side evaluation refreshes h^HF and the collision integral
-    g1g2_status st = gen_stage(c, RK_RHS, c->t, s, s, s, c->io, 0.0, 0.0);
+    g1g2_status st = gen_stage(c, RK_RHS, c->t, s, s, s, s, c->io, 0.0, 0.0);
     if (st != G1G2_OK) return st;
     hipLaunchKernelGGL(gen_obs_kernel, dim3(1), dim3(256), 0, c->stream, s.g1, g.h0, g.hhf, g.icoll,
                        g.nbp, c->dscratch);
