@@ -1,7 +1,9 @@
 """Autotuner of the ragged Hubbard batch.  It first chooses the stage kernel
-(the slice kernel, the row kernel, or the per-element kernel, which negative
-chunks select), then, per cluster size class, the number of G2 elements one
-work-group of the flat work list of g1g2_batch_init handles: for the slice
+(the triangle kernel, which the library takes by itself for a batch of 2^20
+elements or more with real hoppings, the slice kernel, the row kernel, or the
+per-element kernel, which negative chunks select), then, per cluster size class, the number of G2 elements one
+work-group of the flat work list of g1g2_batch_init handles: for the triangle
+kernel the most elements of a packed item (at most 1024), for the slice
 kernel the most elements a work item stages in LDS (whole (i,j) slices; the
 launch sizes its LDS for the longest item, so shorter items leave room for
 more work-groups per compute unit), for the row kernel its granularity
@@ -17,6 +19,8 @@ import os
 import sys
 import time
 
+import numpy as np
+
 PKG = os.path.dirname(os.path.abspath(__file__))
 TABLE = os.path.join(PKG, "tuning", "hubbard_batch.json")
 CLASSES = [(1, 16), (17, 25), (26, 49)]          # ns ranges (inclusive)
@@ -26,8 +30,11 @@ CANDIDATES_ROW = [256, 512, 1024, 2048, 4096]
 CANDIDATES_FLAT = [-256, -512, -1024, -2048]
 # slice kernel: elements per work item (4096 is the library's default and limit)
 CANDIDATES_SLICE = [1024, 2048, 3072, 4096]
+# triangle kernel: elements per packed item; the library takes at most 1024, and
+# the batches that it does not serve run the slice kernel with the same chunks
+CANDIDATES_TRIANGLE = [512, 768, 4096]
 DEFAULT = 1024
-START = {"slice": 4096, "row": DEFAULT, "element": -256}
+START = {"triangle": 4096, "slice": 4096, "row": DEFAULT, "element": -256}
 
 
 def class_of(ns: int) -> int:
@@ -44,7 +51,7 @@ def load_table(path: str = TABLE) -> dict:
     return {}
 
 
-KERNELS = ("slice", "row", "element")
+KERNELS = ("triangle", "slice", "row", "element")
 
 
 def chunks_for(ns_list, table=None):
@@ -65,9 +72,13 @@ def make_batch(B, clusters, selfenergy, stream=0, precision=None, table=None):
     chunks of the tuning table (the stored one by default)."""
     table = load_table() if table is None else table
     ns = [c.ns for c in clusters]
+    flags = flags_for(table)
+    if table.get("kernel") == "triangle" and not (
+            sum(n ** 4 for n in ns) >= 1 << 20 and all(np.isrealobj(c.h0) or not np.any(np.imag(c.h0)) for c in clusters)):
+        flags = B.HUB_SLICE_KERNEL                # the next best kernel of the tuned batch
     return B.Batch(selfenergy, ns, [c.U for c in clusters], [c.h0 for c in clusters],
                    [c.g1 for c in clusters], chunk=chunks_for(ns, table), stream=stream,
-                   precision=B.FP64 if precision is None else precision, flags=flags_for(table))
+                   precision=B.FP64 if precision is None else precision, flags=flags)
 
 
 def _time(B, torch, clusters, selfenergy, chunks, steps, stream, flags=0):
@@ -97,7 +108,7 @@ def tune(n_clusters: int = 512, steps: int = 8, selfenergy_name: str = "tpp", ou
     ns = [c.ns for c in clusters]
     log = []
     # the kernel variant is global: pick it first with uniform chunks
-    kflags = {"slice": B.HUB_SLICE_KERNEL, "row": B.HUB_ROW_KERNEL, "element": 0}
+    kflags = {"triangle": 0, "slice": B.HUB_SLICE_KERNEL, "row": B.HUB_ROW_KERNEL, "element": 0}
     best, base, kernel = None, float("inf"), None
     for kern in KERNELS:
         trial = [START[kern]] * len(CLASSES)
@@ -106,7 +117,8 @@ def tune(n_clusters: int = 512, steps: int = 8, selfenergy_name: str = "tpp", ou
         print(f"kernel {kern} {trial} {ms:.3f} ms/step", flush=True)
         if ms < base:
             base, best, kernel = ms, trial, kern
-    cands = {"slice": CANDIDATES_SLICE, "row": CANDIDATES_ROW, "element": CANDIDATES_FLAT}[kernel]
+    cands = {"triangle": CANDIDATES_TRIANGLE, "slice": CANDIDATES_SLICE, "row": CANDIDATES_ROW,
+             "element": CANDIDATES_FLAT}[kernel]
     for q in range(len(CLASSES)):
         for cand in cands:
             if cand == best[q]:
