@@ -42,8 +42,6 @@ PEAK_HBM = 8000.0          # GB/s
 TRAFFIC = {
     "gen_main/f64": {"bytes": 75.9e6, "src": "general.hip", "sha1": "10279bdbe35c"},
     "gen_main/f32": {"bytes": 50.7e6, "src": "general.hip", "sha1": "10279bdbe35c"},
-    "gen_gemm/f64": {"bytes": 5.177e9, "src": "general.hip", "sha1": "10279bdbe35c"},
-    "gen_gemm/f32": {"bytes": 3.017e9, "src": "general.hip", "sha1": "10279bdbe35c"},
     "hub_stage/2d": {"bytes": 2.385e9, "src": "hubbard.hip", "sha1": "94601047d47b"},
     "hub_stage/2d/mixed": {"bytes": 1.634e9, "src": "hubbard.hip", "sha1": "94601047d47b"},
     "hub_stage/2d/tpp": {"bytes": 2.443e9, "src": "hubbard.hip", "sha1": "94601047d47b"},
@@ -75,6 +73,12 @@ def traffic(key):
 
 SE_CODES = {"soa": lambda B: B.SOA, "gw": lambda B: B.GW, "tpp": lambda B: B.TPP, "tph": lambda B: B.TPH,
             "dsl": lambda B: B.DSL}
+# Mean bytes per G2 element of a stage over one triangle of the pair matrix (the
+# path of large Hubbard systems): half of the elements are read and written, the
+# last stage writes all.  Binary64: 16, 24, 24, 48 B; mixed (running sum, binary32
+# stage copies): 20, 32, 32, 28 B.  The general stage kernels move 64 and 52 B.
+TRIANGLE_BYTES = 28.0
+
 # Hubbard G2 channels per selfenergy: GW and DSL propagate three
 HUB_CHANNELS = {"soa": 1, "tpp": 1, "tph": 1, "gw": 3, "dsl": 3}
 
@@ -88,26 +92,33 @@ def soa_flops(nb: int) -> dict:
 
 
 def gw_flops(nb: int) -> dict:
-    """GW adds h^eps (2 nb^5) and the polarization GEMM (nb^6) per RHS."""
+    """GW adds h^eps (2 nb^5) and the polarization (nb^6) per RHS.  gen_heps and
+    gen_gemm count their unreduced complex forms; the library evaluates h^eps for
+    half of its blocks and the polarization as a real product of 2 nb^6 flops
+    (gen_pair_gemm), and the total counts those."""
     d = soa_flops(nb)
-    d["gen_heps"] = 16 * float(nb) ** 5
-    d["gen_gemm"] = 8 * float(nb) ** 6
-    d["total"] = d["soa_total"] + d["gen_heps"] + d["gen_gemm"]
+    n5, n6 = float(nb) ** 5, float(nb) ** 6
+    d["gen_heps"] = 16 * n5
+    d["gen_gemm"] = 8 * n6
+    d["gen_pair_gemm"] = 2 * n6
+    d["total"] = d["soa_total"] + 8 * n5 + d["gen_pair_gemm"]
     return d
 
 
 def ladder_flops(nb: int, se: str) -> dict:
-    """Each T-matrix ladder adds its quasi-Hamiltonian (two one-sided products
-    per side of the sandwich: 4 nb^5) and one GEMM (nb^6); DSL adds GW's
-    polarization as well.  gen_gemm is the flops of one GEMM launch."""
+    """Each T-matrix ladder adds its quasi-Hamiltonian (two one-sided products for
+    half of its blocks: 1 nb^5) and one nb^6 product, real for TPH (2 nb^6 flops) and
+    over the two exchange sectors for TPP (8 real flops per complex multiply-add,
+    of which the kernel executes 6); DSL adds GW's polarization as well.
+    gen_gemm is the mean of TPP's two sector launches."""
     d = soa_flops(nb)
     n5, n6 = float(nb) ** 5, float(nb) ** 6
-    nlad = {"tpp": 1, "tph": 1, "dsl": 2}[se]
-    ngemm = nlad + (1 if se == "dsl" else 0)
-    d["gen_hlad"] = 32 * n5
-    d["gen_gemm"] = 8 * n6
-    d["total"] = d["soa_total"] + nlad * d["gen_hlad"] + ngemm * d["gen_gemm"] + \
-        (16 * n5 if se == "dsl" else 0.0)
+    ns, na = nb * (nb + 1) / 2.0, nb * (nb - 1) / 2.0
+    nlad = {"tpp": 1, "tph": 1, "dsl": 3}[se]
+    d["gen_gemm"] = 4.0 * (ns ** 3 + na ** 3)
+    d["gen_pair_gemm"] = 2 * n6
+    d["total"] = d["soa_total"] + nlad * 8 * n5 + (0 if se == "tph" else 2 * d["gen_gemm"]) + \
+        {"tpp": 0, "tph": 1, "dsl": 2}[se] * d["gen_pair_gemm"]
     return d
 
 
@@ -328,7 +339,7 @@ def run_general(args, torch, B, se="soa", accuracy=True, steps=None, warmup=None
     f64, mx = res["fp64"], res["mixed"]
     ms_step = f64["ms"] / steps
     mx_step = mx["ms"] / steps
-    dom = "gen_gemm" if gw else "gen_main"
+    dom = "gen_main" if not gw else "gen_gemm" if se == "tpp" else "gen_pair_gemm"
     tot_ms, cnt = f64["prof"][dom]
     achieved = fl[dom] * cnt / (tot_ms * 1e-3) / 1e12
     rhs_flops = fl["total"] if gw else fl["soa_total"]
@@ -346,7 +357,7 @@ def run_general(args, torch, B, se="soa", accuracy=True, steps=None, warmup=None
         "g2_rhs_tflops": round(4 * rhs_flops / (ms_step * 1e-3) / 1e12, 3),
         "roofline": {"kernel": dom, "bound": "mfma", "achieved": round(achieved, 3),
                      "peak": PEAK_FP64_MFMA, "unit": "TFLOP/s", "frac": round(achieved / PEAK_FP64_MFMA, 4),
-                     "traffic": traffic("gen_gemm/f64") if gw else traffic("gen_main/f64"),
+                     "traffic": None if gw else traffic("gen_main/f64"),
                      "kernel_ms_avg": round(tot_ms / cnt, 6),
                      "flop_per_launch": fl[dom], "launches": cnt},
         "kernels": kernel_table(f64["prof"]),
@@ -355,17 +366,16 @@ def run_general(args, torch, B, se="soa", accuracy=True, steps=None, warmup=None
                   "g2_rhs_tflops": round(4 * rhs_flops / (mx_step * 1e-3) / 1e12, 3),
                   "roofline": {"kernel": dom, "achieved": round(mx_ach, 3), "peak": PEAK_FP32_MFMA,
                                "unit": "TFLOP/s", "frac": round(mx_ach / PEAK_FP32_MFMA, 4),
-                               "traffic": traffic("gen_gemm/f32") if gw else traffic("gen_main/f32")},
+                               "traffic": None if gw else traffic("gen_main/f32")},
                   "kernels": kernel_table(mx["prof"])},
     })
     if gw:
-        # gen_gemm forms each complex multiply-add with three real products
-        # (Re = ArBr - AiBi, Im = (Ar+Ai)(Br+Bi) - ArBr - AiBi): 6 real flops
-        # executed for the 8 of the algorithmic count, so the algorithmic rate
-        # can exceed the matrix peak; the matrix cores' own use is 3/4 of it
-        out["roofline"]["executed_flop_per_launch"] = 0.75 * fl[dom]
-        out["roofline"]["matrix_core_frac"] = round(0.75 * achieved / PEAK_FP64_MFMA, 4)
-        out["mixed"]["roofline"]["matrix_core_frac"] = round(0.75 * mx_ach / PEAK_FP32_MFMA, 4)
+        # gen_gemm (TPP) forms each complex multiply-add with three real products,
+        # 6 real flops for the 8 counted; gen_pair_gemm executes what is counted
+        ex = 0.75 if dom == "gen_gemm" else 1.0
+        out["roofline"]["executed_flop_per_launch"] = ex * fl[dom]
+        out["roofline"]["matrix_core_frac"] = round(ex * achieved / PEAK_FP64_MFMA, 4)
+        out["mixed"]["roofline"]["matrix_core_frac"] = round(ex * mx_ach / PEAK_FP32_MFMA, 4)
     if accuracy and se in ("soa", "gw"):
         every = 25 if gw else 50
         gname = "general_gw_nb64.npz" if gw else "general_soa_nb32.npz"
@@ -433,9 +443,10 @@ def run_hubbard(args, torch, B, kind):
     ms_step = ms / args.steps
     n4 = float(ns) ** 4
     tot_ms, cnt = prof["hub_stage"]
-    # algorithmic bytes: 256 B per complex128 G2 element per RK4 step (4 launches);
-    # Hubbard GW and DSL propagate three G2 channels
-    bytes_per_launch = 64.0 * n4 * HUB_CHANNELS[se]
+    # algorithmic bytes per G2 element and launch (TRIANGLE_BYTES at 8x8); Hubbard GW and DSL
+    # propagate three G2 channels
+    b64, b32 = (TRIANGLE_BYTES, TRIANGLE_BYTES) if kind == "hubbard_2d" else (64.0, 52.0)
+    bytes_per_launch = b64 * n4 * HUB_CHANNELS[se]
     achieved = bytes_per_launch * cnt / (tot_ms * 1e-3) / 1e9
     name = f"1D chain, {ns} sites" if kind == "hubbard_chain" else "2D 8x8 open cluster, driven"
     config = {"workload": f"Hubbard {se.upper()} G1-G2, {name}, U={system.U}, dt={system.dt}, RK4",
@@ -459,12 +470,11 @@ def run_hubbard(args, torch, B, kind):
     })
     if persistent:
         out["launched_stage_roofline"] = stage_roof
-    # mixed precision: binary32 G2 stage copies, 52 B per element and launch
-    # (binary64 y and acc, binary32 stage input and output)
+    # mixed precision: binary32 G2 stage copies
     mx_ms, mx_prof, mx_obs, g1_mx, _ = run(B.MIXED)
     mx_step = mx_ms / args.steps
     mx_tot, mx_cnt = mx_prof["hub_stage"]
-    mx_ach = 52.0 * n4 * HUB_CHANNELS[se] * mx_cnt / (mx_tot * 1e-3) / 1e9
+    mx_ach = b32 * n4 * HUB_CHANNELS[se] * mx_cnt / (mx_tot * 1e-3) / 1e9
     out["mixed"] = {"dtype": "f64 state, f32 G2 stage copies", "value": round(1e3 / mx_step, 3),
                     "ms_per_step": round(mx_step, 6), "speedup_vs_fp64": round(ms_step / mx_step, 3),
                     "err_G1_vs_fp64": float(np.abs(g1_mx - g1_64).max() / np.abs(g1_64).max()),
@@ -514,10 +524,10 @@ def run_jellium(args, torch, B):
     mx_step = mx["ms"] / args.steps
     n2 = 3.0 * nb ** 3
     tot, cnt = f64["prof"]["jel_stage"]
-    # 48, 80, 80, 48 B per element over the four stages; the T matrices read
+    # 32, 48, 48, 80 B per element over the four stages; the T matrices read
     # the ladder sums at the element and at its partner (32 B more)
     extra = 32.0 if ladder else 0.0
-    bytes_launch = (64.0 + extra) * n2
+    bytes_launch = (52.0 + extra) * n2
     ach = bytes_launch * cnt / (tot * 1e-3) / 1e9
     mtot, mcnt = mx["prof"]["jel_stage"]
     mbytes = (52.0 + extra) * n2      # binary32 stage copies: 40, 64, 64, 40 B
@@ -725,13 +735,12 @@ def run_batch(args, torch, B):
     ms_step = f64["ms"] / args.steps
     mx_step = mx["ms"] / args.steps
     tot_ms, cnt = f64["prof"]["hub_stage"]
-    # algorithmic bytes per G2 element and RK4 step: 256 (binary64 stage copies)
-    # or 208 (binary32 stage copies); the four stage launches share them
+    # algorithmic bytes per G2 element and launch: stages over one triangle
     nch = HUB_CHANNELS[se]
-    bytes_per_launch = 64.0 * n4 * nch
+    bytes_per_launch = TRIANGLE_BYTES * n4 * nch
     achieved = bytes_per_launch * cnt / (tot_ms * 1e-3) / 1e9
     mx_tot, mx_cnt = mx["prof"]["hub_stage"]
-    mx_bytes = 52.0 * n4 * nch
+    mx_bytes = TRIANGLE_BYTES * n4 * nch
     mx_ach = mx_bytes * mx_cnt / (mx_tot * 1e-3) / 1e9
     err_g1 = max(float(np.abs(m - f).max() / np.abs(f).max()) for m, f in zip(mx["g1"], f64["g1"]))
     err_e = max(abs(m["E_tot"] - f["E_tot"]) / max(abs(f["E_tot"]), 1.0)
@@ -847,7 +856,7 @@ def run_adjoint(args, torch, B):
     total_ms = fwd_ms + 2 * rev_ms
     ms_step = total_ms / args.steps
     tot_ms, cnt = prof["hub_stage"]
-    bytes_per_launch = 64.0 * float(ns) ** 4
+    bytes_per_launch = TRIANGLE_BYTES * float(ns) ** 4
     achieved = bytes_per_launch * cnt / (tot_ms * 1e-3) / 1e9
     # adj_slice_red, the reverse sweep's dominant kernel: per G2 element it reads
     # the cotangent, the stage state, lambda and the running sum and writes the

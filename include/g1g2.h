@@ -69,8 +69,10 @@ typedef enum {
  * to the up-down-up-down channel; they vanish on the equal-spin channels,
  * whose interaction pairs opposite spins, and the exchange form of the
  * source equals Psi there for the same reason.  The general-basis
- * GW, T-matrix and DSL closures cost one (nb^2 x nb^2 x nb^2) complex GEMM per
- * polarization or ladder and right-hand side.                                  */
+ * GW, T-matrix and DSL closures cost one real (nb^2 x nb^2 x nb^2) product per
+ * polarization or particle-hole ladder, and one complex product per exchange
+ * sector of half that edge for the particle-particle ladder, per right-hand
+ * side.                                                                        */
 typedef enum { G1G2_SOA = 0, G1G2_GW = 1, G1G2_TPP = 2, G1G2_TPH = 3, G1G2_DSL = 4 } g1g2_selfenergy;
 
 /* GENERAL: arbitrary orthonormal basis with a four-index w (Sec. III.C).
@@ -97,7 +99,9 @@ enum {
      * work-group stages whole (i,j) slices of G2 in LDS) runs when the clusters
      * hold at least 2^20 G2 elements in all (counting GW's three channels),
      * else the row kernel (one wave per G2 row).  Both need ns <= 64 and at
-     * most 4 neighbours per site, else the per-element kernel runs. */
+     * most 4 neighbours per site, else the per-element kernel runs.  Steps of
+     * systems of that size with real hoppings and a Hermitian state compute one
+     * triangle of the pair matrix instead; either flag turns that off. */
     G1G2_HUB_ROW_KERNEL = 4,    /* Hubbard: row kernel whatever the size          */
     G1G2_HUB_SLICE_KERNEL = 8,  /* Hubbard: slice kernel whatever the size        */
     /* General-basis DSL: build the polarization and particle-hole
