@@ -112,7 +112,7 @@ g1g2_status stage(g1g2_ctx* c, int mode, double t, const Regs& in, const Regs& y
                   const Regs& out, double cb, double cc) {
     if (c->d.basis == G1G2_HUBBARD) return hub_stage(c, mode, t, in, y, acc, out, cb, cc);
     if (c->d.basis == G1G2_JELLIUM) return jel_stage(c, mode, in, y, y, y, acc, out, cb, cc);   // RK_RHS
-    return gen_stage(c, mode, t, in, y, y, y, out, cb, cc);                                     // RK_RHS
+    return gen_stage(c, mode, t, in, y, y, y, acc, out, cb, cc);                                  // RK_RHS
 }
 
 // One classical RK4 step on the registers (y, acc, s0, s1).
@@ -123,13 +123,14 @@ g1g2_status rk4_step(g1g2_ctx* c, double t, double dt) {
                    : hub_tile_step(c, t, dt, c->y, c->y, c->s0, c->s1, c->acc, c->acc, false, true);
     g1g2_status s;
     if (c->d.basis != G1G2_HUBBARD) {
-        // binary64 stage copies (mixed precision keeps them in the general basis): the third
-        // stage register is Y4 (acc is free)
+        // without a running sum the third stage register is Y4; mixed precision keeps the sum
+        // in jellium and in general-basis second Born
         const bool gen = c->d.basis == G1G2_GENERAL;
+        const bool sum = c->d.precision == G1G2_MIXED && (!gen || c->d.selfenergy == G1G2_SOA);
         const Regs &y = c->y, &y2 = c->s0, &y3 = c->s1, &acc = c->acc;
-        const Regs& y4 = gen || c->d.precision != G1G2_MIXED ? c->acc : c->s0;
+        const Regs& y4 = sum ? c->s0 : c->acc;
         const auto run = [&](int mode, double ts, const Regs& in, const Regs& out, double cb, double cc) {
-            return gen ? gen_stage(c, mode, ts, in, y, y2, y3, out, cb, cc)
+            return gen ? gen_stage(c, mode, ts, in, y, y2, y3, acc, out, cb, cc)
                        : jel_stage(c, mode, in, y, y2, y3, acc, out, cb, cc);
         };
         if ((s = run(RK_FIRST, t, y, y2, dt / 6.0, dt / 2.0)) != G1G2_OK) return s;
@@ -425,7 +426,7 @@ g1g2_status g1g2_rhs(g1g2_ctx* c, double t, const void* G1, const void* G2, void
     // general: pad into s0 (dead between steps), evaluate into s1, unpad
     if ((s = load_component(c, G1, true, c->s0.g1, 2)) != G1G2_OK) return s;
     if ((s = load_component(c, G2, true, c->s0.g2, 4)) != G1G2_OK) return s;
-    if ((s = gen_stage(c, RK_RHS, t, c->s0, c->s0, c->s0, c->s0, c->s1, 0.0, 0.0)) != G1G2_OK) return s;
+    if ((s = gen_stage(c, RK_RHS, t, c->s0, c->s0, c->s0, c->s0, c->s0, c->s1, 0.0, 0.0)) != G1G2_OK) return s;
     if ((s = store_component(c, c->s1.g1, dG1, true, 2)) != G1G2_OK) return s;
     if ((s = store_component(c, c->s1.g2, dG2, true, 4)) != G1G2_OK) return s;
     HIP_OK(c, hipStreamSynchronize(c->stream));

@@ -245,7 +245,7 @@ g1g2_status hub_batch_observables(g1g2_ctx* c, const Regs& s, double t, g1g2_obs
 g1g2_status gen_setup(g1g2_ctx* c, const cd* h0_host, const cd* w_host);
 g1g2_status gen_set_h0(g1g2_ctx* c, const cd* h0_host);
 g1g2_status gen_stage(g1g2_ctx* c, int mode, double t, const Regs& in, const Regs& y,
-                      const Regs& y2, const Regs& y3, const Regs& out, double cb, double cc);
+                      const Regs& y2, const Regs& y3, const Regs& acc, const Regs& out, double cb, double cc);
 g1g2_status gen_observables(g1g2_ctx* c, const Regs& s, double t, g1g2_obs* o);
 // layout conversions between the unpadded ABI layout and the padded internal one
 g1g2_status gen_pad(g1g2_ctx* c, const cd* src_dev, cd* dst_dev, int rank);

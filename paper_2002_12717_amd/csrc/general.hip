@@ -502,24 +502,28 @@ struct G1Args {
     const cd* hhf;
     const cd* gl;      // G^< of the stage
     const cd *y, *y2, *y3;
+    cd* acc;           // mixed second Born: the running sum
     cd* out;
     cd* icoll;         // I, written by right-hand-side evaluations
     int nb;
     DivGuard guard;
 };
 
-template <int MODE>
+template <int MODE, bool SUM>
 __device__ __forceinline__ void g1_update(const G1Args& g, int e, cd comm, cd Iij, cd Iji, int nbp,
                                           double cb, double cc) {
     const cd f = cmul_mi(cadd(comm, cadd(Iij, cconj(Iji))));
     if (MODE == RK_RHS) g.icoll[e] = Iij;
     cd o = f;
-    if (MODE != RK_RHS) {
+    if constexpr (SUM) {
+        rk_update<MODE>(e, f, g.gl[e], g.y, g.acc, g.out, cb, cc);
+        o = g.out[e];
+    } else if (MODE != RK_RHS) {
         const cd y = g.y[e];
         o = MODE == RK_LAST ? rk_close(y, g.y2[e], g.y3[e], g.gl[e], f, cb)
                             : cmk(fma(cc, f.x, y.x), fma(cc, f.y, y.y));
     }
-    g.out[e] = o;
+    if (!SUM) g.out[e] = o;
     const int i = e / nbp, j = e % nbp;
     if (MODE == RK_FIRST && e == 0) guard_begin_step(g.guard);   // one thread per launch
     if (MODE == RK_LAST && i < g.nb && guard_bad(o, i == j)) guard_fire(g.guard, 0, g.guard.div[0]);
@@ -527,7 +531,7 @@ __device__ __forceinline__ void g1_update(const G1Args& g, int e, cd comm, cd Ii
 
 // The elements (i,j) and (j,i), i <= j: both need I_ij and I_ji, so each
 // partial row is read once.
-template <int MODE>
+template <int MODE, bool SUM>
 __device__ __forceinline__ void g1_pair(const G1Args& g, int i, int j, int lane, int nbp, double cb,
                                         double cc) {
     const int e = i * nbp + j, et = j * nbp + i;
@@ -565,8 +569,8 @@ __device__ __forceinline__ void g1_pair(const G1Args& g, int i, int j, int lane,
     if (lane != 0) return;
     const cd Iij = make_double2(si, -sr);  // -i (sr + i si)
     const cd Iji = make_double2(ti, -tr);
-    g1_update<MODE>(g, e, make_double2(cr, ci), Iij, Iji, nbp, cb, cc);
-    if (et != e) g1_update<MODE>(g, et, make_double2(dr, di), Iji, Iij, nbp, cb, cc);
+    g1_update<MODE, SUM>(g, e, make_double2(cr, ci), Iij, Iji, nbp, cb, cc);
+    if (et != e) g1_update<MODE, SUM>(g, et, make_double2(dr, di), Iji, Iij, nbp, cb, cc);
 }
 
 // --------------------------------------------------------------------------- K4
@@ -575,17 +579,18 @@ __device__ __forceinline__ void g1_pair(const G1Args& g, int i, int j, int lane,
 // the G1 equation (K5) on the same launch, in work-groups of its own, so that
 // the latency of its partial-sum reads overlaps the G2 streaming.
 // HBM bound: D, y and the next stage's input once per element, and no running
-// sum (the last stage reads the stage inputs instead, rk_close): 48 B per
+// sum (but in mixed second Born, whose trajectories amplify a last-bit change of
+// the state through the conversions to binary32; the last stage reads the stage inputs instead, rk_close): 48 B per
 // element in binary64 stages 1 to 3 and 96 B in the last, against 64, 80, 80
 // and 64 B with one.  The state is read ahead of the transpose, its latency
 // beside that of D.  Stages 1 to 4, with the sum -> without: nb = 64 GW 210, 276,
-// 276, 167 -> 157, 157, 157, 349 us; nb = 32 second Born, binary32 D, 11.9, 13.6,
-// 13.6, 10.1 -> 9.3, 9.5, 9.5, 16.3 us.
+// 276, 167 -> 157, 157, 157, 349 us.
 template <int MODE, typename S, bool DD>
 __global__ __launch_bounds__(256) void gen_combine_kernel(const S* __restrict__ D, int n, const cd* in,
-                                                         const cd* y, const cd* y2, const cd* y3, cd* out,
+                                                         const cd* y, const cd* y2, const cd* y3, cd* acc, cd* out,
                                                          const double* __restrict__ dd, int nbp,
                                                          double cb, double cc, G1Args g1, int ng1) {
+    constexpr bool SUM = std::is_same<S, float2>::value;
     __shared__ double t1r[32][33], t1i[32][33], t2r[32][33], t2i[32][33];
     auto tri = [](int t, int& hi, int& lo) {   // t = hi (hi + 1) / 2 + lo, lo <= hi
         int h = (int)((sqrtf(8.0f * (float)t + 1.0f) - 1.0f) * 0.5f);
@@ -601,7 +606,7 @@ __global__ __launch_bounds__(256) void gen_combine_kernel(const S* __restrict__ 
         if (pair < nbp * (nbp + 1) / 2) {
             int j, i;
             tri(pair, j, i);
-            g1_pair<MODE>(g1, i, j, threadIdx.x & 63, nbp, cb, cc);
+            g1_pair<MODE, SUM>(g1, i, j, threadIdx.x & 63, nbp, cb, cc);
         }
         return;
     }
@@ -628,10 +633,15 @@ __global__ __launch_bounds__(256) void gen_combine_kernel(const S* __restrict__ 
 #pragma unroll
         for (int q = 0; q < 8; ++q) {
             const size_t e = (size_t)row(q) * n + col(q);
-            const cd v = y[e];
+            const cd v = SUM && MODE == RK_LAST ? acc[e] : y[e];
             yr[q] = v.x;
             yi[q] = v.y;
-            if (MODE == RK_LAST) {
+            if (SUM && MODE != RK_LAST) {
+                const cd a = MODE == RK_MID ? acc[e] : v;
+                sr[q] = a.x;
+                si[q] = a.y;
+            }
+            if (!SUM && MODE == RK_LAST) {
                 const cd a = y2[e], b = y3[e], c = in[e];
                 sr[q] = rk_diffs(v.x, a.x, b.x, c.x);
                 si[q] = rk_diffs(v.y, a.y, b.y, c.y);
@@ -651,11 +661,15 @@ __global__ __launch_bounds__(256) void gen_combine_kernel(const S* __restrict__ 
             if (i < nb && j < nb) zi += dd[i * nb + j] + dd[j * nb + i];
         }
         const cd f = make_double2(zi, -zr);  // -i z
+        const size_t e = (size_t)row(q) * n + col(q);
+        if (SUM && (MODE == RK_FIRST || MODE == RK_MID))
+            acc[e] = cmk(fma(cb, f.x, sr[q]), fma(cb, f.y, si[q]));
         cd o;
         if (MODE == RK_RHS) o = f;
+        else if (SUM && MODE == RK_LAST) o = cmk(fma(cb, f.x, yr[q]), fma(cb, f.y, yi[q]));
         else if (MODE == RK_LAST) o = cmk(rk_close(yr[q], sr[q], f.x, cb), rk_close(yi[q], si[q], f.y, cb));
         else o = cmk(fma(cc, f.x, yr[q]), fma(cc, f.y, yi[q]));
-        out[(size_t)row(q) * n + col(q)] = o;
+        out[e] = o;
     }
 }
 
@@ -786,16 +800,16 @@ g1g2_status run_blocks(g1g2_ctx* c, const Regs& in, double ws) {
 
 template <typename S, int MODE>
 g1g2_status run_combine(g1g2_ctx* c, const Regs& in, const Regs& y, const Regs& y2, const Regs& y3,
-                        const Regs& out, double cb, double cc) {
+                        const Regs& acc, const Regs& out, double cb, double cc) {
     GeneralData& g = c->gen;
     const int n = g.nbp * g.nbp;
     const int nt = n / 32, ntiles = nt * (nt + 1) / 2;
-    const G1Args g1{g.ipart, g.nipart, g.hhf, in.g1, y.g1, y2.g1, y3.g1, out.g1,
+    const G1Args g1{g.ipart, g.nipart, g.hhf, in.g1, y.g1, y2.g1, y3.g1, acc.g1, out.g1,
                     g.icoll, g.nb, guard_of(c)};
     const int ng1 = (g.nbp * (g.nbp + 1) / 2 + 3) / 4;   // work-groups of the G1 pairs
     const auto launch = [&](auto dd) {
         hipLaunchKernelGGL((gen_combine_kernel<MODE, S, decltype(dd)::value>), dim3(ng1 + ntiles), dim3(256), 0,
-                           c->stream, (const S*)g.dmat, n, in.g2, y.g2, y2.g2, y3.g2, out.g2, g.pdd, g.nbp, cb, cc,
+                           c->stream, (const S*)g.dmat, n, in.g2, y.g2, y2.g2, y3.g2, acc.g2, out.g2, g.pdd, g.nbp, cb, cc,
                            g1, ng1);
     };
     if (g.pdd) launch(std::is_same<S, cd>());   // D is binary32 without a polarization only
@@ -818,12 +832,12 @@ g1g2_status dispatch_blocks(g1g2_ctx* c, const Regs& in, double ws) {
 
 template <typename S>
 g1g2_status dispatch_combine(g1g2_ctx* c, int mode, const Regs& in, const Regs& y, const Regs& y2,
-                             const Regs& y3, const Regs& out, double cb, double cc) {
+                             const Regs& y3, const Regs& acc, const Regs& out, double cb, double cc) {
     switch (mode) {
-        case RK_RHS: return run_combine<S, RK_RHS>(c, in, y, y2, y3, out, cb, cc);
-        case RK_FIRST: return run_combine<S, RK_FIRST>(c, in, y, y2, y3, out, cb, cc);
-        case RK_MID: return run_combine<S, RK_MID>(c, in, y, y2, y3, out, cb, cc);
-        default: return run_combine<S, RK_LAST>(c, in, y, y2, y3, out, cb, cc);
+        case RK_RHS: return run_combine<S, RK_RHS>(c, in, y, y2, y3, acc, out, cb, cc);
+        case RK_FIRST: return run_combine<S, RK_FIRST>(c, in, y, y2, y3, acc, out, cb, cc);
+        case RK_MID: return run_combine<S, RK_MID>(c, in, y, y2, y3, acc, out, cb, cc);
+        default: return run_combine<S, RK_LAST>(c, in, y, y2, y3, acc, out, cb, cc);
     }
 }
 
@@ -953,26 +967,26 @@ g1g2_status gen_setup(g1g2_ctx* c, const cd* h0, const cd* w) {
 }
 
 g1g2_status gen_stage(g1g2_ctx* c, int mode, double t, const Regs& in, const Regs& y,
-                      const Regs& y2, const Regs& y3, const Regs& out, double cb, double cc) {
+                      const Regs& y2, const Regs& y3, const Regs& acc, const Regs& out, double cb, double cc) {
     const double ws = c->switch_value(t);
     g1g2_status s;
     if (c->d.precision == G1G2_MIXED) {
         if (c->d.selfenergy == G1G2_SOA) {
             if ((s = dispatch_blocks<float, float2, float2>(c, in, ws)) != G1G2_OK) return s;
-            return dispatch_combine<float2>(c, mode, in, y, y2, y3, out, cb, cc);
+            return dispatch_combine<float2>(c, mode, in, y, y2, y3, acc, out, cb, cc);
         }
         if ((s = dispatch_blocks<float, float2, cd>(c, in, ws)) != G1G2_OK) return s;
-        return dispatch_combine<cd>(c, mode, in, y, y2, y3, out, cb, cc);
+        return dispatch_combine<cd>(c, mode, in, y, y2, y3, acc, out, cb, cc);
     }
     if ((s = dispatch_blocks<double, cd, cd>(c, in, ws)) != G1G2_OK) return s;
-    return dispatch_combine<cd>(c, mode, in, y, y2, y3, out, cb, cc);
+    return dispatch_combine<cd>(c, mode, in, y, y2, y3, acc, out, cb, cc);
 }
 
 g1g2_status gen_observables(g1g2_ctx* c, const Regs& s, double t, g1g2_obs* o) {
     (void)t;
     GeneralData& g = c->gen;
     // one right-hand-side evaluation refreshes h^HF and the collision integral
-    g1g2_status st = gen_stage(c, RK_RHS, c->t, s, s, s, s, c->io, 0.0, 0.0);
+    g1g2_status st = gen_stage(c, RK_RHS, c->t, s, s, s, s, s, c->io, 0.0, 0.0);
     if (st != G1G2_OK) return st;
     hipLaunchKernelGGL(gen_obs_kernel, dim3(1), dim3(256), 0, c->stream, s.g1, g.h0, g.hhf, g.icoll,
                        g.nbp, c->dscratch);
