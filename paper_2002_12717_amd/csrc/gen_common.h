@@ -54,10 +54,13 @@ __device__ __forceinline__ void stage_block(const S* __restrict__ src, T* re, T*
 // instead of 1.11 ms per launch in binary64; holding a wave's rows of G> in
 // registers as well gained nothing in binary64 and lost in binary32.  The
 // quasi-Hamiltonians (gen_comm, two work-groups per compute unit) take the same
-// shape.
+// shape.  Nb = 48 (75 KB of LDS in binary64, two work-groups per compute unit) runs
+// nine waves of one tile instead of three of three, 95 registers each, so that both
+// work-groups' waves fit: at 45 orbitals gen_main 331 -> 307 us, gen_vt 200 -> 192 us,
+// and a mixed second Born step 1.73 -> 1.35 ms.
 template <int NB>
 struct MainShape : Shape<NB> {
-    static constexpr int WAVES = NB == 64 ? 8 : Shape<NB>::WAVES;
+    static constexpr int WAVES = NB == 64 ? 8 : NB == 48 ? 9 : Shape<NB>::WAVES;
     static constexpr int TPW = Shape<NB>::TILES / WAVES;
     static constexpr int THREADS = 64 * WAVES;
 };

@@ -56,11 +56,11 @@ struct HfArgs {
 };
 
 // Row (ij) of h^HF by one work-group of THREADS threads, of which at most four
-// waves sum the row: the order of the sum, and so h^HF to the last bit, does not
-// depend on the block size of the launch the rows run in.
+// waves sum the row (three of nine at Nb = 48): the order of the sum, and so h^HF
+// to the last bit, does not depend on the block size of the launch the rows run in.
 template <int THREADS>
 __device__ __forceinline__ void hf_row(const HfArgs& a, int ij) {
-    constexpr int EFF = THREADS < 256 ? THREADS : 256;
+    constexpr int EFF = THREADS < 256 ? THREADS : THREADS % 256 == 0 ? 256 : 192;
     constexpr int NW = EFF / 64;
     __shared__ double part[2][NW];
     const int nbp = a.nbp, n2 = nbp * nbp;
@@ -107,16 +107,16 @@ __device__ __forceinline__ void hf_row(const HfArgs& a, int ij) {
 // --------------------------------------------------------------------------- K2
 // Right sandwich on row blocks of W: Vt[k][l][p][q] = (G<^T W_pq G<)[k][l].
 // Work-groups nvt.. of the launch compute the rows of h^HF (K1).
-// Nb = 64 takes eight waves of two tiles; the other sizes take Shape's waves.
+// The waves are those of MainShape.
 template <int NB>
-__host__ __device__ constexpr int vt_threads() { return NB == 64 ? 512 : Shape<NB>::THREADS; }
+__host__ __device__ constexpr int vt_threads() { return MainShape<NB>::THREADS; }
 
 template <typename T, typename S, int NB>
 __global__ __launch_bounds__(vt_threads<NB>()) void gen_vt_kernel(const S* __restrict__ wrows,
                                                                  const cd* __restrict__ gl,
                                                                  S* __restrict__ vt, int nvt,
                                                                  HfArgs hf) {
-    typedef Shape<NB> SH;
+    typedef MainShape<NB> SH;
     constexpr int LD = SH::LD;
     if ((int)blockIdx.x >= nvt) {
         hf_row<vt_threads<NB>()>(hf, blockIdx.x - nvt);
@@ -215,7 +215,7 @@ __global__ __launch_bounds__(vt_threads<NB>()) void gen_vt_kernel(const S* __res
         }
         return;
     }
-    if constexpr (SH::TPW == 1) {
+    if constexpr (NB <= 32) {
         constexpr int PER = NB * NB / SH::THREADS;
         const int ti = wave / SH::NT, tj = wave % SH::NT;
         const int lane = threadIdx.x & 63, li = lane & 15, lk = lane >> 4;
@@ -333,7 +333,7 @@ __global__ __launch_bounds__(MainShape<NB>::THREADS) void gen_main_kernel(
     cd* __restrict__ ipart, double ws) {
     typedef MainShape<NB> SH;
     constexpr int LD = SH::LD;
-    using Acc = typename std::conditional<SH::TPW == 1, CAcc4<T>, CAcc<T>>::type;
+    using Acc = typename std::conditional<NB <= 32, CAcc4<T>, CAcc<T>>::type;
     constexpr bool STAGE = NB <= 32;
     __shared__ T b0_re[NB * LD], b0_im[NB * LD], b1_re[NB * LD], b1_im[NB * LD];
     __shared__ SmallOps<T, NB, STAGE> ops;
@@ -365,7 +365,7 @@ __global__ __launch_bounds__(MainShape<NB>::THREADS) void gen_main_kernel(
     const int bfirst = xcd_block(blockIdx.x, gridDim.x);
     // Nb <= 32: the next operand blocks are prefetched into registers, so their
     // global loads overlap the matrix-core work of the current phase
-    constexpr bool PRE = SH::TPW == 1;
+    constexpr bool PRE = NB <= 32;
     constexpr int PER = PRE ? NB * NB / SH::THREADS : 1;
     T pv_re[PER], pv_im[PER], pc_re[PER], pc_im[PER];
     auto fetch = [&](auto src, T* re, T* im) {
@@ -785,7 +785,7 @@ g1g2_status run_blocks(g1g2_ctx* c, const Regs& in, double ws) {
     const S* wcoll = mixed ? (const S*)g.w_coll32 : (const S*)g.w_coll;
     // a single-tile-per-wave shape prefetches the next row block in registers and
     // wants several blocks per work-group; the larger shapes want the wider grid
-    const int grid_vt = std::min(NB * NB, Shape<NB>::TPW == 1 ? 512 : 1024);
+    const int grid_vt = std::min(NB * NB, NB <= 32 ? 512 : 1024);
     const HfArgs hf{g.w_hf, g.h0, in.g1, g.hhf, g.gg, g.nbp, g.nb, ws};
     hipLaunchKernelGGL((gen_vt_kernel<T, S, NB>), dim3(grid_vt + NB * NB), dim3(vt_threads<NB>()), 0,
                        c->stream, wrows, in.g1, (S*)g.vt, grid_vt, hf);
