@@ -547,7 +547,8 @@ g1g2_status g1g2_set_h0(g1g2_ctx* c, const void* h0) {
         const int ns = c->d.nb;
         const double U = c->d.U;
         const cd* h0p = hh.p;
-        return hub_setup(c, 1, &ns, &U, &h0p, nullptr);
+        if ((s = hub_setup(c, 1, &ns, &U, &h0p, nullptr)) != G1G2_OK) return s;
+        return hub_check_state(c);   // the new hoppings may have made the cluster eligible
     }
     return gen_set_h0(c, hh.p);
 }

@@ -220,7 +220,7 @@ g1g2_status hub_stage_diag(g1g2_ctx* c, int mode, double t, const Regs& in, cons
 size_t hub_diag_bytes(const g1g2_ctx* c);
 // Stages over one triangle of the pair matrix (hub_tile.hip): the lists of its
 // set-up (kept with the work list, hub_setup), the symmetry check of the state y (synchronizes; call
-// whenever a state is set), whether steps take them now, one step.
+// whenever a state is set and after every hub_setup), whether steps take them now, one step.
 // hub_tile_step writes y4 by the third stage and, with last, the new state to out;
 // full: the stage registers are written whole, not only where stages read them.
 constexpr int TILE_ROW_MIN = 44;   // least ns of the wave-per-row form

@@ -574,6 +574,7 @@ int hub_tile_diags(const g1g2_ctx* c) {
 // 2^-44: states that the library propagated, and inputs symmetric to rounding, pass
 g1g2_status hub_check_state(g1g2_ctx* c) {
     HubbardData& H = c->hub;
+    c->herm = false;   // a state that is not checked does not take the triangle
     if (!H.tiles) return G1G2_OK;
     StageArgs s = hub_make_stage(c, 0.0, c->y, c->y, c->y, c->y, 0.0, 0.0);
     s.work = H.twork;

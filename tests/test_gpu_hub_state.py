@@ -1,0 +1,82 @@
+"""Which kernels the steps of a large Hubbard cluster take follows its state and its
+Hamiltonian, and the adjoint follows the forward pass it belongs to.
+
+The smallest chain whose steps may take one triangle of the pair matrix (33 sites,
+33^4 > 2^20 elements) stands for the size; results of the same kernels are compared
+bit for bit.
+"""
+import numpy as np
+import pytest
+import torch
+
+from workloads import chain_hopping, random_g2, random_gless, rng
+
+pytestmark = pytest.mark.gpu
+
+NS = 33
+
+
+def _system(r, ns=NS):
+    h = chain_hopping(ns)
+    h0 = np.stack([h + np.diag(r.uniform(-0.5, 0.5, ns)), 0.8 * h]).astype(complex)
+    return h0, np.stack([random_gless(ns, r), random_gless(ns, r)])
+
+
+def _complex_hopping(h0):
+    """The same hopping with a phase on one bond."""
+    h = h0.copy()
+    h[:, 0, 1] *= 1j
+    h[:, 1, 0] *= -1j
+    return h
+
+
+def _states(r):
+    sym = random_g2(NS, r, scale=0.05, exchange=False)
+    bad = sym.copy()
+    bad[3, 4, 5, 6] += 1e-3
+    return sym, bad
+
+
+def _equal(a, b):
+    same = [bool(np.array_equal(u, v)) for u, v in zip(a[:2], b[:2])]
+    assert same == [True, True]
+
+
+def test_state_set_under_complex_hoppings(lib):
+    """Real hoppings, complex ones, a state without the pair symmetry set under these,
+    real ones again: the steps evaluate every element, as the slice kernel does."""
+    from paper_2002_12717_amd import binding as B
+    r = rng(601)
+    h0, g1 = _system(r)
+    sym, bad = _states(r)
+    out = []
+    for flags in (0, B.HUB_SLICE_KERNEL):
+        p = B.Propagator(B.HUBBARD, B.SOA, NS, h0, g1, U=1.1, G2_0=sym, flags=flags)
+        p.set_h0(_complex_hopping(h0))
+        p.set_state(g1, bad)
+        p.set_h0(h0)
+        p.step(0.01, 3)
+        out.append(p.get_state())
+        p.close()
+    _equal(*out)
+
+
+def test_hoppings_become_real(lib):
+    """A context made with complex hoppings that becomes real takes the triangle for a
+    symmetric state, as one made with the real ones."""
+    from paper_2002_12717_amd import binding as B
+    r = rng(602)
+    h0, g1 = _system(r)
+    sym, _ = _states(r)
+    p = B.Propagator(B.HUBBARD, B.SOA, NS, _complex_hopping(h0), g1, U=1.1, G2_0=sym)
+    p.set_h0(h0)
+    q = B.Propagator(B.HUBBARD, B.SOA, NS, h0, g1, U=1.1, G2_0=sym)
+    s = B.Propagator(B.HUBBARD, B.SOA, NS, h0, g1, U=1.1, G2_0=sym, flags=B.HUB_SLICE_KERNEL)
+    for x in (p, q, s):
+        x.step(0.01, 3)
+    a, b, c = p.get_state(), q.get_state(), s.get_state()
+    for x in (p, q, s):
+        x.close()
+    _equal(a, b)
+    apart = not np.array_equal(b[1], c[1])   # the two kernels round differently, so equality tells them apart
+    assert apart
