@@ -180,6 +180,11 @@ void drop_graph(g1g2_ctx* c) {
     c->graph_steps = 0;
 }
 
+// Whether the captured steps are of size dt and take the kernels of the present state.
+bool graph_current(const g1g2_ctx* c, double dt) {
+    return c->graph && c->graph_dt == dt && c->graph_tile == hub_tile_ok(c);
+}
+
 // Steps per captured graph: g1g2_step_rk4 replays it for every whole group of
 // that many steps and launches the rest one by one.
 constexpr int GRAPH_STEPS = 8;
@@ -207,6 +212,7 @@ g1g2_status capture(g1g2_ctx* c, double dt, int gsteps) {
     (void)hipGraphDestroy(g);
     HIP_OK(c, e);
     c->graph_dt = dt;
+    c->graph_tile = hub_tile_ok(c);
     c->graph_steps = gsteps;
     return G1G2_OK;
 }
@@ -445,7 +451,7 @@ g1g2_status g1g2_step_rk4(g1g2_ctx* c, double dt, int64_t nsteps) {
     }
     if (n < nsteps && can_capture(c) && nsteps >= GRAPH_STEPS) {
         // one graph of GRAPH_STEPS steps per dt, captured on first use and kept
-        if (!c->graph || c->graph_dt != dt)
+        if (!graph_current(c, dt))
             if ((s = capture(c, dt, GRAPH_STEPS)) != G1G2_OK) return s;
         for (; n + GRAPH_STEPS <= nsteps; n += GRAPH_STEPS) HIP_OK(c, hipGraphLaunch(c->graph, c->stream));
     }
@@ -468,7 +474,7 @@ g1g2_status g1g2_step_path(const g1g2_ctx* c, int32_t* path) {
 g1g2_status g1g2_prepare_graph(g1g2_ctx* c, double dt) {
     if (!c || !(dt > 0.0) || !std::isfinite(dt)) return G1G2_EINVAL;
     if (c->d.basis == G1G2_HUBBARD && hub_persistent_ok(c)) return G1G2_OK;
-    if (!can_capture(c) || (c->graph && c->graph_dt == dt)) return G1G2_OK;
+    if (!can_capture(c) || graph_current(c, dt)) return G1G2_OK;
     return capture(c, dt, GRAPH_STEPS);
 }
 
@@ -516,6 +522,7 @@ g1g2_status g1g2_set_state(g1g2_ctx* c, const void* G1, const void* G2, double t
         return set_error(c, G1G2_ESTATE, "single-cluster call on a batch");
     const bool dev = c->d.flags & G1G2_PTR_DEVICE;
     g1g2_status s;
+    c->herm = false;   // until hub_check_state has seen the whole new state
     if ((s = load_component(c, G1, dev, c->y.g1, 2)) != G1G2_OK) return s;
     if (G2) {
         if ((s = load_component(c, G2, dev, c->y.g2, 4)) != G1G2_OK) return s;
@@ -524,11 +531,7 @@ g1g2_status g1g2_set_state(g1g2_ctx* c, const void* G1, const void* G2, double t
     }
     if ((s = guard_clear(c)) != G1G2_OK) return s;
     if (c->d.basis == G1G2_JELLIUM && (s = jel_state_changed(c)) != G1G2_OK) return s;
-    if (c->d.basis == G1G2_HUBBARD) {
-        const bool before = hub_tile_ok(c);
-        if ((s = hub_check_state(c)) != G1G2_OK) return s;
-        if (hub_tile_ok(c) != before) drop_graph(c);   // captured steps take other kernels
-    }
+    if (c->d.basis == G1G2_HUBBARD && (s = hub_check_state(c)) != G1G2_OK) return s;
     HIP_OK(c, hipStreamSynchronize(c->stream));
     c->t = t;
     return G1G2_OK;

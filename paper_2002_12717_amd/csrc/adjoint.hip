@@ -538,6 +538,7 @@ struct AdjState {
     bool have_mixed = false, have_keep = false;
     bool ready = false;        // its buffers are complete (a forward pass has begun)
     bool keep = false;         // one segment, whose states the forward pass kept
+    bool herm = false;         // the symmetry check's result (ctx) for the states of the forward pass
     bool mixed = false;        // binary32 G2 stage copies (Y2, Y3, Y4), as the mixed forward stages
     int interval = 0;
     double dt = 0.0, t0 = 0.0;
@@ -705,6 +706,7 @@ g1g2_status g1g2_forward_checkpointed(g1g2_ctx* c, double dt, int64_t nsteps, in
     st->nsteps = nsteps;
     st->mixed = mixed;
     st->keep = keep;
+    st->herm = c->herm;
     st->interval = seglen;
     st->dt = dt;
     st->t0 = c->t;
@@ -794,8 +796,12 @@ g1g2_status g1g2_adjoint(g1g2_ctx* c, const double* wa, const double* wb, double
     for (int q = st->nck - 1; q >= 0; --q) {
         const int64_t n0 = (int64_t)q * st->interval;
         const int64_t n1 = std::min<int64_t>(n0 + st->interval, st->nsteps);
-        // recompute the segment forward, keeping y_n and the stage states of every step
-        if (!st->keep && (s = copy_reg(c, c->y, st->ckpt[q])) != G1G2_OK) return s;
+        // recompute the segment forward, keeping y_n and the stage states of every step;
+        // the kernels are those of the forward pass, whatever state has been set since
+        if (!st->keep) {
+            c->herm = st->herm;
+            if ((s = copy_reg(c, c->y, st->ckpt[q])) != G1G2_OK) return s;
+        }
         for (int64_t n = n0; n < n1 && !st->keep; ++n) {
             const int m = (int)(n - n0);
             if ((s = copy_reg(c, st->seg[m], c->y)) != G1G2_OK) return s;
@@ -827,6 +833,7 @@ g1g2_status g1g2_adjoint(g1g2_ctx* c, const double* wa, const double* wb, double
         }
     }
     // restore the final state
+    c->herm = st->herm;
     if ((s = copy_reg(c, c->y, st->ckpt[st->nck])) != G1G2_OK) return s;
     std::vector<double> gr((size_t)8 * st->nsteps);
     double L = 0.0;

@@ -143,7 +143,7 @@ struct g1g2_ctx {
     hipStream_t stream = nullptr;
     int device = 0;
     std::string err;
-    bool herm = false;         // Hubbard: the state passed hub_check_state
+    bool herm = false;         // Hubbard: the state y passed hub_check_state (false while it is not checked)
     double t = 0.0;
     int64_t step = 0;
     size_t n1 = 0, n2 = 0;     // internal element counts of G1 and G2
@@ -166,6 +166,7 @@ struct g1g2_ctx {
     hipGraphExec_t graph = nullptr;
     double graph_dt = 0.0;
     int graph_steps = 0;
+    bool graph_tile = false;   // hub_tile_ok when it was captured
     bool graphs = true;
     // kernel timing (g1g2_profile_rhs): events recorded after every launch
     bool prof = false;

@@ -80,3 +80,48 @@ def test_hoppings_become_real(lib):
     _equal(a, b)
     apart = not np.array_equal(b[1], c[1])   # the two kernels round differently, so equality tells them apart
     assert apart
+
+
+def _gradient(p, a, b):
+    loss, gc, gu = p.adjoint(a, b, 3)
+    return [loss, gu, gc]
+
+
+@pytest.mark.parametrize("first", ["bad", "sym"])
+def test_state_set_between_forward_and_adjoint(lib, first):
+    """A state of the other symmetry set between the forward pass and the adjoint: the
+    segments are recomputed by the kernels of the forward pass, and the steps after
+    the adjoint, which restores the final state, take those that this state calls
+    for, also where a graph of the other kernels was captured in between."""
+    from paper_2002_12717_amd import binding as B
+    r = rng(603)
+    h0, g1 = _system(r)
+    sym, bad = _states(r)
+    a, b = r.uniform(-1, 1, NS), r.uniform(-1, 1, NS)
+    x, c, tc = np.arange(NS) - 16.0, 0.1 * r.standard_normal(3), 0.02 * np.arange(3)
+    start, other = (bad, sym) if first == "bad" else (sym, bad)
+    out = []
+    for between in (True, False):
+        stream = torch.cuda.Stream()
+        p = B.Propagator(B.HUBBARD, B.SOA, NS, h0, g1, U=1.1, stream=stream.cuda_stream)
+        p.set_drive(x, c, tc, 0.02)
+        p.set_state(g1, start)
+        p.forward_checkpointed(0.01, 5, 2)
+        if between:
+            p.set_state(g1, other)
+        res = _gradient(p, a, b)
+        p.set_drive(x, [], [], 0.02)
+        if between:
+            p.set_state(g1, other)
+            p.prepare_graph(0.01)
+            p.set_drive(x, c, tc, 0.02)
+            res += _gradient(p, a, b)
+            p.set_drive(x, [], [], 0.02)
+        else:
+            res += res
+        p.step(0.01, 8)
+        out.append((res, p.get_state()[:2]))
+        p.close()
+    same = [bool(np.array_equal(u, v)) for u, v in zip(out[0][0], out[1][0])]
+    assert all(same)
+    _equal(out[0][1], out[1][1])
