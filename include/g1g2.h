@@ -328,7 +328,7 @@ g1g2_status g1g2_batch_get_state(g1g2_ctx* ctx, int32_t cluster, void* G1, void*
  * (grad_c[M], M as given to g1g2_set_drive; may be NULL) and U (grad_U),
  * by the reverse sweep of the discrete RK4 map with each checkpoint segment
  * recomputed once.  a, b: host arrays of nb doubles.  The final state is left
- * in place.  ESTATE without a preceding forward_checkpointed;
+ * in place.  ESTATE without a preceding forward_checkpointed that returned OK;
  * EUNSUPPORTED for other bases, selfenergies or batches, and with a
  * switching ramp set.                                                       */
 g1g2_status g1g2_forward_checkpointed(g1g2_ctx* ctx, double dt, int64_t nsteps, int32_t interval);

@@ -536,7 +536,7 @@ struct AdjState {
     int have_interval = 0;
     size_t have_n1 = 0, have_n2 = 0;
     bool have_mixed = false, have_keep = false;
-    bool ready = false;        // its buffers are complete (a forward pass has begun)
+    bool ready = false;        // a forward pass has ended and its states are whole
     bool keep = false;         // one segment, whose states the forward pass kept
     bool herm = false;         // the symmetry check's result (ctx) for the states of the forward pass
     bool mixed = false;        // binary32 G2 stage copies (Y2, Y3, Y4), as the mixed forward stages
@@ -741,7 +741,6 @@ g1g2_status g1g2_forward_checkpointed(g1g2_ctx* c, double dt, int64_t nsteps, in
     }
     const int ns = c->hub.hdesc[0].ns;
     HIP_OK(c, hipMemsetAsync(st->red, 0, (size_t)R_N * ns * ns * sizeof(cd), c->stream));
-    st->ready = true;
     if (keep) {
         // the steps themselves fill the segment: y_n, Y2, Y3, Y4 of step n, each step
         // writing the next y_n; checked for divergence as g1g2_step_rk4 does
@@ -759,6 +758,7 @@ g1g2_status g1g2_forward_checkpointed(g1g2_ctx* c, double dt, int64_t nsteps, in
             if ((s = copy_reg(c, c->y, done)) != G1G2_OK) return s;
             if ((s = step_end(c, c->t + (double)(m1 - n) * dt, m1 - n)) != G1G2_OK) return s;
         }
+        st->ready = true;
         return G1G2_OK;
     }
     for (int q = 0; q < st->nck; ++q) {
@@ -766,7 +766,9 @@ g1g2_status g1g2_forward_checkpointed(g1g2_ctx* c, double dt, int64_t nsteps, in
         const int64_t n = std::min<int64_t>(st->interval, nsteps - (int64_t)q * st->interval);
         if ((s = g1g2_step_rk4(c, dt, n)) != G1G2_OK) return s;
     }
-    return copy_reg(c, st->ckpt[st->nck], c->y);
+    if ((s = copy_reg(c, st->ckpt[st->nck], c->y)) != G1G2_OK) return s;
+    st->ready = true;
+    return G1G2_OK;
 }
 
 g1g2_status g1g2_adjoint(g1g2_ctx* c, const double* wa, const double* wb, double* grad_c,

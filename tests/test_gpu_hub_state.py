@@ -125,3 +125,31 @@ def test_state_set_between_forward_and_adjoint(lib, first):
     same = [bool(np.array_equal(u, v)) for u, v in zip(out[0][0], out[1][0])]
     assert all(same)
     _equal(out[0][1], out[1][1])
+
+
+@pytest.mark.parametrize("ns,interval", [(NS, 0), (NS, 2), (4, 2)])
+def test_adjoint_after_a_forward_pass_that_failed(lib, ns, interval):
+    """A forward pass that diverged leaves nothing to differentiate: the adjoint
+    answers ESTATE, also where the buffers of an earlier gradient serve again, and a
+    later forward pass restores it."""
+    from paper_2002_12717_amd import binding as B
+    r = rng(604)
+    h0, g1 = _system(r, ns)
+    a, b = r.uniform(-1, 1, ns), r.uniform(-1, 1, ns)
+    p = B.Propagator(B.HUBBARD, B.SOA, ns, h0, g1, U=1.1)
+    far = g1.copy()
+    far[0, 0, 0] = 2j                          # an occupation of 2
+    out = []
+    for _ in range(2):
+        p.set_state(g1)
+        p.forward_checkpointed(0.01, 5, interval)
+        out.append(p.adjoint(a, b, 0)[::2])
+        p.set_state(far)
+        with pytest.raises(B.G1G2Error) as e:
+            p.forward_checkpointed(0.01, 5, interval)
+        assert e.value.status == B.EDIVERGED
+        with pytest.raises(B.G1G2Error) as e:
+            p.adjoint(a, b, 0)
+        assert e.value.status == B.ESTATE
+    p.close()
+    assert out[0] == out[1]
