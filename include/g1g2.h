@@ -318,9 +318,11 @@ g1g2_status g1g2_batch_get_state(g1g2_ctx* ctx, int32_t cluster, void* G1, void*
  * keeps its states and Runge-Kutta stage states, so device memory grows by
  * about (nsteps/interval + 4 interval + 8) states (a state of ns = 64 is
  * 268 MB: 4000 steps hold about 70 GB).  With interval <= 0 a short run (at most
- * 128 stage states, and an eighth of the device's memory) keeps the states of all
- * its steps instead and recomputes nothing.  The buffers stay with the context
- * and serve the next gradient of the same shape.
+ * 128 stage states, an eighth of the device's memory and a quarter of what is free
+ * of it) keeps the states of all its steps instead and recomputes nothing; where
+ * they cannot be allocated, it takes checkpoints.  The buffers stay with the
+ * context and serve the next gradient of the same shape; after an error none are
+ * held.
  * g1g2_adjoint then returns the loss
  *   L = sum_i a[i] d_i(T) + sum_i b[i] (n^up_ii(T) + n^dn_ii(T)),
  *   n_ii = Im G^<_ii,  d_i = n^up_ii n^dn_ii - Re G2_iiii,

@@ -526,8 +526,10 @@ namespace {
 
 // Stage states that the forward pass may keep when the library chooses the
 // interval: with four states per step the reverse sweep recomputes nothing.  Up to
-// this many (and an eighth of the device's memory) they cost no more than the
-// checkpoints and segments of a longer run would.
+// this many, an eighth of the device's memory and, all buffers of the adjoint
+// counted, a quarter of what is free of it (a program that already holds memory, or
+// several contexts, keep checkpoints instead: the sweep then recomputes each step
+// once, 7.5 instead of 36 GB for 32 steps of the 8x8 cluster).
 constexpr int64_t ADJ_KEEP_STATES = 128;
 
 struct AdjState {
@@ -535,6 +537,7 @@ struct AdjState {
     int64_t have_steps = 0;    // steps, interval and storage the buffers below were made for
     int have_interval = 0;
     size_t have_n1 = 0, have_n2 = 0;
+    size_t have_bytes = 0;     // device memory of their states
     bool have_mixed = false, have_keep = false;
     bool ready = false;        // a forward pass has ended and its states are whole
     bool keep = false;         // one segment, whose states the forward pass kept
@@ -648,6 +651,53 @@ g1g2_status vjp(g1g2_ctx* c, const AdjArgs& s) {
     return G1G2_OK;
 }
 
+// The buffers of a gradient of nsteps steps in segments of `interval`, in place of
+// those of the last one.  After an error none are held.
+g1g2_status adj_alloc(g1g2_ctx* c, int64_t nsteps, int interval, bool mixed, bool keep) {
+    adj_free(c);
+    AdjState* const st = new (std::nothrow) AdjState();
+    if (!st) return set_error(c, G1G2_ENOMEM, "adjoint state");
+    c->adj = st;
+    const int ns = c->hub.hdesc[0].ns;
+    const auto fill = [&]() -> g1g2_status {
+        g1g2_status s;
+        st->ckpt.resize((nsteps + interval - 1) / interval + 1);   // last slot keeps the final state
+        for (auto& r : st->ckpt)
+            if ((s = alloc_reg(c, r)) != G1G2_OK) return s;
+        for (auto* v : {&st->seg, &st->seg2, &st->seg3, &st->seg4}) {
+            v->resize(interval);
+            for (auto& r : *v)
+                if ((s = alloc_reg(c, r, mixed && v != &st->seg)) != G1G2_OK) return s;
+        }
+        for (Regs* r : {&st->LAM, &st->LACC, &st->CA, &st->CB})
+            if ((s = alloc_reg(c, *r)) != G1G2_OK) return s;
+        HIP_OK(c, hipMalloc(&st->red, (size_t)R_N * ns * ns * sizeof(cd)));
+        st->pairs_per_part = ADJ_PAIRS_PER_PART;
+        st->nparts = (ns * ns + ADJ_PAIRS_PER_PART - 1) / ADJ_PAIRS_PER_PART;
+        HIP_OK(c, hipMalloc(&st->part, (size_t)st->nparts * ns * ns * 2 * sizeof(cd)));
+        HIP_OK(c, hipMalloc(&st->spart, (size_t)8 * ns * ns * ns * sizeof(cd)));
+        HIP_OK(c, hipMalloc(&st->ebar, (size_t)2 * ns * sizeof(cd)));
+        HIP_OK(c, hipMalloc(&st->gpart, (size_t)(2 + (2 * ns * ns + 255) / 256) * sizeof(double)));
+        HIP_OK(c, hipMalloc(&st->grads, (size_t)4 * nsteps * 2 * sizeof(double)));
+        HIP_OK(c, hipMalloc(&st->dev_ab, (size_t)(2 * ns + 8) * sizeof(double)));
+        return G1G2_OK;
+    };
+    const g1g2_status s = fill();
+    if (s != G1G2_OK) {
+        (void)hipGetLastError();   // reported here, not by a later launch check
+        adj_free(c);
+        return s;
+    }
+    st->have_steps = nsteps;
+    st->have_interval = interval;
+    st->have_n1 = c->n1;
+    st->have_n2 = c->n2;
+    st->have_bytes = (2 * st->ckpt.size() + (size_t)interval * (mixed ? 5 : 8) + 8) * c->n2 * (sizeof(cd) / 2);
+    st->have_mixed = mixed;
+    st->have_keep = keep;
+    return G1G2_OK;
+}
+
 g1g2_status stage_fwd(g1g2_ctx* c, int mode, double t, const Regs& in, const Regs& y, const Regs& acc,
                       const Regs& out, double cb, double cc) {
     return hub_stage(c, mode, t, in, y, acc, out, cb, cc);
@@ -674,6 +724,16 @@ void adj_free(g1g2_ctx* c) {
 
 extern "C" {
 
+// Whether a run of nsteps steps keeps its states (ADJ_KEEP_STATES), given the size of
+// a G2 register and the device's free and total memory.  Not part of the ABI; host
+// arithmetic with a name that tests can find.
+int adj_keeps_states(int64_t nsteps, size_t state_bytes, size_t free_bytes, size_t total_bytes) {
+    if (nsteps < 1 || nsteps > ADJ_KEEP_STATES / 4) return 0;
+    const size_t kept = 4 * (size_t)nsteps * state_bytes;
+    const size_t all = kept + 6 * state_bytes;   // two checkpoints, four cotangents
+    return kept <= total_bytes / 8 && all <= free_bytes / 4;
+}
+
 g1g2_status g1g2_forward_checkpointed(g1g2_ctx* c, double dt, int64_t nsteps, int32_t interval) {
     if (!c || nsteps < 1 || !(dt > 0.0)) return G1G2_EINVAL;
     if (c->d.basis != G1G2_HUBBARD || c->d.selfenergy != G1G2_SOA || c->hub.ncl != 1)
@@ -685,60 +745,37 @@ g1g2_status g1g2_forward_checkpointed(g1g2_ctx* c, double dt, int64_t nsteps, in
     // default: the interval that minimizes checkpoints + four states per segment step
     const int def = std::max<int>(1, (int)std::ceil(std::sqrt((double)nsteps / 4.0)));
     const int group = interval > 0 ? interval : def;   // steps between divergence checks
-    size_t mtotal = 0;
-    HIP_OK(c, hipDeviceTotalMem(&mtotal, c->device));
-    const bool keep = interval <= 0 && hub_tile_ok(c) && 4 * nsteps <= ADJ_KEEP_STATES &&
-                      4 * (size_t)nsteps * c->n2 * sizeof(cd) <= mtotal / 8;
-    const int seglen = keep ? (int)nsteps : group;
-    AdjState* st = adj_of(c);
     // the buffers of the last gradient serve again while its shape stays (allocating
     // and releasing the 8x8 cluster's 56 states took 9 ms of a 77 ms gradient)
-    const bool reuse = st && st->have_steps == nsteps && st->have_interval == seglen && st->have_n1 == c->n1 &&
-                       st->have_n2 == c->n2 && st->have_mixed == mixed && st->have_keep == keep;
+    const auto same = [&](bool kept) {
+        const AdjState* a = adj_of(c);
+        return a && a->have_steps == nsteps && a->have_interval == (kept ? (int)nsteps : group) &&
+               a->have_n1 == c->n1 && a->have_n2 == c->n2 && a->have_mixed == mixed && a->have_keep == kept;
+    };
     g1g2_status s;
-    if (!reuse) {
-        adj_free(c);
-        st = new (std::nothrow) AdjState();
-        if (!st) return set_error(c, G1G2_ENOMEM, "adjoint state");
-        c->adj = st;
+    bool keep = interval <= 0 && hub_tile_ok(c) && nsteps <= ADJ_KEEP_STATES / 4;
+    if (keep && !same(true)) {
+        size_t mfree = 0, mtotal = 0;
+        HIP_OK(c, hipMemGetInfo(&mfree, &mtotal));
+        const size_t held = adj_of(c) ? adj_of(c)->have_bytes : 0;
+        keep = adj_keeps_states(nsteps, c->n2 * sizeof(cd), mfree + held, mtotal) != 0;
+        if (keep && (s = adj_alloc(c, nsteps, (int)nsteps, mixed, true)) != G1G2_OK) {
+            if (s != G1G2_ENOMEM) return s;
+            keep = false;   // checkpoints need less
+            c->err.clear();
+        }
     }
+    if (!keep && !same(false) && (s = adj_alloc(c, nsteps, group, mixed, false)) != G1G2_OK) return s;
+    AdjState* const st = adj_of(c);
     st->ready = false;
     st->nsteps = nsteps;
     st->mixed = mixed;
     st->keep = keep;
     st->herm = c->herm;
-    st->interval = seglen;
+    st->interval = keep ? (int)nsteps : group;
     st->dt = dt;
     st->t0 = c->t;
     st->nck = (int)((nsteps + st->interval - 1) / st->interval);
-    if (!reuse) {
-        st->ckpt.resize(st->nck + 1);       // last slot keeps the final state
-        for (auto& r : st->ckpt)
-            if ((s = alloc_reg(c, r)) != G1G2_OK) return s;
-        for (auto* v : {&st->seg, &st->seg2, &st->seg3, &st->seg4}) {
-            v->resize(st->interval);
-            for (auto& r : *v)
-                if ((s = alloc_reg(c, r, st->mixed && v != &st->seg)) != G1G2_OK) return s;
-        }
-        for (Regs* r : {&st->LAM, &st->LACC, &st->CA, &st->CB})
-            if ((s = alloc_reg(c, *r)) != G1G2_OK) return s;
-        const int ns = c->hub.hdesc[0].ns;
-        HIP_OK(c, hipMalloc(&st->red, (size_t)R_N * ns * ns * sizeof(cd)));
-        st->pairs_per_part = ADJ_PAIRS_PER_PART;
-        st->nparts = (ns * ns + ADJ_PAIRS_PER_PART - 1) / ADJ_PAIRS_PER_PART;
-        HIP_OK(c, hipMalloc(&st->part, (size_t)st->nparts * ns * ns * 2 * sizeof(cd)));
-        HIP_OK(c, hipMalloc(&st->spart, (size_t)8 * ns * ns * ns * sizeof(cd)));
-        HIP_OK(c, hipMalloc(&st->ebar, (size_t)2 * ns * sizeof(cd)));
-        HIP_OK(c, hipMalloc(&st->gpart, (size_t)(2 + (2 * ns * ns + 255) / 256) * sizeof(double)));
-        HIP_OK(c, hipMalloc(&st->grads, (size_t)4 * nsteps * 2 * sizeof(double)));
-        HIP_OK(c, hipMalloc(&st->dev_ab, (size_t)(2 * ns + 8) * sizeof(double)));
-        st->have_steps = nsteps;
-        st->have_interval = seglen;
-        st->have_n1 = c->n1;
-        st->have_n2 = c->n2;
-        st->have_mixed = mixed;
-        st->have_keep = keep;
-    }
     const int ns = c->hub.hdesc[0].ns;
     HIP_OK(c, hipMemsetAsync(st->red, 0, (size_t)R_N * ns * ns * sizeof(cd), c->stream));
     if (keep) {

@@ -272,3 +272,4 @@ g1g2_status jel_observables(g1g2_ctx* c, const Regs& s, g1g2_obs* o);
 
 // ---- adjoint (adjoint.hip)
 void adj_free(g1g2_ctx* c);
+extern "C" int adj_keeps_states(int64_t nsteps, size_t state_bytes, size_t free_bytes, size_t total_bytes);
