@@ -19,8 +19,8 @@
  *                                      G2 = G2^{up down up down}: [nb]^4
  * States obey eq:Gsymm_b, G2_ijkl = conj(G2_klij), and G^< is anti-Hermitian; the
  * general basis relies on it.  Large Hubbard clusters evaluate one triangle of a
- * state that has the symmetry (to 2^-44, checked when it is set) and every
- * element of one that has not.
+ * state that has the symmetry (G2 bit for bit, G^< to 2^-51 of its largest element,
+ * checked when it is set; steps keep it so) and every element of one that has not.
  *
  * Pointers are host memory unless G1G2_PTR_DEVICE is set in desc.flags (then
  * they are device pointers on the current HIP device, e.g. torch data_ptr()).

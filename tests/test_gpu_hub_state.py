@@ -9,7 +9,7 @@ import numpy as np
 import pytest
 import torch
 
-from workloads import chain_hopping, random_g2, random_gless, rng
+from workloads import chain_hopping, random_g2, random_gless, rng, square_hopping
 
 pytestmark = pytest.mark.gpu
 
@@ -153,3 +153,55 @@ def test_adjoint_after_a_forward_pass_that_failed(lib, ns, interval):
         assert e.value.status == B.ESTATE
     p.close()
     assert out[0] == out[1]
+
+
+@pytest.mark.parametrize("size", [2.0 ** -46, 2.0 ** -51])
+def test_slightly_asymmetric_state_is_evolved_in_full(lib, size):
+    """An asymmetry of G2, however small, is part of the state: every element is
+    evaluated, bit for bit as by the slice kernel."""
+    from paper_2002_12717_amd import binding as B
+    r = rng(605)
+    h0, g1 = _system(r)
+    sym, _ = _states(r)
+    g2 = sym.copy()
+    g2[3, 4, 5, 6] += size * np.abs(sym).max()
+    out = []
+    for flags in (0, B.HUB_SLICE_KERNEL):
+        p = B.Propagator(B.HUBBARD, B.SOA, NS, h0, g1, U=1.1, flags=flags)
+        p.set_state(g1, g2)
+        p.step(0.01, 2)
+        out.append(p.get_state())
+        p.close()
+    _equal(*out)
+
+
+@pytest.mark.parametrize("lx,ly,se", [(33, 1, "soa"), (33, 1, "tpp"), (33, 1, "tph"), (9, 5, "soa"), (5, 5, "gw"),
+                                      (9, 5, "dsl")])
+@pytest.mark.parametrize("prec", ["fp64", "mixed"])
+def test_steps_keep_the_symmetry_bit_for_bit(lib, lx, ly, se, prec):
+    """A symmetric state stays so to the last bit, so that a context restarted from a
+    saved state goes on exactly as the one that saved it."""
+    from paper_2002_12717_amd import binding as B
+    r = rng(606, lx, ly, len(se))
+    ns, nch = lx * ly, 3 if se in ("gw", "dsl") else 1
+    h = square_hopping(lx, ly, periodic=False) if ly > 1 else chain_hopping(lx)
+    h0 = np.stack([h + np.diag(r.uniform(-0.5, 0.5, ns)), 0.8 * h]).astype(complex)
+    g1 = np.stack([random_gless(ns, r), random_gless(ns, r)])
+    g2 = np.stack([random_g2(ns, r, scale=0.05, exchange=False) for _ in range(nch)])
+    g2 = g2 if nch == 3 else g2[0]
+    code = {"soa": B.SOA, "tpp": B.TPP, "tph": B.TPH, "gw": B.GW, "dsl": B.DSL}[se]
+    kw = dict(U=1.3, precision=B.FP64 if prec == "fp64" else B.MIXED)
+    p = B.Propagator(B.HUBBARD, code, ns, h0, g1, **kw)
+    p.set_state(g1, g2)
+    p.step(0.01, 7)
+    s1, s2, _ = p.get_state()
+    m = s2.reshape(nch, ns * ns, ns * ns)
+    kept = [bool(np.array_equal(s1, -s1.conj().transpose(0, 2, 1))), bool(np.array_equal(m, m.conj().transpose(0, 2, 1)))]
+    assert kept == [True, True]
+    q = B.Propagator(B.HUBBARD, code, ns, h0, s1, G2_0=s2, **kw)
+    p.step(0.01, 3)
+    q.step(0.01, 3)
+    a, b = p.get_state(), q.get_state()
+    p.close()
+    q.close()
+    _equal(a, b)
