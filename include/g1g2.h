@@ -100,8 +100,9 @@ enum {
      * hold at least 2^20 G2 elements in all (counting GW's three channels),
      * else the row kernel (one wave per G2 row).  Both need ns <= 64 and at
      * most 4 neighbours per site, else the per-element kernel runs.  Steps of
-     * systems of that size with real hoppings and a Hermitian state compute one
-     * triangle of the pair matrix instead; either flag turns that off. */
+     * systems of that size with real, symmetric hoppings and a Hermitian state
+     * compute one triangle of the pair matrix instead; either flag turns that
+     * off. */
     G1G2_HUB_ROW_KERNEL = 4,    /* Hubbard: row kernel whatever the size          */
     G1G2_HUB_SLICE_KERNEL = 8,  /* Hubbard: slice kernel whatever the size        */
     /* General-basis DSL: build the polarization and particle-hole

@@ -26,8 +26,8 @@
 //
 // Condition: state with the symmetry to the last bit (checked when a state is set,
 // hub_check_state: an asymmetry, however small, is evolved by the kernels that
-// evaluate every element), real
-// hoppings, ns <= 64, at most Z_MAX_ROW neighbours per site.
+// evaluate every element), real hoppings that are equal in both directions,
+// ns <= 64, at most Z_MAX_ROW neighbours per site.
 #include <algorithm>
 #include <type_traits>
 #include <vector>

@@ -1429,6 +1429,7 @@ g1g2_status hub_setup(g1g2_ctx* c, int ncl, const int* nsv, const double* Uv, co
     std::vector<WorkItem> work, g1work, dwork;
     std::vector<long long> wcost;   // elements of each G2 work item
     bool realhop = true;            // every hopping of every cluster is real
+    bool symhop = true;             // h_ij and h_ji agree bit for bit (the Hermitian check allows 1e-12)
     std::vector<int> chunks(ncl);
     bool rowk = true;
     for (int cl = 0; cl < ncl; ++cl) {
@@ -1480,6 +1481,7 @@ g1g2_status hub_setup(g1g2_ctx* c, int ncl, const int* nsv, const double* Uv, co
                         rows[s * ns + i].push_back({j, v});
                         if (v.y != 0.0) realhop = false;
                     }
+                    if (v.x != vt.x) symhop = false;
                 }
         int zmax = 1;
         for (auto& r : rows) zmax = std::max<int>(zmax, (int)r.size());
@@ -1583,10 +1585,10 @@ g1g2_status hub_setup(g1g2_ctx* c, int ncl, const int* nsv, const double* Uv, co
     g1g2_status s;
     if ((s = upload(c, &H.desc, desc)) != G1G2_OK) return s;
     // steps over one triangle of the pair matrix, at the sizes that take whole slices
-    // by default
+    // by default; the transposed block is the conjugate only for symmetric hoppings
     std::vector<int> tiles;
     std::vector<WorkItem> twork;
-    const bool tile = slicek && !small1 && realhop && !(fl & G1G2_HUB_SLICE_KERNEL);
+    const bool tile = slicek && !small1 && realhop && symhop && !(fl & G1G2_HUB_SLICE_KERNEL);
     if (tile) {
         std::vector<int> per(ncl, SLICE_ELEMS);
         if (chunk_in)

@@ -205,3 +205,21 @@ def test_steps_keep_the_symmetry_bit_for_bit(lib, lx, ly, se, prec):
     p.close()
     q.close()
     _equal(a, b)
+
+
+def test_unequal_hoppings_are_evolved_in_full(lib):
+    """h0 passes as Hermitian to 1e-12; hoppings h_ij and h_ji that differ within that
+    take the slice kernel, which reads both."""
+    from paper_2002_12717_amd import binding as B
+    r = rng(607)
+    h0, g1 = _system(r)
+    sym, _ = _states(r)
+    h0[0, 3, 4] += 5e-13
+    h0[1, 7, 20] = 4e-13                       # h_ji = 0: a neighbour in one direction only
+    out = []
+    for flags in (0, B.HUB_SLICE_KERNEL):
+        p = B.Propagator(B.HUBBARD, B.SOA, NS, h0, g1, U=1.1, G2_0=sym, flags=flags)
+        p.step(0.01, 2)
+        out.append(p.get_state())
+        p.close()
+    _equal(*out)
