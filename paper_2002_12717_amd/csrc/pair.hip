@@ -29,10 +29,14 @@
 //
 // TPH and TPP also rest on the exchange symmetry of G2 (eq:Gsymm_a).  G2 is
 // split into its exchange-even and -odd parts; where the odd part exceeds
-// 2^-44 of the largest element (a state that lacks the symmetry; propagation
-// keeps it to rounding), its product is formed too.  gen_xop measures both on
-// the device and the later kernels of the stage read the result, so no
-// synchronization is involved.
+// Nb 2^-54 of the largest element (a state that lacks the symmetry), its product is
+// formed too.  Below that bound it is under the rounding of the even product: sums
+// of Nb^2 terms of size t round to about 0.4 Nb^2 2^-53 t, and an odd part of that
+// size contributes Nb 2^-54 Nb t.  Propagation keeps the symmetry to rounding: the odd
+// part reaches 0.5 to 4.5 2^-53 after one step and 1 to 10 after 64 (3 to 64 orbitals,
+// bounds 1.5 to 32), so that a long run may cross the bound and then costs the second
+// product.  gen_xop measures both on the device and the later kernels of the stage
+// read the result, so no synchronization is involved.
 #include <algorithm>
 #include <cmath>
 #include <type_traits>
@@ -54,7 +58,7 @@ struct PairTab {
 __device__ __forceinline__ bool has_odd(const PairTab& tab) {
     const double o = __longlong_as_double((long long)tab.stat[0]);
     const double g = __longlong_as_double((long long)tab.stat[1]);
-    return !(o <= 0x1p-44 * g);
+    return !(o <= tab.nb * 0x1p-54 * g);
 }
 
 template <typename T>
