@@ -522,6 +522,17 @@ void launch_tile_se(g1g2_ctx* c, const StageArgs& s, const TileArgs& t) {
 
 }  // namespace
 
+// Tiles of a work item of a cluster of ns sites that holds at most `most` elements: no
+// more than the cluster has, since the launch takes the LDS of its largest item for
+// all (a two-site cluster has three tiles, and room for 192 of them, 61 KB, took
+// every work-group of its batch from four per compute unit to two).  Host
+// arithmetic with a name that tests can find.
+extern "C" int hub_tile_per_item(int ns, int most) {
+    if (ns >= TILE_ROW_MIN) return 1;
+    const int fit = std::min(std::min(most, TILE_ELEMS) / (ns * ns), TILE_VEC / ns);
+    return std::max(1, std::min(fit, ns * (ns + 1) / 2));
+}
+
 // Tiles and work items of every cluster.  nbr: the host neighbour tables;
 // per_item: the most G2 elements of an item per cluster.
 void hub_tile_lists(g1g2_ctx* c, const std::vector<ClusterDesc>& desc, const std::vector<int>& nbr,
@@ -550,7 +561,7 @@ void hub_tile_lists(g1g2_ctx* c, const std::vector<ClusterDesc>& desc, const std
                         hi[q] = std::max(hi[q], nb[q * z + u]);
                     }
             }
-            const int per = ns >= TILE_ROW_MIN ? 1 : std::max(1, std::min(std::min(per_item[cl], TILE_ELEMS) / (ns * ns), TILE_VEC / ns));
+            const int per = hub_tile_per_item(ns, per_item[cl]);
             const size_t first = tiles.size();
             for (int i = 0; i < ns; ++i)
                 for (int k = 0; k <= i; ++k)
