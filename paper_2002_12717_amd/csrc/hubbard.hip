@@ -984,8 +984,18 @@ __global__ __launch_bounds__(PERSIST_THREADS) void hub_persistent_kernel(Persist
 // of every neighbour, Z slots per index, and the indices into G1.  What is left
 // per stage are the loads of the state, two fused update lines and one barrier
 // (the diagonal of h^HF is formed from G1 by each thread, and G1 runs beside G2
-// instead of after it).  ns <= 5 takes PER = 1; ns = 6 takes PER = 2 for chains (Z = 2),
-// whose neighbours still fit the registers.  Buffers as in
+// instead of after it).  ns <= 5 takes PER = 1, ns = 6 PER = 2.  Only PER = 1 with Z = 2
+// fits the registers whole; the other forms spill slots that a stage reads back, PER = 2
+// with Z = 4 most (250 to 430 bytes per lane).  200 steps, binary64 / mixed, here against
+// hub_persistent_kernel, in us:
+//   5 sites, chain (Z = 2): SOA 641 / 622, 1854 / 1908; TPH 788 / 765, 1999 / 2058
+//   5 sites, star  (Z = 4): SOA 858 / 966, 2809 / 2866; TPH 1040 / 1121, 2944 / 3025
+//   6 sites, chain (Z = 2): SOA 1304 / 1527, 2876 / 2953; TPH 1678 / 1960, 3160 / 3227
+//   6 sites, 2x3, 3 neighbours (Z = 4): SOA 3484 / 3135, 3667 / 3743;
+//     TPP 3720 / 3877, 3975 / 4036; TPH 4575 / 3888, 3930 / 3996
+//   6 sites, 4 neighbours: SOA 3458 / 3123, 4454 / 4550; TPH 4572 / 3901, 4770 / 4880
+// so that binary64 TPH with 6 sites and 3 neighbours stays with hub_persistent_kernel,
+// whose time follows the neighbours.  Buffers as in
 // hub_persistent_kernel: binary64 alternates between two, mixed precision keeps y
 // in the first and two binary32 stage copies in the second.
 // threads: ns^4 / PER + 2 ns^2 in whole waves, at most three waves per SIMD
@@ -1655,7 +1665,7 @@ void launch_persistent_t(g1g2_ctx* c, const PersistArgs& p) {
     if (H.realhop && ns <= 5 && z <= 2) small(one(), two());
     else if (H.realhop && ns <= 5 && z <= 4) small(one(), four());
     else if (H.realhop && ns <= 6 && z <= 2) small(two(), two());
-    else if (H.realhop && ns <= 6 && z <= 4) small(two(), four());
+    else if (H.realhop && ns <= 6 && z <= 4 && !(SE == SE_TPH && !MIXED && z == 3)) small(two(), four());
     else if (H.realhop)
         hipLaunchKernelGGL((hub_persistent_kernel<SE, MIXED, true>), dim3(1), dim3(PERSIST_THREADS), 0, c->stream, p);
     else
