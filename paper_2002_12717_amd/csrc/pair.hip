@@ -544,8 +544,8 @@ __global__ __launch_bounds__(256, 2) void gen_pair_gemm_kernel(const T* __restri
 
 // --------------------------------------------------------------------------- TPP
 // Lambda of one exchange sector of the left pair, A^T B with A = h[K][rows] and
-// B = G2[K][cols], complex, 64x64 tiles, four waves of 32x32, K staged in slices
-// of 16.  A complex multiply-add takes three real products,
+// B = G2[K][cols], complex.  Products that give every compute unit a 64x64 tile:
+// four waves of 32x32, K staged in slices of 16.  A complex multiply-add takes three real products,
 //   Re = Ar Br - Ai Bi,  Im = (Ar + Ai)(Br + Bi) - Ar Br - Ai Bi,
 // the operand sums formed in registers.  Slices are kept as interleaved complex
 // values, so an operand pair is one LDS access; two work-groups per compute unit.
@@ -555,14 +555,12 @@ __global__ __launch_bounds__(256, 2) void gen_pair_gemm_kernel(const T* __restri
 // sectors coincide, so each is a launch of its own.  Where G2 has an
 // exchange-odd part, the tile's product with it (whose columns lie in the other
 // sector) follows in the same work-group.
-template <typename T, int W, bool ODD>
+template <typename T, bool ODD>
 __device__ __forceinline__ void pp_tile(const typename V2<T>::type* __restrict__ A,
                                     const typename V2<T>::type* __restrict__ B, cd* __restrict__ D,
                                     const PairTab& tab, bool even, int nr, int lds, int lda,
-                                    typename V2<T>::type (*a_c)[32 * W + 1],
-                                        typename V2<T>::type (*b_c)[32 * W + 1]) {
-    typedef typename V2<T>::type CT;
-    constexpr int TILE = 32 * W, KS = 16, PER = TILE * KS / 256;
+                                    typename V2<T>::type (*a_c)[65], typename V2<T>::type (*b_c)[65]) {
+    constexpr int W = 2, TILE = 32 * W, KS = 16, PER = TILE * KS / 256;
     const int ns = tab.nt + tab.nb;
     const int ldr = even ? lds : lda;                  // rows and K of this sector
     const int kend = ((even ? ns : tab.nt) + KS - 1) / KS * KS;
@@ -703,14 +701,131 @@ __device__ __forceinline__ void pp_tile(const typename V2<T>::type* __restrict__
         }
 }
 
-template <typename T, int W>
+template <typename T>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2)))
 void gen_gemm_kernel(const typename V2<T>::type* __restrict__ A, const typename V2<T>::type* __restrict__ B,
                      const typename V2<T>::type* __restrict__ Bodd, cd* __restrict__ D, PairTab tab, bool even,
                      int nr, int lds, int lda) {
-    __shared__ typename V2<T>::type a_c[16][32 * W + 1], b_c[16][32 * W + 1];
-    pp_tile<T, W, false>(A, B, D, tab, even, nr, lds, lda, a_c, b_c);
-    if (has_odd(tab)) pp_tile<T, W, true>(A, Bodd, D, tab, even, nr, lds, lda, a_c, b_c);
+    __shared__ typename V2<T>::type a_c[16][65], b_c[16][65];
+    pp_tile<T, false>(A, B, D, tab, even, nr, lds, lda, a_c, b_c);
+    if (has_odd(tab)) pp_tile<T, true>(A, Bodd, D, tab, even, nr, lds, lda, a_c, b_c);
+}
+
+// Smaller products: 32x32 tiles of the pairs (t, t'), all four products of a tile at
+// once.  The even and the odd sector number their pairs p < q alike, so that a tile
+// of one and the same tile of the other share their exchange images in D, and one
+// work-group owns them: group g of four waves takes the product g of
+//   0: even rows, even columns   1: odd, odd   2: even, odd   3: odd, even
+// (2 and 3 where G2 has an exchange-odd part), the results meet in LDS, and a thread
+// adds one element's combinations into its four images.  Such a product is bound by the
+// chain of its K slices on few compute units, so the products of a tile run beside
+// each other.  Per stage, in us, against a launch per sector whose work-groups take
+// the odd product after the even one: 16 orbitals 19 (30 there) in binary64, 26 (49) with
+// the odd part, 21 (44) in mixed precision, which always has one; 32 orbitals 78 (84),
+// 127 (154) and 87 (115).  64 registers and 67 KB of LDS (slices of 8 in binary64, 16 in
+// binary32, two buffers) leave two work-groups per compute unit: at 32 orbitals there are
+// 289; one per compute unit took 86, 138 and 99 us.
+template <typename T>
+struct PpSmall {
+    typedef typename V2<T>::type CT;
+    const CT *hs, *ha;            // h^pp [lds][lds], [lda][lda]
+    const CT *gs, *ga, *gso, *gao;   // G2 [lds][lds], [lda][lda], [lds][lda], [lda][lds]
+};
+
+template <typename T>
+__global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(8))) void gen_pp_small_kernel(PpSmall<T> s, cd* __restrict__ D, PairTab tab, int nr,
+                                                           int lds, int lda) {
+    typedef typename V2<T>::type CT;
+    typedef T CV __attribute__((ext_vector_type(2)));
+    constexpr bool F32 = sizeof(T) == 4;
+    constexpr int TILE = 32, KS = F32 ? 16 : 8, LD = TILE + 1, PER = TILE * KS / 256, BUF = 2;
+    // the slices of A and B per group, or the four results
+    constexpr int STAGE = 4 * BUF * 2 * KS * LD, EPI = 4 * TILE * LD * (int)(sizeof(cd) / sizeof(CT));
+    __shared__ __attribute__((aligned(16))) CT buf[STAGE > EPI ? STAGE : EPI];
+    const bool odd = has_odd(tab);
+    const int ns = tab.nt + tab.nb;
+    const int g = __builtin_amdgcn_readfirstlane(threadIdx.x >> 8), tid = threadIdx.x & 255;
+    const int wave = tid >> 6, lane = tid & 63, li = lane & 15, lk = lane >> 4;
+    const int wm = (wave >> 1) * 16, wn = (wave & 1) * 16;
+    int tr, tc;
+    tile_order(blockIdx.x, nr, nr, tr, tc);
+    const int bm = tr * TILE, bn = tc * TILE;
+    const bool reven = g == 0 || g == 2, ceven = g == 0 || g == 3;
+    const CT* const A = reven ? s.hs : s.ha;
+    const CT* const B = g == 0 ? s.gs : g == 1 ? s.ga : g == 2 ? s.gso : s.gao;
+    const int ldr = reven ? lds : lda, ldb = ceven ? lds : lda;
+    // odd sectors end at nt pairs; lda covers every tile that begins before that
+    const bool on = (reven || bm < tab.nt) && (ceven || bn < tab.nt) && (g < 2 || odd);
+    const int kend = on ? ((reven ? ns : tab.nt) + KS - 1) / KS * KS : 0, kall = (ns + KS - 1) / KS * KS;
+    typename MF<T>::acc p1 = MF<T>::zero(), p2 = MF<T>::zero(), p3 = MF<T>::zero();
+    double re[4] = {0, 0, 0, 0}, im[4] = {0, 0, 0, 0};
+    CV pa[PER], pb[PER];
+    auto fetch = [&](int k0) {
+#pragma unroll
+        for (int u = 0; u < PER; ++u) {
+            const int idx = tid + u * 256, k = idx / TILE, c = idx % TILE;
+            pa[u] = *(const CV*)(A + (size_t)(k0 + k) * ldr + bm + c);
+            pb[u] = *(const CV*)(B + (size_t)(k0 + k) * ldb + bn + c);
+        }
+    };
+    auto flush = [&]() {
+#pragma unroll
+        for (int r4 = 0; r4 < 4; ++r4) {
+            const double d1 = p1[r4], d2 = p2[r4], d3 = p3[r4];
+            re[r4] += d1 - d2;
+            im[r4] += d3 - d1 - d2;
+        }
+        p1 = p2 = p3 = MF<T>::zero();
+    };
+    if (kend > 0) fetch(0);
+    for (int k0 = 0; k0 < kall; k0 += KS) {
+        CT* const as = buf + (k0 / KS % BUF * 4 + g) * 2 * KS * LD;
+        CT* const bs = as + KS * LD;
+        if (k0 < kend)
+#pragma unroll
+            for (int u = 0; u < PER; ++u) {
+                const int idx = tid + u * 256;
+                *(CV*)(as + idx / TILE * LD + idx % TILE) = pa[u];
+                *(CV*)(bs + idx / TILE * LD + idx % TILE) = pb[u];
+            }
+        __syncthreads();
+        if (k0 + KS < kend) fetch(k0 + KS);
+        if (k0 < kend)
+#pragma unroll
+        for (int k4 = 0; k4 < KS; k4 += 4) {
+            const CV a = *(const CV*)(as + (k4 + lk) * LD + wm + li), b = *(const CV*)(bs + (k4 + lk) * LD + wn + li);
+            p1 = MF<T>::mac(a.x, b.x, p1);
+            p2 = MF<T>::mac(a.y, b.y, p2);
+            p3 = MF<T>::mac(a.x + a.y, b.x + b.y, p3);
+        }
+        if (F32 && (k0 + KS) % 64 == 0) flush();
+        if (BUF == 1) __syncthreads();
+    }
+    flush();
+    __syncthreads();
+    cd* const res = (cd*)buf;
+#pragma unroll
+    for (int r4 = 0; r4 < 4; ++r4)
+        res[(g * TILE + wm + tile_row<T>(r4)) * LD + wn + tile_col()] = cmk(re[r4], im[r4]);
+    __syncthreads();
+    const int r = threadIdx.x / TILE, c = threadIdx.x % TILE, row = bm + r, col = bn + c;
+    if (row >= ns || col >= ns) return;
+    int i, j, k, l;
+    pair_of(tab, row, i, j);
+    pair_of(tab, col, k, l);
+    const cd ee = res[r * LD + c], oo = res[(TILE + r) * LD + c];
+    const cd eo = res[(2 * TILE + r) * LD + c], oe = res[(3 * TILE + r) * LD + c];
+    const cd sp = cadd(ee, oo), sm = csub(ee, oo), op = cadd(eo, oe), om = csub(eo, oe);
+    const size_t n1 = tab.nbp;
+    const size_t x0 = ((i * n1 + j) * n1 + k) * n1 + l, x1 = ((j * n1 + i) * n1 + k) * n1 + l;
+    const size_t x2 = ((i * n1 + j) * n1 + l) * n1 + k, x3 = ((j * n1 + i) * n1 + l) * n1 + k;
+    const bool u1 = i != j, u2 = k != l;
+    const cd z = cmk(0.0, 0.0);
+    const cd d0 = D[x0], d1 = u1 ? D[x1] : z, d2 = u2 ? D[x2] : z, d3 = u1 && u2 ? D[x3] : z;
+    D[x0] = cadd(d0, cadd(sp, op));
+    if (u1) D[x1] = cadd(d1, cadd(sm, om));
+    if (u2) D[x2] = cadd(d2, csub(sm, om));
+    if (u1 && u2) D[x3] = cadd(d3, csub(sp, op));
 }
 
 // --------------------------------------------------------------------------- host side
@@ -804,22 +919,23 @@ g1g2_status pair_run(g1g2_ctx* c, const Regs& in, double ws) {
     g1g2_status s;
     if (gw && (s = product(std::integral_constant<int, K_GW>())) != G1G2_OK) return s;
     if (ph && (s = product(std::integral_constant<int, K_PH>())) != G1G2_OK) return s;
-    if (pp) {
-        auto sector = [&](auto w, bool even) -> g1g2_status {
-            constexpr int W = decltype(w)::value, E = 32 * W;
-            const int nr = tiles(even ? npair : nt, E), nc = g.plds / E;
-            hipLaunchKernelGGL((gen_gemm_kernel<T, W>), dim3(nr * nc), dim3(256), 0, c->stream,
+    if (pp && fills(npair, 64)) {
+        for (int even = 1; even >= 0; --even) {
+            const int nr = tiles(even ? npair : nt, 64), nc = g.plds / 64;
+            hipLaunchKernelGGL((gen_gemm_kernel<T>), dim3(nr * nc), dim3(256), 0, c->stream,
                                (const CT*)(even ? g.phs : g.pha), (const CT*)(even ? g.pgs : g.pga),
-                               (const CT*)(even ? g.pgso : g.pgao), D, tab, even, nr, g.plds, g.plda);
+                               (const CT*)(even ? g.pgso : g.pgao), D, tab, even != 0, nr, g.plds, g.plda);
             HIP_OK(c, hipGetLastError());
             prof_mark(c, "gen_gemm");
-            return G1G2_OK;
-        };
-        for (int even = 1; even >= (nt > 0 ? 0 : 1); --even) {
-            s = fills(npair, 64) ? sector(std::integral_constant<int, 2>(), even != 0)
-                                 : sector(std::integral_constant<int, 1>(), even != 0);
-            if (s != G1G2_OK) return s;
         }
+    } else if (pp) {
+        const int nr = tiles(npair, 32);
+        const PpSmall<T> ps{(const CT*)g.phs, (const CT*)g.pha,  (const CT*)g.pgs,
+                            (const CT*)g.pga, (const CT*)g.pgso, (const CT*)g.pgao};
+        hipLaunchKernelGGL((gen_pp_small_kernel<T>), dim3(nr * nr), dim3(1024), 0, c->stream, ps, D, tab, nr, g.plds,
+                           g.plda);
+        HIP_OK(c, hipGetLastError());
+        prof_mark(c, "gen_gemm");
     }
     return G1G2_OK;
 }
