@@ -57,10 +57,10 @@ struct HubbardData {
     std::vector<int> chunk;        // elements of G2 per work-group, per cluster
     // stages over one triangle of the pair matrix (hub_tile.hip); tiles null: not eligible
     int* tiles = nullptr;          // tile words of all clusters
-    WorkItem* twork = nullptr;     // work list over them
-    int ntwork = 0;
-    bool tile_row = false;         // one tile per item, a wave per row
-    std::vector<std::pair<int, int>> tile_shapes;   // (tiles per item, ns) of the items
+    WorkItem* twork = nullptr;     // work lists over them: the wave-per-row form's, then the packed form's
+    int ntrow = 0, ntpack = 0;     // items of either
+    int row_ns = 0;                // largest cluster of the wave-per-row form (one tile per item)
+    std::vector<std::pair<int, int>> tile_shapes;   // (tiles per item, ns) of the packed form's items
     unsigned long long* tsym = nullptr;   // result of the symmetry check
     int* nbr = nullptr;            // concatenated neighbour tables
     cd* hop = nullptr;

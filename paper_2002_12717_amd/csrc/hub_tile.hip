@@ -493,14 +493,17 @@ void launch_tile(g1g2_ctx* c, const StageArgs& s, const TileArgs& t) {
         hipLaunchKernelGGL((hub_tdiag_kernel<TI, SE>), dim3(H.ndwork), dim3(256), 0, c->stream, H.desc, H.dwork, s.in2,
                            const_cast<cd*>(t.diag));
     }
-    size_t lds = 0;
-    for (const auto& x : H.tile_shapes) lds = std::max(lds, tile_lds<MODE, SE, MIXED>(x.first, x.second));
-    if (H.tile_row)
-        hipLaunchKernelGGL((hub_tile_kernel<MODE, SE, MIXED, true>), dim3(H.ntwork), dim3(tile_threads(SE, true)), lds, c->stream,
-                           s, t);
-    else
-        hipLaunchKernelGGL((hub_tile_kernel<MODE, SE, MIXED, false>), dim3(H.ntwork),
-                           dim3(tile_threads(SE, false)), lds, c->stream, s, t);
+    if (H.ntrow > 0)
+        hipLaunchKernelGGL((hub_tile_kernel<MODE, SE, MIXED, true>), dim3(H.ntrow), dim3(tile_threads(SE, true)),
+                           (tile_lds<MODE, SE, MIXED>(1, H.row_ns)), c->stream, s, t);
+    if (H.ntpack > 0) {
+        size_t lds = 0;
+        for (const auto& x : H.tile_shapes) lds = std::max(lds, tile_lds<MODE, SE, MIXED>(x.first, x.second));
+        StageArgs sp = s;
+        sp.work += H.ntrow;
+        hipLaunchKernelGGL((hub_tile_kernel<MODE, SE, MIXED, false>), dim3(H.ntpack), dim3(tile_threads(SE, false)), lds,
+                           c->stream, sp, t);
+    }
 }
 
 template <int MODE, int SE>
@@ -540,14 +543,14 @@ void hub_tile_lists(g1g2_ctx* c, const std::vector<ClusterDesc>& desc, const std
     HubbardData& H = c->hub;
     const int sel = c->d.selfenergy;
     const int nch = sel == G1G2_GW || sel == G1G2_DSL ? 3 : 1;
-    std::vector<WorkItem> g1;
-    std::vector<long long> cost;
+    std::vector<WorkItem> items[2], g1[2];   // wave-per-row form, packed form
+    std::vector<long long> cost[2];
     H.tile_shapes.clear();
-    H.tile_row = true;
+    H.row_ns = 0;
     for (int cl = 0; cl < (int)desc.size(); ++cl) {
         const ClusterDesc& d = desc[cl];
-        const int ns = d.ns, z = d.zmax;
-        H.tile_row = H.tile_row && ns >= TILE_ROW_MIN;
+        const int ns = d.ns, z = d.zmax, form = ns >= TILE_ROW_MIN ? 0 : 1;
+        if (form == 0) H.row_ns = std::max(H.row_ns, ns);
         for (int ch = 0; ch < nch; ++ch) {
             // block (b,a) of the upper triangle, b < a, is read by a stage when it neighbours
             // an evaluated block: some neighbour of b is >= a, or one of a is <= b
@@ -568,19 +571,22 @@ void hub_tile_lists(g1g2_ctx* c, const std::vector<ClusterDesc>& desc, const std
                     tiles.push_back(i | k << 8 | ch << 16 | (hi[k] >= i || lo[i] <= k ? TW_NEED : 0));
             for (size_t t0 = first; t0 < tiles.size(); t0 += per) {
                 const size_t t1 = std::min(tiles.size(), t0 + per);
-                work.push_back({cl, (int)t0, (int)t1});
-                cost.push_back((long long)(t1 - t0) * ns * ns);
+                items[form].push_back({cl, (int)t0, (int)t1});
+                cost[form].push_back((long long)(t1 - t0) * ns * ns);
             }
             const std::pair<int, int> shape(per, ns);
-            if (std::find(H.tile_shapes.begin(), H.tile_shapes.end(), shape) == H.tile_shapes.end())
+            if (form == 1 && std::find(H.tile_shapes.begin(), H.tile_shapes.end(), shape) == H.tile_shapes.end())
                 H.tile_shapes.push_back(shape);
         }
-        g1.push_back({cl, -1, -1});
+        g1[form].push_back({cl, -1, -1});
     }
     // contiguous ranges per XCD: a block's i- and k-neighbours lie mostly in its range
     // (8x8 SOA 207 us; round-robin 222, ranges of 8x8 patches of blocks 214)
-    work = xcd_order(work, cost, g1);
-    H.ntwork = (int)work.size();
+    work = xcd_order(items[0], cost[0], g1[0]);
+    const std::vector<WorkItem> packed = xcd_order(items[1], cost[1], g1[1]);
+    H.ntrow = (int)work.size();
+    H.ntpack = (int)packed.size();
+    work.insert(work.end(), packed.begin(), packed.end());
 }
 
 int hub_tile_diags(const g1g2_ctx* c) {
@@ -604,7 +610,7 @@ g1g2_status hub_check_state(g1g2_ctx* c) {
     StageArgs s = hub_make_stage(c, 0.0, c->y, c->y, c->y, c->y, 0.0, 0.0);
     s.work = H.twork;
     HIP_OK(c, hipMemsetAsync(H.tsym, 0, 4 * sizeof(unsigned long long), c->stream));
-    hipLaunchKernelGGL(hub_herm_kernel, dim3(H.ntwork), dim3(256), 0, c->stream, s, H.tiles, H.tsym);
+    hipLaunchKernelGGL(hub_herm_kernel, dim3(H.ntrow + H.ntpack), dim3(256), 0, c->stream, s, H.tiles, H.tsym);
     HIP_OK(c, hipGetLastError());
     double r[4];
     HIP_OK(c, hipMemcpyAsync(r, H.tsym, sizeof(r), hipMemcpyDeviceToHost, c->stream));

@@ -1399,7 +1399,9 @@ std::vector<WorkItem> xcd_order(const std::vector<WorkItem>& g2, const std::vect
     long long total = 0;
     for (long long v : cost) total += v;
     std::vector<std::vector<WorkItem>> grp(NX), g2grp(NX);
-    std::vector<int> first_group(g1.size(), -1);
+    int ncl = 0;
+    for (const WorkItem& w : g1) ncl = std::max(ncl, w.cluster + 1);
+    std::vector<int> first_group(ncl, -1);
     long long prefix = 0;
     for (size_t q = 0; q < g2.size(); ++q) {
         const long long mid2 = 2 * prefix + cost[q];   // twice the item's midpoint
@@ -1408,7 +1410,7 @@ std::vector<WorkItem> xcd_order(const std::vector<WorkItem>& g2, const std::vect
         g2grp[x].push_back(g2[q]);
         if (first_group[g2[q].cluster] < 0) first_group[g2[q].cluster] = x;
     }
-    for (size_t cl = 0; cl < g1.size(); ++cl) grp[std::max(first_group[cl], 0)].push_back(g1[cl]);
+    for (const WorkItem& w : g1) grp[std::max(first_group[w.cluster], 0)].push_back(w);
     size_t m = 0;
     for (int x = 0; x < NX; ++x) {
         grp[x].insert(grp[x].end(), g2grp[x].begin(), g2grp[x].end());

@@ -166,3 +166,28 @@ def test_gradient_with_kept_states(lib, prec):
         assert u[0] == v[0] and u[2] == v[2] and np.array_equal(u[1], v[1])
         assert np.array_equal(u[3], v[3]) and np.array_equal(u[4], v[4])
     assert out[0][0][0] == out[0][1][0] and np.array_equal(out[0][0][1], out[0][1][1])
+
+
+@pytest.mark.parametrize("shapes", [[(3, 3), (9, 5), (33, 1)], [(9, 5), (2, 1), (11, 4)]])
+@pytest.mark.parametrize("se,prec", [("soa", "fp64"), ("soa", "mixed"), ("tpp", "fp64"), ("dsl", "fp64")])
+def test_tile_batch_of_both_forms(lib, shapes, se, prec):
+    """Clusters of the wave-per-row form (44 sites and more) and of the packed form in one
+    batch, either of them first: a launch of each form per stage."""
+    from paper_2002_12717_amd import binding as B
+    say(f"[tile batch, both forms] {shapes} {se} {prec}")
+    r = rng(515, len(se), shapes[0][0])
+    cl = [_system(a, b, b > 2, r) for a, b in shapes]
+    U = [0.7 + 0.2 * q for q in range(len(cl))]
+    b = B.Batch(_code(se), [c[0] for c in cl], U, [c[1] for c in cl], [c[2] for c in cl],
+                precision=B.FP64 if prec == "fp64" else B.MIXED)
+    b.step(0.02, 2)
+    assert [o["step"] for o in b.observables()] == [2] * len(cl)
+    worst = 0.0
+    for q, (ns, h0, g1) in enumerate(cl):
+        nch = 3 if se == "dsl" else 1
+        r1, r2 = _oracle(h0, U[q], se, g1, np.zeros((nch,) + (ns,) * 4, complex), 0.02, 2)
+        G1, G2 = b.get_cluster(q)
+        worst = max(worst, rel(G1, r1), rel(G2, r2 if nch == 3 else r2[0]))
+    b.close()
+    say(f"   worst rel err {worst:.2e}")
+    assert worst < (1e-10 if prec == "fp64" else 1e-5)
