@@ -101,8 +101,9 @@ enum {
      * else the row kernel (one wave per G2 row).  Both need ns <= 64 and at
      * most 4 neighbours per site, else the per-element kernel runs.  Steps of
      * systems of that size with real, symmetric hoppings and a Hermitian state
-     * compute one triangle of the pair matrix instead; either flag turns that
-     * off. */
+     * compute one triangle of the pair matrix instead, unless most of their
+     * elements lie in clusters of less than 8 (TPP) or 5 sites (GW, DSL);
+     * either flag turns that off. */
     G1G2_HUB_ROW_KERNEL = 4,    /* Hubbard: row kernel whatever the size          */
     G1G2_HUB_SLICE_KERNEL = 8,  /* Hubbard: slice kernel whatever the size        */
     /* General-basis DSL: build the polarization and particle-hole

@@ -228,6 +228,8 @@ constexpr int TILE_ROW_MIN = 44;   // least ns of the wave-per-row form
 constexpr int TILE_VEC = 384;      // most tiles x ns of an item (its LDS vectors)
 void hub_tile_lists(g1g2_ctx* c, const std::vector<ClusterDesc>& desc, const std::vector<int>& nbr,
                     const std::vector<int>& per_item, std::vector<int>& tiles, std::vector<WorkItem>& work);
+extern "C" int hub_tile_least(int selfenergy);
+extern "C" int hub_tile_pays(int selfenergy, int mixed, int z, long long elems, long long small, long long single);
 extern "C" int hub_tile_per_item(int ns, int most);
 int hub_tile_diags(const g1g2_ctx* c);   // its diagonal tensors per cluster, in units of ns^3
 g1g2_status hub_check_state(g1g2_ctx* c);

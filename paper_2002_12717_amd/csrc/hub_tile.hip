@@ -525,15 +525,42 @@ void launch_tile_se(g1g2_ctx* c, const StageArgs& s, const TileArgs& t) {
 
 }  // namespace
 
+// Least cluster, in sites, that the steps over one triangle pay for, per closure.  Below
+// it the diagonal gather and the vectors of a tile weigh more than the half of the
+// elements they save.  Batches of 1.2 x 2^20 elements in clusters of one size, 8 steps,
+// slice kernel against this one, binary64 / mixed, in us:
+//   TPP  5 sites 1271 / 1185 against 1476 / 1394, 7 sites 1138 / 1033 against 1200 / 1230,
+//        8 sites 990 / 910 against 935 / 920
+//   DSL  4 sites 4830 / 4680 against 6222 / 6280, 5 sites 0.99 and 1.00 of each other
+//   GW   4 sites 5450 / 5280 against 5602 / 5390, 5 sites 1.10 and 1.15 times faster here
+// Second Born and TPH gain at every size (1.06 to 2.3 times).
+extern "C" int hub_tile_least(int selfenergy) {
+    return selfenergy == G1G2_TPP ? 8 : selfenergy == G1G2_DSL || selfenergy == G1G2_GW ? 5 : 1;
+}
+
+// Whether a system of `elems` G2 elements per channel, `small` of them in clusters below
+// hub_tile_least and `single` in clusters of 26 to 36 sites, and at most z neighbours per
+// site takes the triangle: its larger part must pay.  In mixed TPP with more than two
+// neighbours an item of one tile fills its 512 threads worse than the slice kernel's
+// three or four slices do, which tells while the system is a few waves of work (8 steps,
+// slice kernel against this one, in us: 12x3 sites 1326 against 1494, 6x6 1374 / 1484, two
+// of 7x4 1062 / 1163; but three of 7x4 1817 / 1296, 13x3 2019 / 1852, a chain of 33 sites
+// 1122 / 1048).  Host arithmetic with names that tests can find.
+extern "C" int hub_tile_pays(int selfenergy, int mixed, int z, long long elems, long long small, long long single) {
+    if (2 * small > elems) return 0;
+    return !(selfenergy == G1G2_TPP && mixed && z > 2 && elems < (7LL << 18) && 2 * single > elems);
+}
+
 // Tiles of a work item of a cluster of ns sites that holds at most `most` elements: no
 // more than the cluster has, since the launch takes the LDS of its largest item for
 // all (a two-site cluster has three tiles, and room for 192 of them, 61 KB, took
-// every work-group of its batch from four per compute unit to two).  Host
-// arithmetic with a name that tests can find.
+// every work-group of its batch from four per compute unit to two), and in equal
+// shares (seven sites: 14 and 14 tiles rather than 20 and 8).
 extern "C" int hub_tile_per_item(int ns, int most) {
     if (ns >= TILE_ROW_MIN) return 1;
     const int fit = std::min(std::min(most, TILE_ELEMS) / (ns * ns), TILE_VEC / ns);
-    return std::max(1, std::min(fit, ns * (ns + 1) / 2));
+    const int nt = ns * (ns + 1) / 2, items = (nt + std::max(1, fit) - 1) / std::max(1, fit);
+    return (nt + items - 1) / items;   // equal shares
 }
 
 // Tiles and work items of every cluster.  nbr: the host neighbour tables;

@@ -1600,7 +1600,16 @@ g1g2_status hub_setup(g1g2_ctx* c, int ncl, const int* nsv, const double* Uv, co
     // by default; the transposed block is the conjugate only for symmetric hoppings
     std::vector<int> tiles;
     std::vector<WorkItem> twork;
-    const bool tile = slicek && !small1 && realhop && symhop && !(fl & G1G2_HUB_SLICE_KERNEL);
+    long long small = 0, single = 0;
+    int zall = 0;
+    for (const ClusterDesc& d : desc) {
+        const long long n4 = (long long)d.ns * d.ns * d.ns * d.ns;
+        zall = std::max(zall, d.zmax);
+        if (d.ns < hub_tile_least(sel)) small += n4;
+        if (d.ns >= 26 && d.ns <= 36) single += n4;
+    }
+    const bool tile = slicek && !small1 && realhop && symhop && !(fl & G1G2_HUB_SLICE_KERNEL) &&
+                      hub_tile_pays(sel, c->d.precision == G1G2_MIXED, zall, total, small, single);
     if (tile) {
         std::vector<int> per(ncl, SLICE_ELEMS);
         if (chunk_in)

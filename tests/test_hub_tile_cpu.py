@@ -10,4 +10,30 @@ def test_items_hold_no_more_tiles_than_a_cluster_has():
             p = per(ns, most)
             assert 1 <= p <= ns * (ns + 1) // 2
             assert p == 1 or (p * ns * ns <= min(most, 1024) and ns < 44)
-    assert [per(ns, 4096) for ns in (1, 2, 3, 9, 16, 25, 33, 64)] == [1, 3, 6, 12, 4, 1, 1, 1]
+    assert [per(ns, 4096) for ns in (1, 2, 3, 7, 8, 9, 16, 25, 33, 64)] == [1, 3, 6, 14, 12, 12, 4, 1, 1, 1]
+
+
+def test_systems_that_take_the_triangle():
+    """Clusters below the least size of a closure must not hold the larger part, and
+    mixed TPP with more than two neighbours needs 7 x 2^18 elements where clusters of 26
+    to 36 sites hold it."""
+    import ctypes
+
+    from paper_2002_12717_amd import binding as B
+    lib = B.load()
+    lib.hub_tile_pays.argtypes = [ctypes.c_int] * 3 + [ctypes.c_longlong] * 3
+
+    def takes(se, mixed, z, sizes):
+        small = sum(n ** 4 for n in sizes if n < lib.hub_tile_least(se))
+        single = sum(n ** 4 for n in sizes if 26 <= n <= 36)
+        return bool(lib.hub_tile_pays(se, mixed, z, sum(n ** 4 for n in sizes), small, single))
+    for se in (B.SOA, B.TPH):
+        assert takes(se, 0, 2, [2] * 70000) and takes(se, 1, 2, [4] * 5000)
+    assert not takes(B.TPP, 0, 2, [7] * 500) and takes(B.TPP, 0, 2, [8] * 300)
+    assert not takes(B.DSL, 1, 2, [4] * 5000) and takes(B.DSL, 1, 2, [5] * 2000)
+    assert not takes(B.GW, 0, 2, [4] * 5000) and takes(B.GW, 0, 2, [5] * 2000)
+    assert takes(B.TPP, 0, 4, [36] + [4] * 1500)            # the larger part is the 36-site cluster
+    assert not takes(B.TPP, 0, 4, [36] + [4] * 7000)
+    assert not takes(B.TPP, 1, 4, [36]) and takes(B.TPP, 0, 4, [36]) and takes(B.TPP, 1, 2, [36])
+    assert takes(B.TPP, 1, 4, [37]) and takes(B.TPP, 1, 4, [32, 32])
+    assert takes(B.TPP, 1, 4, [16] * 19) and takes(B.TPP, 1, 4, [25] * 3) and takes(B.DSL, 1, 4, [36])
