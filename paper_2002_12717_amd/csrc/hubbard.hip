@@ -995,11 +995,15 @@ __global__ __launch_bounds__(PERSIST_THREADS) void hub_persistent_kernel(Persist
 //     TPP 3720 / 3877, 3975 / 4036; TPH 4575 / 3888, 3930 / 3996
 //   6 sites, 4 neighbours: SOA 3458 / 3123, 4454 / 4550; TPH 4572 / 3901, 4770 / 4880
 // so that binary64 TPH with 6 sites and 3 neighbours stays with hub_persistent_kernel,
-// whose time follows the neighbours.  Buffers as in
+// whose time follows the neighbours.  Filling the slots costs PER = 2 with Z = 4 some 6 us
+// a call (2x3, one step: SOA 51 us against 45, TPP 54 / 48; five steps 119 / 117 and
+// 128 / 126; fifty 878 / 932 and 951 / 1007): calls of fewer than SMALL_STEPS steps stay,
+// too.  Buffers as in
 // hub_persistent_kernel: binary64 alternates between two, mixed precision keeps y
 // in the first and two binary32 stage copies in the second.
 // threads: ns^4 / PER + 2 ns^2 in whole waves, at most three waves per SIMD
 constexpr int small_threads(int per) { return per == 1 ? 704 : 768; }
+constexpr int SMALL_STEPS = 8;
 
 template <int SE, bool MIXED, int PER, int Z>
 __global__ __launch_bounds__(small_threads(PER)) void hub_small_kernel(PersistArgs p) {
@@ -1661,8 +1665,9 @@ bool hub_persistent_ok(const g1g2_ctx* c) {
     return ns * ns * ns * ns <= PERSIST_MAX_G2 && 2 * ns * ns <= PERSIST_G1 && 2 * ns * z <= PERSIST_NBR;
 }
 
+// nsteps: of the whole call (p.nsteps: of this launch)
 template <int SE, bool MIXED>
-void launch_persistent_t(g1g2_ctx* c, const PersistArgs& p) {
+void launch_persistent_t(g1g2_ctx* c, const PersistArgs& p, int64_t nsteps) {
     const HubbardData& H = c->hub;
     const int ns = H.hdesc[0].ns, z = H.hdesc[0].zmax, n2 = ns * ns * ns * ns, n1 = 2 * ns * ns;
     const auto threads = [&](int per) { return ((n2 + per - 1) / per + n1 + 63) / 64 * 64; };
@@ -1676,7 +1681,8 @@ void launch_persistent_t(g1g2_ctx* c, const PersistArgs& p) {
     if (H.realhop && ns <= 5 && z <= 2) small(one(), two());
     else if (H.realhop && ns <= 5 && z <= 4) small(one(), four());
     else if (H.realhop && ns <= 6 && z <= 2) small(two(), two());
-    else if (H.realhop && ns <= 6 && z <= 4 && !(SE == SE_TPH && !MIXED && z == 3)) small(two(), four());
+    else if (H.realhop && ns <= 6 && z <= 4 && nsteps >= SMALL_STEPS && !(SE == SE_TPH && !MIXED && z == 3))
+        small(two(), four());
     else if (H.realhop)
         hipLaunchKernelGGL((hub_persistent_kernel<SE, MIXED, true>), dim3(1), dim3(PERSIST_THREADS), 0, c->stream, p);
     else
@@ -1684,11 +1690,11 @@ void launch_persistent_t(g1g2_ctx* c, const PersistArgs& p) {
 }
 
 template <bool MIXED>
-void launch_persistent(g1g2_ctx* c, const PersistArgs& p) {
+void launch_persistent(g1g2_ctx* c, const PersistArgs& p, int64_t nsteps) {
     switch (c->d.selfenergy) {
-        case G1G2_TPP: launch_persistent_t<SE_TPP, MIXED>(c, p); break;
-        case G1G2_TPH: launch_persistent_t<SE_TPH, MIXED>(c, p); break;
-        default: launch_persistent_t<SE_SOA, MIXED>(c, p); break;
+        case G1G2_TPP: launch_persistent_t<SE_TPP, MIXED>(c, p, nsteps); break;
+        case G1G2_TPH: launch_persistent_t<SE_TPH, MIXED>(c, p, nsteps); break;
+        default: launch_persistent_t<SE_SOA, MIXED>(c, p, nsteps); break;
     }
 }
 
@@ -1698,8 +1704,8 @@ g1g2_status hub_step_persistent(g1g2_ctx* c, double dt, int64_t nsteps) {
     for (int64_t n = 0; n < nsteps;) {
         const int chunk = (int)std::min<int64_t>(nsteps - n, 1024);
         PersistArgs p{H.desc, H.nbr, H.hop, H.d0, H.xdrv, c->y.g1, c->y.g2, dt, chunk, guard_of(c)};
-        if (c->d.precision == G1G2_MIXED) launch_persistent<true>(c, p);
-        else launch_persistent<false>(c, p);
+        if (c->d.precision == G1G2_MIXED) launch_persistent<true>(c, p, nsteps);
+        else launch_persistent<false>(c, p, nsteps);
         HIP_OK(c, hipGetLastError());
         n += chunk;
     }
