@@ -275,7 +275,11 @@ __global__ __launch_bounds__(64 * JEL_WAVES) void jel_stage_kernel(StageArgsJ s)
         }
         cd sb_sum = cmk(0.0, 0.0);
         // the loads of the JEL_PB elements go out together, at clamped indices: behind
-        // the branch of each element they were issued one element at a time
+        // the branch of each element they were issued one element at a time.  What a later
+        // one-element read adds to the chain tells on small grids: stage of 3x3x3 TPH,
+        // binary64 / mixed, 18.3 / 17.9 us with the update's reads behind the arithmetic,
+        // 17.2 / 17.6 before it (16.2 / 16.9 with the running sum and no reads ahead), 4x4x3
+        // 28.3 / 27.8 and 26.3 / 27.0 (27.0 / 27.5), 6x6x6 724 / 742 and 713 / 737 (836 / 747)
         cd avs[JEL_PB], yvs[JEL_PB];
 #pragma unroll
         for (int j = 0; j < JEL_PB; ++j) {
@@ -288,6 +292,13 @@ __global__ __launch_bounds__(64 * JEL_WAVES) void jel_stage_kernel(StageArgsJ s)
             if (!qok || Pv[j] < 0) continue;
             const size_t e = ((size_t)Pv[j] * nb + Pb) * nb + Q;
             const cd av = avs[j];
+            // the sum or the stages that the update reads go out before the arithmetic
+            cd ac, u2, u3;
+            if (!REDUCE && SUM && (MODE == RK_MID || MODE == RK_LAST)) ac = acc[e];
+            if (!REDUCE && !SUM && MODE == RK_LAST) {
+                u2 = r2[e];
+                u3 = r3[e];
+            }
             cd o;
             if (REDUCE) {
                 o = av;
@@ -339,19 +350,12 @@ __global__ __launch_bounds__(64 * JEL_WAVES) void jel_stage_kernel(StageArgsJ s)
                     st_c(out, (long long)e, o);
                 } else if (MODE == RK_MID) {
                     const cd yv = yvs[j];
-                    if (SUM) {
-                        const cd ac = acc[e];
-                        acc[e] = cmk(fma(s.cb, f.x, ac.x), fma(s.cb, f.y, ac.y));
-                    }
+                    if (SUM) acc[e] = cmk(fma(s.cb, f.x, ac.x), fma(s.cb, f.y, ac.y));
                     o = cmk(fma(s.cc, f.x, yv.x), fma(s.cc, f.y, yv.y));
                     st_c(out, (long long)e, o);
                 } else {
-                    if (SUM) {
-                        const cd ac = acc[e];
-                        o = cmk(fma(s.cb, f.x, ac.x), fma(s.cb, f.y, ac.y));
-                    } else {
-                        o = rk_close(yvs[j], r2[e], r3[e], av, f, s.cb);
-                    }
+                    o = SUM ? cmk(fma(s.cb, f.x, ac.x), fma(s.cb, f.y, ac.y))
+                            : rk_close(yvs[j], u2, u3, av, f, s.cb);
                     st_c(out, (long long)e, o);
                 }
                 o = stored_value<TO>(o);                    // as stored (rounded when binary32)
