@@ -42,9 +42,6 @@ PEAK_HBM = 8000.0          # GB/s
 TRAFFIC = {
     "gen_main/f64": {"bytes": 75.9e6, "src": "general.hip", "sha1": "10279bdbe35c"},
     "gen_main/f32": {"bytes": 50.7e6, "src": "general.hip", "sha1": "10279bdbe35c"},
-    "hub_stage/2d": {"bytes": 2.385e9, "src": "hubbard.hip", "sha1": "94601047d47b"},
-    "hub_stage/2d/mixed": {"bytes": 1.634e9, "src": "hubbard.hip", "sha1": "94601047d47b"},
-    "hub_stage/2d/tpp": {"bytes": 2.443e9, "src": "hubbard.hip", "sha1": "94601047d47b"},
     "jel_stage/gw": {"bytes": 2.03e9, "src": "jellium.hip", "sha1": "370a4e568f25"},
     "jel_stage/gw/mixed": {"bytes": 1.70e9, "src": "jellium.hip", "sha1": "370a4e568f25"},
     "jel_stage/tpp": {"bytes": 4.651e9, "src": "jellium.hip", "sha1": "370a4e568f25"},
@@ -81,6 +78,12 @@ TRIANGLE_BYTES = 28.0
 
 # Hubbard G2 channels per selfenergy: GW and DSL propagate three
 HUB_CHANNELS = {"soa": 1, "tpp": 1, "tph": 1, "gw": 3, "dsl": 3}
+
+
+def hub_kernel(prof: dict) -> str:
+    """The stage kernel that a profile of Hubbard steps holds: over one triangle of
+    the pair matrix, or over every element."""
+    return "hub_tile" if "hub_tile" in prof else "hub_stage"
 
 
 def soa_flops(nb: int) -> dict:
@@ -442,10 +445,11 @@ def run_hubbard(args, torch, B, kind):
     persistent = path == "hub_persistent"
     ms_step = ms / args.steps
     n4 = float(ns) ** 4
-    tot_ms, cnt = prof["hub_stage"]
-    # algorithmic bytes per G2 element and launch (TRIANGLE_BYTES at 8x8); Hubbard GW and DSL
-    # propagate three G2 channels
-    b64, b32 = (TRIANGLE_BYTES, TRIANGLE_BYTES) if kind == "hubbard_2d" else (64.0, 52.0)
+    kern = hub_kernel(prof)
+    tot_ms, cnt = prof[kern]
+    # algorithmic bytes per G2 element and launch; Hubbard GW and DSL propagate three
+    # G2 channels
+    b64, b32 = (TRIANGLE_BYTES, TRIANGLE_BYTES) if kern == "hub_tile" else (64.0, 52.0)
     bytes_per_launch = b64 * n4 * HUB_CHANNELS[se]
     achieved = bytes_per_launch * cnt / (tot_ms * 1e-3) / 1e9
     name = f"1D chain, {ns} sites" if kind == "hubbard_chain" else "2D 8x8 open cluster, driven"
@@ -453,11 +457,11 @@ def run_hubbard(args, torch, B, kind):
               "ns": ns, "U": system.U, "dt": system.dt, "selfenergy": se.upper(),
               "parallelism": "single GPU"}
     out = base_line(args, 1e3 / ms_step, ms_step, "f64", config)
-    stage_roof = {"kernel": "hub_stage", "bound": "hbm", "achieved": round(achieved, 2),
+    stage_roof = {"kernel": kern, "bound": "hbm", "achieved": round(achieved, 2),
                   "peak": PEAK_HBM, "unit": "GB/s", "frac": round(achieved / PEAK_HBM, 4),
                   # the counters were taken on the SOA and TPP instantiations
-                  "traffic": (traffic("hub_stage/2d") if se == "soa" else traffic("hub_stage/2d/tpp")
-                              if se == "tpp" else None) if kind == "hubbard_2d" else None,
+                  "traffic": (traffic("hub_tile/2d") if se == "soa" else traffic("hub_tile/2d/tpp")
+                              if se == "tpp" else None) if kern == "hub_tile" else None,
                   "kernel_ms_avg": round(tot_ms / cnt, 6),
                   "bytes_per_launch": bytes_per_launch, "launches": cnt}
     out.update({
@@ -473,16 +477,16 @@ def run_hubbard(args, torch, B, kind):
     # mixed precision: binary32 G2 stage copies
     mx_ms, mx_prof, mx_obs, g1_mx, _ = run(B.MIXED)
     mx_step = mx_ms / args.steps
-    mx_tot, mx_cnt = mx_prof["hub_stage"]
+    mx_tot, mx_cnt = mx_prof[kern]
     mx_ach = b32 * n4 * HUB_CHANNELS[se] * mx_cnt / (mx_tot * 1e-3) / 1e9
     out["mixed"] = {"dtype": "f64 state, f32 G2 stage copies", "value": round(1e3 / mx_step, 3),
                     "ms_per_step": round(mx_step, 6), "speedup_vs_fp64": round(ms_step / mx_step, 3),
                     "err_G1_vs_fp64": float(np.abs(g1_mx - g1_64).max() / np.abs(g1_64).max()),
                     "err_E_vs_fp64": abs(mx_obs["E_tot"] - obs["E_tot"]) / max(abs(obs["E_tot"]), 1.0),
-                    "roofline": {"kernel": "hub_stage", "achieved": round(mx_ach, 2), "peak": PEAK_HBM,
+                    "roofline": {"kernel": kern, "achieved": round(mx_ach, 2), "peak": PEAK_HBM,
                                  "unit": "GB/s", "frac": round(mx_ach / PEAK_HBM, 4),
-                                 "traffic": traffic("hub_stage/2d/mixed")
-                                 if kind == "hubbard_2d" and se == "soa" else None}}
+                                 "traffic": traffic("hub_tile/2d/mixed")
+                                 if kern == "hub_tile" and se == "soa" else None}}
     if not args.no_cpu_baseline:
         out["cpu_baseline"] = cpu_baseline_hubbard(system, selfenergy=se)
     return out
@@ -734,13 +738,15 @@ def run_batch(args, torch, B):
     f64, mx = res["fp64"], res["mixed"]
     ms_step = f64["ms"] / args.steps
     mx_step = mx["ms"] / args.steps
-    tot_ms, cnt = f64["prof"]["hub_stage"]
-    # algorithmic bytes per G2 element and launch: stages over one triangle
+    kern = hub_kernel(f64["prof"])
+    tot_ms, cnt = f64["prof"][kern]
+    # algorithmic bytes per G2 element and launch
+    b64, b32 = (TRIANGLE_BYTES, TRIANGLE_BYTES) if kern == "hub_tile" else (64.0, 52.0)
     nch = HUB_CHANNELS[se]
-    bytes_per_launch = TRIANGLE_BYTES * n4 * nch
+    bytes_per_launch = b64 * n4 * nch
     achieved = bytes_per_launch * cnt / (tot_ms * 1e-3) / 1e9
-    mx_tot, mx_cnt = mx["prof"]["hub_stage"]
-    mx_bytes = TRIANGLE_BYTES * n4 * nch
+    mx_tot, mx_cnt = mx["prof"][kern]
+    mx_bytes = b32 * n4 * nch
     mx_ach = mx_bytes * mx_cnt / (mx_tot * 1e-3) / 1e9
     err_g1 = max(float(np.abs(m - f).max() / np.abs(f).max()) for m, f in zip(mx["g1"], f64["g1"]))
     err_e = max(abs(m["E_tot"] - f["E_tot"]) / max(abs(f["E_tot"]), 1.0)
@@ -753,7 +759,7 @@ def run_batch(args, torch, B):
               "parallelism": "single GPU"}
     out = base_line(args, 1e3 / ms_step, ms_step, "f64", config)
     out.update({
-        "roofline": {"kernel": "hub_stage", "bound": "hbm", "achieved": round(achieved, 2),
+        "roofline": {"kernel": kern, "bound": "hbm", "achieved": round(achieved, 2),
                      "peak": PEAK_HBM, "unit": "GB/s", "frac": round(achieved / PEAK_HBM, 4),
                      "traffic": None, "kernel_ms_avg": round(tot_ms / cnt, 6),
                      "bytes_per_launch": bytes_per_launch, "launches": cnt},
@@ -762,7 +768,7 @@ def run_batch(args, torch, B):
                   "value": round(1e3 / mx_step, 3), "ms_per_step": round(mx_step, 6),
                   "speedup_vs_fp64": round(ms_step / mx_step, 3),
                   "err_G1_vs_fp64": err_g1, "err_E_vs_fp64": err_e,
-                  "roofline": {"kernel": "hub_stage", "achieved": round(mx_ach, 2), "peak": PEAK_HBM,
+                  "roofline": {"kernel": kern, "achieved": round(mx_ach, 2), "peak": PEAK_HBM,
                                "unit": "GB/s", "frac": round(mx_ach / PEAK_HBM, 4),
                                "bytes_per_launch": mx_bytes},
                   "kernels": kernel_table(mx["prof"])},
@@ -855,8 +861,9 @@ def run_adjoint(args, torch, B):
     rev_ms = (t3 - t1) * 1e3 / 2
     total_ms = fwd_ms + 2 * rev_ms
     ms_step = total_ms / args.steps
-    tot_ms, cnt = prof["hub_stage"]
-    bytes_per_launch = TRIANGLE_BYTES * float(ns) ** 4
+    kern = hub_kernel(prof)
+    tot_ms, cnt = prof[kern]
+    bytes_per_launch = (TRIANGLE_BYTES if kern == "hub_tile" else 64.0) * float(ns) ** 4
     achieved = bytes_per_launch * cnt / (tot_ms * 1e-3) / 1e9
     # adj_slice_red, the reverse sweep's dominant kernel: per G2 element it reads
     # the cotangent, the stage state, lambda and the running sum and writes the
@@ -879,7 +886,7 @@ def run_adjoint(args, torch, B):
                      "peak": PEAK_HBM, "unit": "GB/s", "frac": round(a_ach / PEAK_HBM, 4),
                      "traffic": None, "kernel_ms_avg": round(a_tot / a_cnt, 6),
                      "bytes_per_launch": a_bytes, "launches": a_cnt},
-        "forward_roofline": {"kernel": "hub_stage", "bound": "hbm", "achieved": round(achieved, 2),
+        "forward_roofline": {"kernel": kern, "bound": "hbm", "achieved": round(achieved, 2),
                              "peak": PEAK_HBM, "unit": "GB/s", "frac": round(achieved / PEAK_HBM, 4),
                              "kernel_ms_avg": round(tot_ms / cnt, 6), "bytes_per_launch": bytes_per_launch,
                              "launches": cnt},

@@ -226,17 +226,19 @@ g1g2_status g1g2_rhs_noalloc(g1g2_ctx* ctx, double t, const void* G1, const void
 g1g2_status g1g2_step_rk4(g1g2_ctx* ctx, double dt, int64_t nsteps);
 
 /* Which kernels g1g2_step_rk4 uses for this context, as decided by the
- * library (sizes, selfenergy, flags, drive and switching ramp as they are
- * now): GENERAL (the general-basis matrix-core stages), HUB_PERSISTENT
- * (whole steps of one small Hubbard cluster in one work-group), HUB_SLICE,
- * HUB_ROW or HUB_ELEMENT (one launch per Runge-Kutta stage), JELLIUM.      */
+ * library (sizes, selfenergy, flags, state, drive and switching ramp as they
+ * are now): GENERAL (the general-basis matrix-core stages), HUB_PERSISTENT
+ * (whole steps of one small Hubbard cluster in one work-group), HUB_TRIANGLE
+ * (stages over one triangle of the pair matrix), HUB_SLICE, HUB_ROW or
+ * HUB_ELEMENT (one launch per Runge-Kutta stage), JELLIUM.                   */
 enum {
     G1G2_PATH_GENERAL = 0,
     G1G2_PATH_HUB_PERSISTENT = 1,
     G1G2_PATH_HUB_SLICE = 2,
     G1G2_PATH_HUB_ROW = 3,
     G1G2_PATH_HUB_ELEMENT = 4,
-    G1G2_PATH_JELLIUM = 5
+    G1G2_PATH_JELLIUM = 5,
+    G1G2_PATH_HUB_TRIANGLE = 6
 };
 g1g2_status g1g2_step_path(const g1g2_ctx* ctx, int32_t* path);
 
@@ -293,8 +295,9 @@ g1g2_status g1g2_set_switch(g1g2_ctx* ctx, double t_on, double tau);
  * [2][ns][ns]; G2(0) = 0.  chunk[c] sets the G2 elements handled by one
  * work-group of cluster c (NULL or 0: default), e.g. from an autotuning
  * table: chunk > 0 is, for the slice kernel, the most G2 elements one work
- * item stages (whole (i,j) slices, at least one, at most 4096 elements), and,
- * for the row kernel, the granularity of its work (one wave per G2 row
+ * item stages (whole (i,j) slices, at least one, at most 4096 elements), for
+ * the stages over one triangle the most elements of an item that packs the
+ * blocks of a cluster below 44 sites (at most 1024), and, for the row kernel, the granularity of its work (one wave per G2 row
  * A[i][j][k][:], rounded to whole wave units of rows); chunk < 0 selects the
  * per-element kernel with |chunk| elements per work-group (any negative entry
  * selects the per-element kernel for the whole batch).

@@ -465,6 +465,7 @@ g1g2_status g1g2_step_path(const g1g2_ctx* c, int32_t* path) {
     if (c->d.basis == G1G2_GENERAL) *path = G1G2_PATH_GENERAL;
     else if (c->d.basis == G1G2_JELLIUM) *path = G1G2_PATH_JELLIUM;
     else if (hub_persistent_ok(c)) *path = G1G2_PATH_HUB_PERSISTENT;
+    else if (hub_tile_ok(c)) *path = G1G2_PATH_HUB_TRIANGLE;
     else if (c->hub.slices) *path = G1G2_PATH_HUB_SLICE;
     else if (c->hub.rows) *path = G1G2_PATH_HUB_ROW;
     else *path = G1G2_PATH_HUB_ELEMENT;

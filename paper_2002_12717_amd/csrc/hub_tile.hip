@@ -661,7 +661,7 @@ g1g2_status hub_tile_stage(g1g2_ctx* c, int mode, double t, const Regs& in, cons
         default: launch_tile_se<RK_LAST>(c, s, ta); break;
     }
     HIP_OK(c, hipGetLastError());
-    prof_mark(c, "hub_stage");
+    prof_mark(c, "hub_tile");
     return G1G2_OK;
 }
 

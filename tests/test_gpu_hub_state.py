@@ -223,3 +223,44 @@ def test_unequal_hoppings_are_evolved_in_full(lib):
         out.append(p.get_state())
         p.close()
     _equal(*out)
+
+
+def test_step_path_and_profile_name_the_kernels(lib):
+    """step_path answers hub_triangle exactly where steps run over one triangle, and the
+    profile counts their stages under a name of their own; a gradient that keeps its
+    states runs no stage in its reverse sweep."""
+    from paper_2002_12717_amd import binding as B
+    r = rng(608)
+    h0, g1 = _system(r)
+    sym, bad = _states(r)
+    p = B.Propagator(B.HUBBARD, B.SOA, NS, h0, g1, U=1.1)
+    assert p.step_path() == "hub_triangle"
+    prof = p.profile(0.01, 2)
+    assert prof["hub_tile"][1] == 8 and "hub_stage" not in prof
+    p.set_state(g1, bad)
+    assert p.step_path() == "hub_slice"
+    prof = p.profile(0.01, 2)
+    assert prof["hub_stage"][1] == 8 and "hub_tile" not in prof
+    p.set_state(g1, sym)
+    assert p.step_path() == "hub_triangle"
+    p.set_h0(_complex_hopping(h0))
+    assert p.step_path() == "hub_slice"
+    p.set_h0(h0)
+    assert p.step_path() == "hub_triangle"
+    a, b = r.uniform(-1, 1, NS), r.uniform(-1, 1, NS)
+    p.forward_checkpointed(0.01, 4)
+    assert not {"hub_tile", "hub_stage"} & set(p.profile_adjoint(a, b))
+    p.set_state(g1, sym)
+    p.forward_checkpointed(0.01, 4, 2)
+    assert p.profile_adjoint(a, b)["hub_tile"][1] == 14      # two segments of two steps, the last stage left out
+    p.set_state(g1, bad)
+    p.forward_checkpointed(0.01, 4)
+    assert p.profile_adjoint(a, b)["hub_stage"][1] > 0
+    p.close()
+    for flags, path in ((B.HUB_SLICE_KERNEL, "hub_slice"), (B.HUB_ROW_KERNEL, "hub_row")):
+        q = B.Propagator(B.HUBBARD, B.SOA, NS, h0, g1, U=1.1, flags=flags)
+        assert q.step_path() == path
+        q.close()
+    b4 = B.Batch(B.TPP, [NS, 3], [1.0, 1.0], [h0, _system(r, 3)[0]], [g1, _system(r, 3)[1]])
+    assert b4.step_path() == "hub_triangle"
+    b4.close()

@@ -37,3 +37,14 @@ def test_systems_that_take_the_triangle():
     assert not takes(B.TPP, 1, 4, [36]) and takes(B.TPP, 0, 4, [36]) and takes(B.TPP, 1, 2, [36])
     assert takes(B.TPP, 1, 4, [37]) and takes(B.TPP, 1, 4, [32, 32])
     assert takes(B.TPP, 1, 4, [16] * 19) and takes(B.TPP, 1, 4, [25] * 3) and takes(B.DSL, 1, 4, [36])
+
+
+def test_binding_names_every_step_path():
+    import os
+    import re
+
+    from paper_2002_12717_amd import binding as B
+    root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+    with open(os.path.join(root, "include", "g1g2.h")) as f:
+        paths = dict(re.findall(r"G1G2_PATH_(\w+) = (\d+)", f.read()))
+    assert {int(v): k.lower() for k, v in paths.items()} == B.PATHS
