@@ -19,8 +19,6 @@ import os
 import sys
 import time
 
-import numpy as np
-
 PKG = os.path.dirname(os.path.abspath(__file__))
 TABLE = os.path.join(PKG, "tuning", "hubbard_batch.json")
 CLASSES = [(1, 16), (17, 25), (26, 49)]          # ns ranges (inclusive)
@@ -67,14 +65,21 @@ def flags_for(table=None) -> int:
     return {"slice": B.HUB_SLICE_KERNEL, "row": B.HUB_ROW_KERNEL}.get(table.get("kernel"), 0)
 
 
+def library_takes_slices(B, ns, selfenergy) -> bool:
+    """Whether a batch is large enough for the library to choose by itself between the
+    triangle and the slice kernel (2^20 G2 elements, GW and DSL with three channels);
+    it takes smaller ones to the row kernel."""
+    channels = 3 if selfenergy in (B.GW, B.DSL) else 1
+    return channels * sum(n ** 4 for n in ns) >= 1 << 20
+
+
 def make_batch(B, clusters, selfenergy, stream=0, precision=None, table=None):
     """g1g2_batch_init of the clusters with the stage kernel and the per-class
     chunks of the tuning table (the stored one by default)."""
     table = load_table() if table is None else table
     ns = [c.ns for c in clusters]
     flags = flags_for(table)
-    if table.get("kernel") == "triangle" and not (
-            sum(n ** 4 for n in ns) >= 1 << 20 and all(np.isrealobj(c.h0) or not np.any(np.imag(c.h0)) for c in clusters)):
+    if table.get("kernel") == "triangle" and not library_takes_slices(B, ns, selfenergy):
         flags = B.HUB_SLICE_KERNEL                # the next best kernel of the tuned batch
     return B.Batch(selfenergy, ns, [c.U for c in clusters], [c.h0 for c in clusters],
                    [c.g1 for c in clusters], chunk=chunks_for(ns, table), stream=stream,

@@ -48,3 +48,27 @@ def test_binding_names_every_step_path():
     with open(os.path.join(root, "include", "g1g2.h")) as f:
         paths = dict(re.findall(r"G1G2_PATH_(\w+) = (\d+)", f.read()))
     assert {int(v): k.lower() for k, v in paths.items()} == B.PATHS
+
+
+def test_tuned_batches_count_every_channel():
+    """make_batch leaves the choice to the library where it takes slices or the triangle by
+    itself: 2^20 elements with the three channels of GW and DSL counted, whatever the
+    hoppings."""
+    from types import SimpleNamespace
+
+    import numpy as np
+
+    from paper_2002_12717_amd import autotune
+    from paper_2002_12717_amd import binding as B
+    seen = []
+    fake = SimpleNamespace(GW=B.GW, DSL=B.DSL, FP64=B.FP64, HUB_SLICE_KERNEL=B.HUB_SLICE_KERNEL,
+                           Batch=lambda *a, flags, **k: seen.append(flags))
+
+    def flags(se, ns, n, h=np.zeros(1)):
+        cl = [SimpleNamespace(ns=ns, U=1.0, h0=h, g1=None)] * n
+        autotune.make_batch(fake, cl, se, table={"kernel": "triangle"})
+        return seen.pop()
+    assert flags(B.TPP, 16, 16) == 0 and flags(B.TPP, 16, 15) == B.HUB_SLICE_KERNEL
+    for se in (B.GW, B.DSL):
+        assert flags(se, 16, 6) == 0 and flags(se, 16, 5) == B.HUB_SLICE_KERNEL
+    assert flags(B.TPP, 16, 16, np.full(1, 1j)) == 0
