@@ -40,12 +40,20 @@ PEAK_HBM = 8000.0          # GB/s
 # counters were taken (source_hash below: the whole file, so that a change of
 # the kernel or of how it is launched voids it).
 TRAFFIC = {
-    "gen_main/f64": {"bytes": 75.9e6, "src": "general.hip", "sha1": "10279bdbe35c"},
-    "gen_main/f32": {"bytes": 50.7e6, "src": "general.hip", "sha1": "10279bdbe35c"},
-    "jel_stage/gw": {"bytes": 2.03e9, "src": "jellium.hip", "sha1": "370a4e568f25"},
-    "jel_stage/gw/mixed": {"bytes": 1.70e9, "src": "jellium.hip", "sha1": "370a4e568f25"},
-    "jel_stage/tpp": {"bytes": 4.651e9, "src": "jellium.hip", "sha1": "370a4e568f25"},
-    "jel_lad/tpp": {"bytes": 0.968e9, "src": "jellium.hip", "sha1": "370a4e568f25"},
+    "gen_pair_gemm/gw64/f64": {"bytes": 3.049e9, "src": "pair.hip", "sha1": "281143e36a0e"},
+    "gen_pair_gemm/gw64/f32": {"bytes": 2.386e9, "src": "pair.hip", "sha1": "281143e36a0e"},
+    "gen_gemm/tpp64/f64": {"bytes": 1.411e9, "src": "pair.hip", "sha1": "281143e36a0e"},
+    "gen_gemm/tpp64/f32": {"bytes": 2.533e9, "src": "pair.hip", "sha1": "281143e36a0e"},
+    "gen_main/f64": {"bytes": 75.9e6, "src": "general.hip", "sha1": "f7c62d6db8f9"},
+    "gen_main/f32": {"bytes": 50.7e6, "src": "general.hip", "sha1": "f7c62d6db8f9"},
+    "hub_tile/2d": {"bytes": 1.220e9, "src": "hub_tile.hip", "sha1": "1d87cdbb0fd5"},
+    "hub_tile/2d/mixed": {"bytes": 0.913e9, "src": "hub_tile.hip", "sha1": "1d87cdbb0fd5"},
+    "hub_tile/2d/tpp": {"bytes": 1.357e9, "src": "hub_tile.hip", "sha1": "1d87cdbb0fd5"},
+    "adj_slice_red": {"bytes": 2.405e9, "src": "adjoint.hip", "sha1": "c8ff37dd02a6"},
+    "jel_stage/gw": {"bytes": 1.694e9, "src": "jellium.hip", "sha1": "dc985f73a6d8"},
+    "jel_stage/gw/mixed": {"bytes": 1.710e9, "src": "jellium.hip", "sha1": "dc985f73a6d8"},
+    "jel_stage/tpp": {"bytes": 3.999e9, "src": "jellium.hip", "sha1": "dc985f73a6d8"},
+    "jel_lad/tpp": {"bytes": 0.968e9, "src": "jellium.hip", "sha1": "dc985f73a6d8"},
 }
 
 
@@ -343,6 +351,7 @@ def run_general(args, torch, B, se="soa", accuracy=True, steps=None, warmup=None
     ms_step = f64["ms"] / steps
     mx_step = mx["ms"] / steps
     dom = "gen_main" if not gw else "gen_gemm" if se == "tpp" else "gen_pair_gemm"
+    counted = {"soa": "gen_main", "gw": "gen_pair_gemm/gw64", "tpp": "gen_gemm/tpp64"}.get(se)
     tot_ms, cnt = f64["prof"][dom]
     achieved = fl[dom] * cnt / (tot_ms * 1e-3) / 1e12
     rhs_flops = fl["total"] if gw else fl["soa_total"]
@@ -360,7 +369,7 @@ def run_general(args, torch, B, se="soa", accuracy=True, steps=None, warmup=None
         "g2_rhs_tflops": round(4 * rhs_flops / (ms_step * 1e-3) / 1e12, 3),
         "roofline": {"kernel": dom, "bound": "mfma", "achieved": round(achieved, 3),
                      "peak": PEAK_FP64_MFMA, "unit": "TFLOP/s", "frac": round(achieved / PEAK_FP64_MFMA, 4),
-                     "traffic": None if gw else traffic("gen_main/f64"),
+                     "traffic": traffic(f"{counted}/f64"),
                      "kernel_ms_avg": round(tot_ms / cnt, 6),
                      "flop_per_launch": fl[dom], "launches": cnt},
         "kernels": kernel_table(f64["prof"]),
@@ -369,7 +378,7 @@ def run_general(args, torch, B, se="soa", accuracy=True, steps=None, warmup=None
                   "g2_rhs_tflops": round(4 * rhs_flops / (mx_step * 1e-3) / 1e12, 3),
                   "roofline": {"kernel": dom, "achieved": round(mx_ach, 3), "peak": PEAK_FP32_MFMA,
                                "unit": "TFLOP/s", "frac": round(mx_ach / PEAK_FP32_MFMA, 4),
-                               "traffic": None if gw else traffic("gen_main/f32")},
+                               "traffic": traffic(f"{counted}/f32")},
                   "kernels": kernel_table(mx["prof"])},
     })
     if gw:
@@ -884,7 +893,7 @@ def run_adjoint(args, torch, B):
         "forward_ms": round(fwd_ms, 3), "reverse_ms_per_loss": round(rev_ms, 3),
         "roofline": {"kernel": "adj_slice_red", "bound": "hbm", "achieved": round(a_ach, 2),
                      "peak": PEAK_HBM, "unit": "GB/s", "frac": round(a_ach / PEAK_HBM, 4),
-                     "traffic": None, "kernel_ms_avg": round(a_tot / a_cnt, 6),
+                     "traffic": traffic("adj_slice_red"), "kernel_ms_avg": round(a_tot / a_cnt, 6),
                      "bytes_per_launch": a_bytes, "launches": a_cnt},
         "forward_roofline": {"kernel": kern, "bound": "hbm", "achieved": round(achieved, 2),
                              "peak": PEAK_HBM, "unit": "GB/s", "frac": round(achieved / PEAK_HBM, 4),
